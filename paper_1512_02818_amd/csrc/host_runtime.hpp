@@ -32,6 +32,7 @@ constexpr double kBridgeSkip = 24.953298500158186;     // 36 ln 2: p < 2^-36 ski
 constexpr uint64_t kDefaultMaxSteps = 1ull << 26;
 constexpr uint64_t kScratchSlots = 1ull << 27;         // record slots per launch
 constexpr uint64_t kMaxLaunchSlots = 1ull << 31;
+constexpr double kFp64TrigRevolutions = 1 << 25;       // arguments that the FP64 walks reduce themselves (a margin of 8 to 2^31)
 constexpr double kHwTrigRevolutions = 256.0;           // input range of the FP32 hardware sine / cosine
 
 struct DeviceBuffer {

@@ -51,7 +51,6 @@ __device__ __forceinline__ void gstore(T *p, T v)
 
 constexpr float kLn2f = 0.6931471805599453f;
 constexpr float kLog2ef = 1.4426950408889634f;
-constexpr double kTwoPi = 6.283185307179586476925286766559;
 
 struct Block4 {
     uint32_t w0, w1, w2, w3;
@@ -162,6 +161,18 @@ __device__ __forceinline__ double madd(double a, double b, double c) { return __
 template <class T>
 struct Arith;
 
+// What a walk keeps in registers for its elementary functions: in FP64 the
+// coefficients of sine and cosine, which a step uses three times.
+template <class T>
+struct MathOf {
+    __device__ __forceinline__ void init() {}
+};
+template <>
+struct MathOf<double> {
+    double S[6], C[6];
+    __device__ __forceinline__ void init();
+};
+
 // FP32 path arithmetic: 24-bit uniforms, hardware transcendentals.
 template <>
 struct Arith<float> {
@@ -178,28 +189,32 @@ struct Arith<float> {
     {
         return __builtin_amdgcn_sqrtf(-2.0f * kLn2f * __builtin_amdgcn_logf(unif(w)));
     }
-    __device__ static __forceinline__ void box_muller(uint32_t a, uint32_t b, float &n0, float &n1)
+    __device__ static __forceinline__ void box_muller(const MathOf<float> &, uint32_t a, uint32_t b, float &n0, float &n1)
     {
         const float r = radius(a);
         const float t = unif(b);  // revolutions
         n0 = r * __builtin_amdgcn_cosf(t);
         n1 = r * __builtin_amdgcn_sinf(t);
     }
-    __device__ static __forceinline__ float box_muller_cos(uint32_t a, uint32_t b)
+    __device__ static __forceinline__ float box_muller_cos(const MathOf<float> &, uint32_t a, uint32_t b)
     {
         return radius(a) * __builtin_amdgcn_cosf(unif(b));
     }
     // k and ph are in revolutions; the hardware sine and cosine reduce any
     // argument within +-256 revolutions themselves.
-    __device__ static __forceinline__ void trig(const DevTrig<float> &t, int d, float x, float &s,
-                                                float &c)
+    template <bool BIG>
+    __device__ static __forceinline__ void trig(const MathOf<float> &, const DevProblem<float> &P, int m, int d, float x,
+                                                float &s, float &c)
     {
+        const DevTrig<float> &t = P.trig[m];
         const float rev = fmaf(t.k[d], x, t.ph[d]);
         s = __builtin_amdgcn_sinf(rev);
         c = __builtin_amdgcn_cosf(rev);
     }
-    __device__ static __forceinline__ float sine(const DevTrig<float> &t, int d, float x)
+    template <bool BIG>
+    __device__ static __forceinline__ float sine(const MathOf<float> &, const DevProblem<float> &P, int m, int d, float x)
     {
+        const DevTrig<float> &t = P.trig[m];
         return __builtin_amdgcn_sinf(fmaf(t.k[d], x, t.ph[d]));
     }
     __device__ static __forceinline__ float exp_neg(float x)
@@ -209,38 +224,199 @@ struct Arith<float> {
     __device__ static __forceinline__ float sqrt_(float x) { return __builtin_amdgcn_sqrtf(x); }
 };
 
-// FP64 path arithmetic: 32-bit uniforms, correctly rounded-ish library calls.
+// FP64 path arithmetic: 32-bit uniforms. The elementary functions are written
+// for the arguments that a walk gives them (a uniform of 32 bits, a quarter
+// turn with an exact remainder, the trig terms' arguments over the domain, a
+// bridge exponent), which leaves out the library's general cases. FP64 walks
+// are bound by vector issue, and these functions are most of a step: 18 nodes
+// x 200,000 paths on the unit square (h = 1e-3) take 6.6 ms, 9.1 ms with the
+// library's functions; 1,792 nodes x 256 paths on [0, 4]^2 16.4 ms, before
+// 24.3 ms. Polynomials are minimax in relative
+// error (Remez exchange in 50 digits), so each function is within 1.2 units in
+// the last place of its argument's exact value.
+// Their coefficients come from constant memory by scalar loads at each use:
+// as literals the compiler keeps all of them for the whole walk loop in scalar
+// registers, which do not hold them, and each use then reads its spilled
+// halves back through v_readlane (170 spilled registers).
+__constant__ __attribute__((aligned(64))) const double kFp64Tab[40] = {
+    // S of sin, highest power first; C of cos
+    0x1.5d8fa2e5c73e7p-33, -0x1.ae5e59f4a6204p-26, 0x1.71de356710e0dp-19, -0x1.a01a019bfd15ep-13,
+    0x1.111111110f7cap-7, -0x1.5555555555548p-3, -0x1.8ff9ad8c46497p-37, 0x1.1eea890e2e204p-29,
+    -0x1.27e4f903ab84cp-22, 0x1.a01a019e24894p-16, -0x1.6c16c16c16131p-10, 0x1.5555555555553p-5,
+    // 2 / pi; -pi / 2 in two parts; 2 pi 2^-32
+    0x1.45f306dc9c883p-1, -0x1.921fb54442d18p+0, -0x1.1a62633145c07p-54, 0x1.921fb54442d18p-30,
+    // L of ln; ln 2 in two parts
+    0x1.2f048c754a96ep-3, 0x1.39a1d39b3401dp-3, 0x1.74663dcc62912p-3, 0x1.c71c520f847cdp-3,
+    0x1.24924941e89a6p-2, 0x1.999999997fe64p-2, 0x1.5555555555592p-1, 0x1.62e42fefa39efp-1,
+    0x1.abc9e3b39803fp-56, 0.0, 0.0, 0.0,
+    // E of exp; -log2 e; (ln 2 above)
+    0x1.af632ad6abee8p-26, 0x1.28b410d73d492p-22, 0x1.71ddf6b3f10d1p-19, 0x1.a01993b37a9cap-16,
+    0x1.a01a01b00c2c6p-13, 0x1.6c16c18601e8cp-10, 0x1.111111110f803p-7, 0x1.55555555503e3p-5,
+    0x1.5555555555558p-3, 0x1.0000000000009p-1, -0x1.71547652b82fep+0, 0.0};
+
+struct Fp64Math {
+    using Tab = const __attribute__((address_space(4))) double *;
+    // The table's entries from `at` on, opaque to the optimiser.
+    __device__ static __forceinline__ Tab tab(int at)
+    {
+        Tab t = (Tab)(kFp64Tab + at);
+        asm volatile("" : "+s"(t));
+        return t;
+    }
+    // sin x and cos x for |x| <= pi / 4:  x + x z S(z), 1 - z / 2 + z^2 C(z),
+    // z = x^2 (S to 2^-57.9, C to 2^-62.1).
+    // The angle is x + dx, dx below a unit in the last place of x.
+    __device__ static __forceinline__ void sincos_octant(const MathOf<double> &m, double x, double dx, double &s,
+                                                         double &c)
+    {
+        const double z = x * x;
+        double S = m.S[0], C = m.C[0];
+#pragma unroll
+        for (int i = 1; i < 6; ++i) {
+            S = madd(S, z, m.S[i]);
+            C = madd(C, z, m.C[i]);
+        }
+        s = x + madd(x * z, S, dx);
+        const double w = madd(-0.5, z, 1.0);
+        c = w + madd(z * z, C, madd(-x, dx, madd(-0.5, z, 1.0 - w)));  // 1 - w - z / 2: what rounding w left out
+    }
+    // Of x + q pi / 2 from those of x.
+    __device__ static __forceinline__ void quadrant(uint32_t q, double &s, double &c)
+    {
+        const double a = (q & 1u) ? c : s, b = (q & 1u) ? s : c;
+        s = sign_flip(a, q << 30);
+        c = sign_flip(b, (q + 1u) << 30);
+    }
+    // v with its sign changed if bit 31 of `bit` is set.
+    __device__ static __forceinline__ double sign_flip(double v, uint32_t bit)
+    {
+        const uint64_t b = (uint64_t)__double_as_longlong(v);
+        const uint32_t hi = (uint32_t)(b >> 32) ^ (bit & 0x80000000u);
+        return __longlong_as_double((long long)(((uint64_t)hi << 32) | (uint32_t)b));
+    }
+    // sin and cos of 2 pi (w + 1/2) 2^-32: the nearest quarter turn and the
+    // remainder are exact integers of w.
+    __device__ static __forceinline__ void sincos_turn(const MathOf<double> &m, uint32_t w, double &s, double &c)
+    {
+        const uint32_t q = (w + 0x20000000u) >> 30;
+        const double r = (double)(int32_t)(w - (q << 30)) + 0.5;
+        sincos_octant(m, r * 0x1.921fb54442d18p-30, 0.0, s, c);
+        quadrant(q, s, c);
+    }
+    // sin and cos of x, |x| < 2^31: two-part reduction by pi / 2, whose
+    // products are exact in the fused operations.
+    __device__ static __forceinline__ void sincos(const MathOf<double> &m, double x, double &s, double &c)
+    {
+        const Tab t = tab(12);
+        const double n = __builtin_rint(x * t[0]);
+        const double a = madd(n, t[1], x), r = madd(n, t[2], a);
+        sincos_octant(m, r, madd(n, t[2], a - r), s, c);
+        quadrant((uint32_t)(int32_t)n, s, c);
+    }
+    // -2 ln((w + 1/2) 2^-32). ln(1 + f) = 2 atanh(s), s = f / (2 + f), is
+    // f - f^2 / 2 + s (f^2 / 2 + z L(z)), z = s^2, which keeps the relative
+    // accuracy near 1 (L to 2^-59.5 for sqrt(1/2) <= 1 + f < sqrt(2)).
+    __device__ static __forceinline__ double minus_two_ln(uint32_t w)
+    {
+        const uint64_t b = (uint64_t)__double_as_longlong((double)w + 0.5);
+        const int32_t hi = (int32_t)(b >> 32);
+        const int32_t k = (hi - 0x3fe6a09e) >> 20;  // d = (1 + f) 2^k
+        const double f =
+            __longlong_as_double((long long)(((uint64_t)(uint32_t)(hi - (k << 20)) << 32) | (uint32_t)b)) - 1.0;
+        const double den = 2.0 + f;
+        double y = __builtin_amdgcn_rcp(den);
+        y = madd(y, madd(-den, y, 1.0), y);
+        y = madd(y, madd(-den, y, 1.0), y);
+        double t = f * y;
+        t = madd(madd(-den, t, f), y, t);
+        const double z = t * t;
+        const Tab l = tab(16);
+        double L = l[0];
+#pragma unroll
+        for (int i = 1; i < 7; ++i) L = madd(L, z, l[i]);
+        const double h = 0.5 * f * f;
+        const double e = (double)(k - 32);
+        const double ln = madd(e, l[7], f - (h - madd(t, madd(z, L, h), e * l[8])));
+        return -2.0 * ln;
+    }
+    // sqrt x for normal x: two coupled Newton steps (Goldschmidt) and a
+    // residual correction.
+    __device__ static __forceinline__ double sqrt_normal(double x)
+    {
+        const double y = __builtin_amdgcn_rsq(x);
+        double g = x * y, h = 0.5 * y;
+        double r = madd(-h, g, 0.5);
+        g = madd(g, r, g);
+        h = madd(h, r, h);
+        g = madd(madd(-g, g, x), h, g);
+        return madd(madd(-g, g, x), h, g);
+    }
+    // exp(-x), 0 <= x below some hundreds: 2^n (1 + r + r^2 E(r)) (E to 2^-56.8).
+    __device__ static __forceinline__ double exp_neg(double x)
+    {
+        const Tab t = tab(23), ec = t + 5;
+        const double n = __builtin_rint(x * ec[10]);
+        const double a = madd(n, -t[0], -x), r = madd(n, -t[1], a), dr = madd(n, -t[1], a - r);
+        double E = ec[0];
+#pragma unroll
+        for (int i = 1; i < 10; ++i) E = madd(E, r, ec[i]);
+        return __builtin_ldexp(1.0 + (r + madd(r * r, E, dr)), (int)n);
+    }
+};
+
+__device__ __forceinline__ void MathOf<double>::init()
+{
+#pragma unroll
+    for (int i = 0; i < 12; ++i) {  // opaque moves: otherwise the loads would move to the uses
+        const uint64_t b = (uint64_t)__double_as_longlong(kFp64Tab[i]);
+        uint32_t lo, hi;
+        asm volatile("v_mov_b32 %0, %1" : "=v"(lo) : "s"((uint32_t)b));
+        asm volatile("v_mov_b32 %0, %1" : "=v"(hi) : "s"((uint32_t)(b >> 32)));
+        (i < 6 ? S[i] : C[i - 6]) = __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+    }
+}
+
 template <>
 struct Arith<double> {
-    __device__ static __forceinline__ double unif(uint32_t w)
+    __device__ static __forceinline__ double unif_bridge(uint32_t w)
     {
         return ((double)w + 0.5) * 0x1.0p-32;
     }
-    __device__ static __forceinline__ double unif_bridge(uint32_t w) { return unif(w); }
-    __device__ static __forceinline__ void box_muller(uint32_t a, uint32_t b, double &n0,
+    __device__ static __forceinline__ void box_muller(const MathOf<double> &m, uint32_t a, uint32_t b, double &n0,
                                                       double &n1)
     {
-        const double r = sqrt(-2.0 * log(unif(a)));
-        const double th = kTwoPi * unif(b);
+        const double r = Fp64Math::sqrt_normal(Fp64Math::minus_two_ln(a));
         double s, c;
-        sincos(th, &s, &c);
+        Fp64Math::sincos_turn(m, b, s, c);
         n0 = r * c;
         n1 = r * s;
     }
-    __device__ static __forceinline__ double box_muller_cos(uint32_t a, uint32_t b)
+    __device__ static __forceinline__ double box_muller_cos(const MathOf<double> &m, uint32_t a, uint32_t b)
     {
-        return sqrt(-2.0 * log(unif(a))) * cos(kTwoPi * unif(b));
+        double s, c;
+        Fp64Math::sincos_turn(m, b, s, c);
+        return Fp64Math::sqrt_normal(Fp64Math::minus_two_ln(a)) * c;
     }
-    __device__ static __forceinline__ void trig(const DevTrig<double> &t, int d, double x,
-                                                double &s, double &c)
+    // BIG: arguments may reach 2^31 and take the library's functions then.
+    template <bool BIG>
+    __device__ static __forceinline__ void trig(const MathOf<double> &mt, const DevProblem<double> &P, int m, int d,
+                                                double x, double &s, double &c)
     {
-        sincos(madd(t.k[d], x, t.ph[d]), &s, &c);
+        const double arg = madd(P.trig[m].k[d], x, P.trig[m].ph[d]);
+        if (BIG && P.big_trig)
+            ::sincos(arg, &s, &c);
+        else
+            Fp64Math::sincos(mt, arg, s, c);
     }
-    __device__ static __forceinline__ double sine(const DevTrig<double> &t, int d, double x)
+    template <bool BIG>
+    __device__ static __forceinline__ double sine(const MathOf<double> &mt, const DevProblem<double> &P, int m, int d,
+                                                  double x)
     {
-        return sin(madd(t.k[d], x, t.ph[d]));
+        double s, c;
+        trig<BIG>(mt, P, m, d, x, s, c);
+        return s;
     }
-    __device__ static __forceinline__ double exp_neg(double x) { return exp(-x); }
+    __device__ static __forceinline__ double exp_neg(double x) { return Fp64Math::exp_neg(x); }
     __device__ static __forceinline__ double sqrt_(double x) { return sqrt(x); }
 };
 
@@ -312,8 +488,8 @@ template <class T, int D>
 __device__ __forceinline__ T interp_corners(const T *p, const T *w);
 template <class T>
 __device__ __forceinline__ T interp_corner_values(T c00, T c10, T c01, T c11, const T *w);
-template <class T, int D>
-__device__ __forceinline__ void analytic_source(const DevProblem<T> &P, const T *x, const T *b, T c, T &f,
+template <class T, int D, bool BIG>
+__device__ __forceinline__ void analytic_source(const MathOf<T> &mt, const DevProblem<T> &P, const T *x, const T *b, T c, T &f,
                                                 const T *cf);
 
 // b(x), c(x) and, when asked, f(x) = F(x) + sum over trig terms T of
@@ -366,8 +542,8 @@ __device__ __forceinline__ void pair_chunks(const Vec4<T> *base, uint32_t rec, V
     }
 }
 
-template <class T, int D>
-__device__ __forceinline__ void coefficients(const DevProblem<T> &P, const T *x, T *b, T &c,
+template <class T, int D, bool BIG>
+__device__ __forceinline__ void coefficients(const MathOf<T> &mt, const DevProblem<T> &P, const T *x, T *b, T &c,
                                              T &f, bool want_f, const T *cf, uint32_t tab,
                                              Vec4<T> *tr = nullptr)
 {
@@ -409,19 +585,19 @@ __device__ __forceinline__ void coefficients(const DevProblem<T> &P, const T *x,
             f = interp_cells<T, D>(P.tabv[4], x);
             want_f = false;
         }
-        if (want_f) analytic_source<T, D>(P, x, b, c, f, cf);
+        if (want_f) analytic_source<T, D, BIG>(mt, P, x, b, c, f, cf);
 #pragma unroll
         for (int d = 0; d < D; ++d)
             if (tab & (1u << d)) b[d] = interp_cells<T, D>(P.tabv[d], x);
         if (tab & 8u) c = interp_cells<T, D>(P.tabv[3], x);
         return;
     }
-    if (want_f) analytic_source<T, D>(P, x, b, c, f, cf);
+    if (want_f) analytic_source<T, D, BIG>(mt, P, x, b, c, f, cf);
 }
 
 // The analytic source for the analytic b and c.
-template <class T, int D>
-__device__ __forceinline__ void analytic_source(const DevProblem<T> &P, const T *x, const T *b, T c, T &f,
+template <class T, int D, bool BIG>
+__device__ __forceinline__ void analytic_source(const MathOf<T> &mt, const DevProblem<T> &P, const T *x, const T *b, T c, T &f,
                                                 const T *cf)
 {
     T acc = (T)0;
@@ -433,7 +609,7 @@ __device__ __forceinline__ void analytic_source(const DevProblem<T> &P, const T 
         const DevTrig<T> &t = P.trig[m];
         T s[D], co[D];
 #pragma unroll
-        for (int d = 0; d < D; ++d) Arith<T>::trig(t, d, x[d], s[d], co[d]);
+        for (int d = 0; d < D; ++d) Arith<T>::template trig<BIG>(mt, P, m, d, x[d], s[d], co[d]);
         T prod = s[0];
 #pragma unroll
         for (int d = 1; d < D; ++d) prod *= s[d];
@@ -452,8 +628,8 @@ __device__ __forceinline__ void analytic_source(const DevProblem<T> &P, const T 
 }
 
 // g = G + sum(trig) at a boundary point.
-template <class T, int D>
-__device__ __forceinline__ T boundary_value(const DevProblem<T> &P, const T *x, uint32_t tab)
+template <class T, int D, bool BIG>
+__device__ __forceinline__ T boundary_value(const MathOf<T> &mt, const DevProblem<T> &P, const T *x, uint32_t tab)
 {
     if (tab & 32u) return interp_cells<T, D>(P.tabv[5], x);  // tabulated g
     T u = poly_value<T, D>(P.gpoly, P.n_g, x);
@@ -461,7 +637,7 @@ __device__ __forceinline__ T boundary_value(const DevProblem<T> &P, const T *x, 
         const DevTrig<T> &t = P.trig[m];
         T v = t.amp;
 #pragma unroll
-        for (int d = 0; d < D; ++d) v *= Arith<T>::sine(t, d, x[d]);
+        for (int d = 0; d < D; ++d) v *= Arith<T>::template sine<BIG>(mt, P, m, d, x[d]);
         u += v;
     }
     return u;
@@ -621,6 +797,7 @@ __global__ void grid_points_kernel(const S *__restrict__ data, uint64_t n_points
 // box), where the per-lane branches of the other form would run at nearly
 // every step; both give the same bits.
 struct RuntimeMode {
+    static constexpr bool kBigTrig = true;
     template <class T>
     __device__ static __forceinline__ int domain(const DevProblem<T> &P) { return P.domain; }
     template <class T>
@@ -634,6 +811,7 @@ struct RuntimeMode {
 };
 template <bool DENSE>
 struct BoxBridgeGaussT {
+    static constexpr bool kBigTrig = false;
     template <class T>
     __device__ static constexpr int domain(const DevProblem<T> &) { return kBox; }
     template <class T>
@@ -729,10 +907,10 @@ __device__ __forceinline__ void project(const DevProblem<T> &P, int domain, cons
 // (plain), e = (g - u_prev)(X_tau) Y - R (correction), phi and phi + xi (Ito),
 // and the exit step word.
 template <class T, int D, int EST, class M>
-__device__ __forceinline__ void score_path(const ItemCore<T> &a, const DevProblem<T> &P, const T *Xt, T Y, double Z,
+__device__ __forceinline__ void score_path(const MathOf<T> &mt, const ItemCore<T> &a, const DevProblem<T> &P, const T *Xt, T Y, double Z,
                                            double R, uint32_t word, uint64_t r)
 {
-    const T gv = boundary_value<T, D>(P, Xt, M::tab(P));
+    const T gv = boundary_value<T, D, M::kBigTrig>(mt, P, Xt, M::tab(P));
     if (EST == kEstIto) {  // phi and phi + xi
         const double phi = madd((double)gv, (double)Y, Z);
         gstore(a.rec_phi + r, phi);
@@ -764,6 +942,26 @@ struct EndRing {
     EndedPath<T, D> e[kEndRing];
 };
 
+// The same object behind a pointer that the optimiser cannot see through, in
+// FP64: fields read after this are loaded again (by scalar loads) instead of
+// being kept from an earlier part of the step in scalar registers, which the
+// FP64 coefficients fill (each spilled value costs a v_writelane and a
+// v_readlane per step).
+template <class T, class X>
+__device__ __forceinline__ const X &reread(const X &x)
+{
+    if constexpr (sizeof(T) == 8) {
+        const uint64_t v = reinterpret_cast<uint64_t>(&x);
+        uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+        uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
+        asm volatile("" : "+s"(lo), "+s"(hi));
+        typedef const __attribute__((address_space(4))) X ConstX;
+        return *(const X *)(ConstX *)(((uint64_t)hi << 32) | lo);
+    } else {
+        return x;
+    }
+}
+
 template <class T, int D, int EST, class M, bool RNG_TABLE>
 struct Walker {
     T X[D], Xt[D];
@@ -780,6 +978,7 @@ struct Walker {
     uint32_t bb_blk;
     uint64_t bw01, bw23;  // cached bridge block, words (0,1) and (2,3)
     KeysOf<T> ks;
+    MathOf<T> mt;
     const T *cf;          // dense source coefficients of the problem, in LDS
     Vec4<T> *tr;          // the wave's LDS block for gathering pair records (single-item kernel)
 
@@ -875,21 +1074,26 @@ struct Walker {
     // path (leaving the domain, a live bridge face, the shift band of the next
     // step, the step cap) goes through one rarely taken branch.
     template <class A>
-    __device__ __forceinline__ bool step(const A &a, const DevProblem<T> &P, uint32_t wa,
+    __device__ __forceinline__ bool step(const A &a0, const DevProblem<T> &P0, uint32_t wa,
                                          uint32_t wb, uint32_t wc, uint32_t wd)
     {
-        T n[D];
-        if (M::law(a) == kLawGauss) {
-            Arith<T>::box_muller(wa, wb, n[0], n[1]);
-            if (D == 3) n[2 % D] = Arith<T>::box_muller_cos(wc, wd);
-        } else {
-            n[0] = (wa >> 31) ? (T)1 : (T)-1;
-            n[1] = (wb >> 31) ? (T)1 : (T)-1;
-            if (D == 3) n[2 % D] = (wc >> 31) ? (T)1 : (T)-1;
+        T n[D], b[D], c, f = (T)0;
+        {
+            const A &a = reread<T>(a0);
+            const DevProblem<T> &P = reread<T>(P0);
+            if (M::law(a) == kLawGauss) {
+                Arith<T>::box_muller(mt, wa, wb, n[0], n[1]);
+                if (D == 3) n[2 % D] = Arith<T>::box_muller_cos(mt, wc, wd);
+            } else {
+                n[0] = (wa >> 31) ? (T)1 : (T)-1;
+                n[1] = (wb >> 31) ? (T)1 : (T)-1;
+                if (D == 3) n[2 % D] = (wc >> 31) ? (T)1 : (T)-1;
+            }
+            coefficients<T, D, M::kBigTrig>(mt, P, X, b, c, f, EST == kEstIto || a.score_plain != 0, cf, M::tab(P),
+                               RNG_TABLE ? nullptr : tr);
         }
-        T b[D], c, f = (T)0;
-        coefficients<T, D>(P, X, b, c, f, EST == kEstIto || a.score_plain != 0, cf, M::tab(P),
-                           RNG_TABLE ? nullptr : tr);
+        const A &a = reread<T>(a0);
+        const DevProblem<T> &P = reread<T>(P0);
         const T hY = a.h * Y;
         if (EST == kEstIto || a.score_plain) Z -= (double)(hY * f);
         if (EST == kEstCorrection) R += (double)(hY * interp_cells<T, D>(a.resid, X));
@@ -1099,7 +1303,7 @@ struct Walker {
     __device__ __forceinline__ void finish(const ItemCore<T> &a, const DevProblem<T> &P,
                                            uint64_t rec_base)
     {
-        score_path<T, D, EST, M>(a, P, Xt, Y, Z, R, k | (capped ? kCappedBit : 0u), slot - rec_base);
+        score_path<T, D, EST, M>(mt, a, P, Xt, Y, Z, R, k | (capped ? kCappedBit : 0u), slot - rec_base);
     }
 
     // What scoring the ended path needs, for scoring later from the ring.
@@ -1201,6 +1405,7 @@ __global__ void __launch_bounds__(256) path_kernel_one(const OneItemArgs<T> A)
     EndRing<T, D> *ring = &wl->ring;
     Walker<T, D, EST, M, false> w;
     w.cf = s_cf;
+    w.mt.init();
     w.tr = std::is_same<M, RuntimeMode>::value ? wl->tr : nullptr;
     w.ks = key_schedule<KeysOf<T>>(P.key0, P.key1);
     int st = 0;  // 0 idle, 1 walking, 2 ended (to be scored)
@@ -1233,7 +1438,7 @@ __global__ void __launch_bounds__(256) path_kernel_one(const OneItemArgs<T> A)
                         T Xt[D];
 #pragma unroll
                         for (int d = 0; d < D; ++d) Xt[d] = e.Xt[d];
-                        score_path<T, D, EST, M>(a, P, Xt, e.Y, e.Z, e.R, e.word, e.r);
+                        score_path<T, D, EST, M>(w.mt, a, P, Xt, e.Y, e.Z, e.R, e.word, e.r);
                     }
                     ring_head = (ring_head + n) & (kEndRing - 1);
                     ring_count -= n;
@@ -1352,7 +1557,7 @@ struct ItemQueue {
 // the FP32 2D box / bridge / Gaussian correction walks five (96 registers:
 // one 8-byte value is reloaded at refill turns).
 template <class T, int D, int EST, class M>
-constexpr int kManyMinWaves = sizeof(T) == 8 ? 3
+constexpr int kManyMinWaves = sizeof(T) == 8 ? (D == 3 && (EST == kEstIto || std::is_same<M, RuntimeMode>::value) ? 2 : 3)
                               : (D == 2 && EST == kEstCorrection && !std::is_same<M, RuntimeMode>::value) ? 5
                                                                                                           : 1;
 template <class T, int D, int EST, class M>
@@ -1369,6 +1574,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kManyM
     Walker<T, D, EST, M, true> w;
     w.cf = my_cf;
     w.tr = nullptr;
+    w.mt.init();
     int st = 0;
     ItemQueue<T> q;
     // Ended paths are scored 64 at a time, one per lane, from the wave's ring
@@ -1401,7 +1607,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kManyM
                     T Xt[D];
 #pragma unroll
                     for (int d = 0; d < D; ++d) Xt[d] = e.Xt[d];
-                    score_path<T, D, EST, M>(it, probs[it.prob], Xt, e.Y, e.Z, e.R, e.word, e.r);
+                    score_path<T, D, EST, M>(w.mt, it, probs[it.prob], Xt, e.Y, e.Z, e.R, e.word, e.r);
                 }
                 ring_head = (ring_head + n) & (kEndRing - 1);
                 ring_count -= n;
@@ -1496,6 +1702,8 @@ __global__ void __launch_bounds__(256) grid_residual_kernel(const DevProblem<dou
     const uint64_t m01 = (uint64_t)n0 * n1;
     const uint64_t total = m01 * (D == 3 ? (uint64_t)n2 : 1);
     const int nn[3] = {n0, n1, n2};
+    MathOf<double> mt;
+    mt.init();
     const double lo[3] = {lo0, lo1, lo2}, dx[3] = {dx0, dx1, dx2};
     const uint64_t st[3] = {1, (uint64_t)n0, m01};
     for (uint64_t p = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; p < total;
@@ -1505,7 +1713,7 @@ __global__ void __launch_bounds__(256) grid_residual_kernel(const DevProblem<dou
 #pragma unroll
         for (int d = 0; d < D; ++d) x[d] = lo[d] + (double)idx[d] * dx[d];
         double b[D], c, f = 0.0;
-        coefficients<double, D>(P, x, b, c, f, true, s_cf, P.tab);
+        coefficients<double, D, true>(mt, P, x, b, c, f, true, s_cf, P.tab);
         double lap = 0.0, adv = 0.0;
 #pragma unroll
         for (int d = 0; d < D; ++d) {
@@ -1529,6 +1737,8 @@ __global__ void __launch_bounds__(256) stage2_boundary_kernel(const DevProblem<d
 {
     const int n0 = g.n0, n1 = g.n1;
     const int total = 2 * n0 + 2 * (n1 - 2);
+    MathOf<double> mt;
+    mt.init();
     for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < total; q += gridDim.x * blockDim.x) {
         int i, j;
         if (q < n0) {
@@ -1541,7 +1751,7 @@ __global__ void __launch_bounds__(256) stage2_boundary_kernel(const DevProblem<d
             j = 1 + (r >> 1);
         }
         const double x[2] = {stage2_coord(g.lo0, g.span0, n0, i), stage2_coord(g.lo1, g.span1, n1, j)};
-        g.u[(size_t)j * n0 + i] = boundary_value<double, 2>(P, x, P.tab);
+        g.u[(size_t)j * n0 + i] = boundary_value<double, 2, true>(mt, P, x, P.tab);
     }
 }
 
@@ -1605,6 +1815,8 @@ __global__ void __launch_bounds__(256) stage2_stencil_kernel(const DevProblem<do
     for (int q = threadIdx.x; q < kMaxDense; q += blockDim.x) s_cf[q] = P.fdense[q];
     __syncthreads();
     const SubBox b = boxes[blockIdx.y];
+    MathOf<double> mt;
+    mt.init();
     const uint64_t n = (uint64_t)b.w * (uint64_t)b.L;
     const double cx = g.half_s2 / (g.dx0 * g.dx0), cy = g.half_s2 / (g.dx1 * g.dx1);
     for (uint64_t r = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; r < n; r += (uint64_t)gridDim.x * blockDim.x) {
@@ -1612,7 +1824,7 @@ __global__ void __launch_bounds__(256) stage2_stencil_kernel(const DevProblem<do
         stage2_point(b, r, i, j);
         const double x[2] = {stage2_coord(g.lo0, g.span0, g.n0, i), stage2_coord(g.lo1, g.span1, g.n1, j)};
         double bb[2], c, f = 0.0;
-        coefficients<double, 2>(P, x, bb, c, f, true, s_cf, P.tab);
+        coefficients<double, 2, true>(mt, P, x, bb, c, f, true, s_cf, P.tab);
         const double aW = cx - bb[0] / (2.0 * g.dx0), aE = cx + bb[0] / (2.0 * g.dx0);
         const double aS = cy - bb[1] / (2.0 * g.dx1), aN = cy + bb[1] / (2.0 * g.dx1);
         double out[6] = {0.0, 0.0, -2.0 * cx - 2.0 * cy + c, 0.0, 0.0, f};

@@ -81,7 +81,7 @@ struct DevProblem {
     // tabulated coefficients: bit q of tab set when tabv[q] replaces the
     // analytic b_0, b_1, b_2, c, f, g (q = 0..5); read through their cell layout
     uint32_t tab;
-    int32_t tab_pad;
+    int32_t big_trig;  // FP64: a trig term's argument may leave the reduction's range (generic kernels only)
     GridView<T> tabv[6];
     // bit 6 of tab: b_0 .. b_{dim-1}, c and f are all tabulated on one
     // geometry and interleaved (tabv[q] then keep only the geometry): cell r's

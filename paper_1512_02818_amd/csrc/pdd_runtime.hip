@@ -358,7 +358,7 @@ uint64_t next_problem_serial()
 bool pdd::specialised(const HostItem &it)
 {
     return it.prob->desc.domain == PDD_DOMAIN_BOX && it.o->exit_mode == PDD_EXIT_BRIDGE &&
-           it.o->law == PDD_LAW_GAUSS && it.prob->pf.tab == 0;
+           it.o->law == PDD_LAW_GAUSS && it.prob->pf.tab == 0 && !it.prob->pd.big_trig;
 }
 
 // A face can be live within about 3.5 sigma sqrt(dt) of it (2 a a' / (sigma^2
@@ -1061,6 +1061,7 @@ pdd_status pdd_create_problem(pdd_ctx *ctx, const pdd_problem_desc *desc, pdd_pr
         delete p;
         return st;
     }
+    p->pd.big_trig = !(p->trig_rev_max <= kFp64TrigRevolutions);
     *out = p;
     return PDD_OK;
 }
@@ -1141,6 +1142,7 @@ pdd_status pdd_create_problem_tabulated(pdd_ctx *ctx, const pdd_problem_desc *de
         delete p;
         return st;
     }
+    p->pd.big_trig = !(p->trig_rev_max <= kFp64TrigRevolutions);
     if (tab) {
         auto bail = [&](pdd_status s2) {
             pdd_destroy_problem(p);
@@ -1440,6 +1442,7 @@ pdd_status pdd_autotune(pdd_ctx *ctx, const pdd_work_item *item, pdd_tuning *out
     HIP_TRY(hipSetDevice(ctx->device));
     // the kernel this group launches for a single item, and its occupancy
     const bool spec = item->problem->desc.domain == PDD_DOMAIN_BOX && item->problem->pf.tab == 0 &&
+                      !item->problem->pd.big_trig &&
                       item->opts->exit_mode == PDD_EXIT_BRIDGE && item->opts->law == PDD_LAW_GAUSS;
     const int kind = !spec ? kKernelGeneric
                      : dense_boundary(item->problem->desc, item->opts->dt) ? kKernelDense : kKernelSparse;
