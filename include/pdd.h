@@ -131,12 +131,13 @@ typedef struct {
 /* Launch shape of the path kernel. A solve whose opts give no tuning uses the
  * context's entry for its (precision, dim, estimator) group, set by
  * pdd_autotune or pdd_set_tuning, else the default {256, occupancy, 64, 0,
- * 0, 0}; fields left 0 in a given tuning take the default. Results never
- * depend on the launch shape. */
+ * 0, 0}; fields left 0 in a given tuning take the default. Launches of at most
+ * 400,000 paths have a shape of their own. Results never depend on the launch
+ * shape. */
 typedef struct {
     int32_t block;        /* threads per workgroup: 64, 128 or 256 */
     int32_t blocks_per_cu;/* persistent workgroups per compute unit */
-    int32_t grab;         /* paths a wavefront takes from the queue at a time */
+    int32_t grab;         /* paths a wavefront takes from the queue at a time, at most */
     int32_t max_launch_paths; /* cap on paths per path-kernel launch (0 = 2^27; records
                                  given by the caller: no cap) */
     int32_t refill;       /* walk-loop iterations between refills of the lanes that

@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <map>
 #include <string>
@@ -72,6 +73,31 @@ inline uint32_t refill_mask(const pdd_tuning &t)
 {
     return (uint32_t)((t.refill ? t.refill : (D == 2 ? 2 : 4)) - 1);
 }
+// Launches of at most this many paths are walked by groups of lanes only: up
+// to about one and a half paths per resident lane, one path per lane leaves
+// most lanes idle for most of the launch. Measured, group walk against one
+// path per lane and a hand-over (18 nodes, h = 1e-3): 180,000 paths 0.44 and
+// 0.54 ms in FP32 2D, 0.65 and 0.82 ms in FP64; 360,000: 0.62 and 0.78, 1.06
+// and 1.09; 540,000: 0.81 and 0.86, 1.44 and 1.32.
+constexpr uint64_t kGroupDirectSlots = 400000;
+// Paths handed over by a launch, at most (their buffer: 33 MB in FP32 3D). The
+// items of a batch share it: 64 uneven problems take 140 ms with it and 180 ms
+// with half of it, no less with twice of it.
+constexpr uint64_t kTailEntries = 1ull << 19;
+// Workgroups of a group-walk launch over at most `paths` paths: as many lanes
+// per path as two workgroups per CU give (FP32 from 2^17 paths on three: 0.62
+// ms for 360,000 paths, 0.69 ms with two; 18,000 paths 0.22 and 0.21 ms).
+template <class T>
+int group_grid(const pdd_ctx *ctx, uint64_t paths);
+// Paths a wave takes from the queue at a time: the tuning's, but not so many
+// that waves run dry at very different times (about eight tickets a wave; 18
+// nodes x 100,000 correction paths with the tuned 256: 1.94 ms, 1.79 ms), and
+// not below 32, where the waves wait for the one counter (2.2 ms with 16).
+inline int32_t ticket_size(const pdd_tuning &t, uint64_t paths, uint64_t waves)
+{
+    const uint64_t even = paths / (waves * 8) / 16 * 16;
+    return (int32_t)std::min<uint64_t>((uint64_t)t.grab, std::max<uint64_t>(32, even));
+}
 // Whether many lanes of a wave are near a face at every step of a walk of
 // this problem at step dt (then the dense form of the bridge test is the
 // faster one).
@@ -108,6 +134,7 @@ struct pdd_ctx {
     hipEvent_t staged = nullptr;  // last copy out of the staging buffer
     bool any_done = false, any_staged = false;
     pdd::DeviceBuffer nodes, starts, acc, counters, rec, partials, gather, cells;
+    pdd::DeviceBuffer tail;    // walking paths handed over between path kernels of a launch
     pdd::DeviceBuffer stage2;  // second stage: tables and stencils
     // LU factors of the last second stage's subdomain matrices, and what they
     // factor (the operator, the grid, the interfaces): a call with the same
@@ -128,6 +155,18 @@ struct pdd_ctx {
     // launch shapes by (precision, dim, estimator), from pdd_autotune / pdd_set_tuning
     std::map<int, pdd_tuning> tuned;
 };
+
+namespace pdd {
+template <class T>
+int group_grid(const pdd_ctx *ctx, uint64_t paths)
+{
+    constexpr uint64_t waves = kGroupBlock / 64;
+    const uint64_t most = (uint64_t)ctx->n_cu * (sizeof(T) == 4 && paths >= (1u << 17) ? 3 : 2);
+    uint64_t share = 1;  // paths of a wave
+    while (share < 16 && paths > share * most * waves) share *= 2;
+    return (int)std::max<uint64_t>(1, std::min(most, (paths + share * waves - 1) / (share * waves)));
+}
+}  // namespace pdd
 
 struct pdd_problem {
     pdd_ctx *ctx = nullptr;

@@ -166,7 +166,28 @@ struct LaunchArgs {
     uint32_t refill_mask;  // lanes are refilled at walk-loop iterations i with (i & refill_mask) == 0
     uint32_t *counter;
     const uint32_t *seg;
+    // Paths handed over to the group-walk kernel: item item_lo + q of the
+    // launch has the entries [tail_off[q], tail_off[q + 1]) of `tail`
+    // (TailState) and tail_n[q] counts those asked for. The one-path-per-lane
+    // kernels hand over a wave's walking lanes once its item has no more slots
+    // and at most tail_max are left (0: never). The group-walk kernel takes
+    // its paths from there, or, with `tail` null, from the slots.
+    void *tail;
+    uint32_t *tail_n;
+    const uint32_t *tail_off;
+    uint32_t tail_max;
 };
+
+// A walking path between two blocks of random numbers.
+template <class T, int D>
+struct TailState {
+    T X[D], Y, m;
+    double Z, R;
+    uint64_t slot;
+    uint32_t k, j, node, tag;
+};
+
+constexpr int kGroupBlock = 256;  // threads per workgroup of the group-walk kernel
 
 // Compensated (Neumaier) per-node accumulators: phi, phi^2, e, e^2, phi*e.
 struct NodeAcc {
@@ -266,6 +287,10 @@ hipError_t launch_path_kernel(const LaunchArgs &l, const ItemDesc<T> *items,
                               const DevProblem<T> *probs, int grid, int block, int kind, hipStream_t s);
 template <class T, int D, int EST>
 hipError_t launch_path_kernel_one(const OneItemArgs<T> &a, int grid, int block, int kind, hipStream_t s);
+// The group-walk kernel (kind: generic or not).
+template <class T, int D, int EST>
+hipError_t launch_path_kernel_group(const LaunchArgs &l, const ItemDesc<T> *items, const DevProblem<T> *probs,
+                                    int grid, int kind, hipStream_t s);
 template <class T, int D, int EST>
 const void *path_kernel_symbol(bool one, int kind);
 // Fills `cells` (cell_values entries) from the point values of a grid,

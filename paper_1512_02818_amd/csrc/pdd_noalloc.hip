@@ -177,7 +177,6 @@ pdd_status run_noalloc(pdd_ctx *ctx, const HostItem &it, const pdd_tuning &tune,
         L.slot_begin = b;
         L.launch_slots = (uint32_t)len;
         L.n_items = 1;
-        L.grab = tune.grab;
         L.counter = counter;
         L.item_lo = 0;
         L.n_seg = 1;
@@ -185,7 +184,10 @@ pdd_status run_noalloc(pdd_ctx *ctx, const HostItem &it, const pdd_tuning &tune,
         L.seg = d_seg + (len == per_launch ? 0 : 2);
         const uint64_t blocks_needed = ((len + 63) / 64 * 64 + tune.block - 1) / tune.block;
         const int grid = (int)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)ctx->n_cu * bpc, blocks_needed));
-        if (one) {
+        L.grab = ticket_size(tune, len, (uint64_t)grid * (tune.block / 64));
+        if (len <= kGroupDirectSlots) {  // (nothing is handed over here: there is no buffer for it)
+            HIP_TRY((launch_path_kernel_group<T, D, kEstPlain>(L, d_item, d_prob, group_grid<T>(ctx, len), kind, s)));
+        } else if (one) {
             OneItemArgs<T> A;
             A.launch = L;
             A.item = a;

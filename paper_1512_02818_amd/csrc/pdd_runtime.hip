@@ -585,7 +585,9 @@ pdd_status run_group(pdd_ctx *ctx, std::vector<HostItem *> &items, const pdd_tun
         ctr_at[l + 1] = ctr_at[l] + std::max<uint32_t>(seg_n[l], 1);
     }
     const size_t n_ctr = (size_t)ctr_at[n_launch] + 2;
-    const size_t ctr_bytes = (n_ctr * sizeof(uint32_t) + 7) & ~size_t(7);  // cleared in 8-byte words
+    // three counters per queue: its slots taken, its paths handed over to the
+    // group-walk kernel, and those taken there
+    const size_t ctr_bytes = (3 * n_ctr * sizeof(uint32_t) + 7) & ~size_t(7);  // cleared in 8-byte words
 
     // staged upload: nodes | global node starts | item node starts | kernel
     // items | problems | node -> item | per-item post-processing entries |
@@ -599,9 +601,41 @@ pdd_status run_group(pdd_ctx *ctx, std::vector<HostItem *> &items, const pdd_tun
     const size_t off_fitems = align_up(off_nitem + n_nodes_all * sizeof(uint32_t), 256);
     const size_t off_seg = align_up(off_fitems + n_items * sizeof(FinalItem), 256);
     const size_t off_rng = align_up(off_seg + n_ctr * 2 * sizeof(uint32_t), 256);
-    const size_t bytes = align_up(off_rng + (any_merged ? n_nodes_all * 4 * sizeof(uint32_t) : 0), 256);
+    const size_t off_tail = align_up(off_rng + (any_merged ? n_nodes_all * 4 * sizeof(uint32_t) : 0), 256);
+    const size_t bytes = align_up(off_tail + (n_ctr + n_launch) * sizeof(uint32_t), 256);
 
+    // launch shape: the path kernel's, and how its walks end
+    const int block = tune.block;
+    // (the single-item kernel has no per-node RNG table)
+    const bool one = n_k == 1 && kOneItemKernel<T, D, EST> && kfirst[1] == 1;
+    // box / bridge / Gaussian / analytic throughout: the specialised kernel,
+    // in the bridge form of the walks that hold most of the group's slots
+    const bool spec = std::all_of(items.begin(), items.end(), [](const HostItem *i) { return specialised(*i); });
+    uint64_t dense_slots = 0;
+    for (int q = 0; q < n_items; ++q)
+        if (dense_boundary(items[q]->prob->desc, items[q]->o->dt)) dense_slots += items[q]->total;
+    const int kind = !spec                ? kKernelGeneric
+                     : tune.bridge == 1     ? kKernelSparse
+                     : tune.bridge == 2     ? kKernelDense
+                     : 2 * dense_slots >= total ? kKernelDense
+                                            : kKernelSparse;
+    const void *fn = path_kernel_symbol<T, D, EST>(one, kind);
+    // more workgroups than fit at once only queue behind the resident ones
+    const int occ = occupancy(ctx, fn, block);
+    const int bpc = tune.blocks_per_cu > 0 ? std::min(tune.blocks_per_cu, occ) : occ;
+    // live lanes at most at which a wave hands its paths over: a group walk of
+    // 16 paths costs what about 40 lanes of a wave do, but with several items
+    // a wave has the next item's paths to go on with (64 uneven problems: 142
+    // ms at 16, 150 ms at 32; one item of 360,000 FP64 paths: 8.5 and 7.4 ms)
+    const uint32_t tail_max = n_k > 1 ? 16 : 32;
+    // the longest launch decides whether paths are handed over at all; without
+    // memory for them they end where they began
+    uint64_t tail_cap = std::min(per_launch, total) > kGroupDirectSlots ? std::min<uint64_t>(total, kTailEntries) : 0;
     pdd_status st;
+    if (tail_cap && ensure(ctx, ctx->tail, tail_cap * sizeof(TailState<T, D>))) {
+        tail_cap = 0;
+        (void)hipGetLastError();
+    }
     if ((st = ensure(ctx, ctx->nodes, bytes))) return st;
     if ((st = ensure(ctx, ctx->acc, n_nodes_all * sizeof(NodeAcc)))) return st;
     if ((st = ensure(ctx, ctx->counters, ctr_bytes))) return st;
@@ -667,6 +701,26 @@ pdd_status run_group(pdd_ctx *ctx, std::vector<HostItem *> &items, const pdd_tun
             h_seg[2 * (ctr_at[l] + k)] = (uint32_t)(lo - b);
             h_seg[2 * (ctr_at[l] + k) + 1] = (uint32_t)(std::max(lo, hi) - b);
         }
+    }
+    // regions of the handed-over paths, per launch: as many as its waves may
+    // hand over per item, scaled down to the buffer
+    uint32_t *h_tail = reinterpret_cast<uint32_t *>(h + off_tail);
+    for (uint64_t l = 0; l < n_launch && tail_cap; ++l) {
+        const uint64_t waves = (uint64_t)ctx->n_cu * bpc * (block / 64);
+        uint64_t want = 0;
+        for (uint32_t k = 0; k < seg_n[l]; ++k) {
+            const uint32_t *r = h_seg + 2 * (ctr_at[l] + k);
+            want += std::min<uint64_t>(r[1] - r[0], waves * tail_max);
+        }
+        uint32_t *o = h_tail + ctr_at[l] + l;
+        uint64_t at = 0;
+        for (uint32_t k = 0; k < seg_n[l]; ++k) {
+            const uint32_t *r = h_seg + 2 * (ctr_at[l] + k);
+            const uint64_t w = std::min<uint64_t>(r[1] - r[0], waves * tail_max);
+            o[k] = (uint32_t)at;
+            at += want <= tail_cap ? w : w * tail_cap / want;
+        }
+        o[seg_n[l]] = (uint32_t)at;
     }
     std::vector<ItemDesc<T>> oitems(n_items);  // one per item, before merging
     std::memset(oitems.data(), 0, n_items * sizeof(ItemDesc<T>));
@@ -805,24 +859,6 @@ pdd_status run_group(pdd_ctx *ctx, std::vector<HostItem *> &items, const pdd_tun
         }
     }
 
-    const int block = tune.block;
-    // (the single-item kernel has no per-node RNG table)
-    const bool one = n_k == 1 && kOneItemKernel<T, D, EST> && kfirst[1] == 1;
-    // box / bridge / Gaussian / analytic throughout: the specialised kernel,
-    // in the bridge form of the walks that hold most of the group's slots
-    const bool spec = std::all_of(items.begin(), items.end(), [](const HostItem *i) { return specialised(*i); });
-    uint64_t dense_slots = 0;
-    for (int q = 0; q < n_items; ++q)
-        if (oitems[q].dense_bridge) dense_slots += oitems[q].n_slots;
-    const int kind = !spec                ? kKernelGeneric
-                     : tune.bridge == 1     ? kKernelSparse
-                     : tune.bridge == 2     ? kKernelDense
-                     : 2 * dense_slots >= total ? kKernelDense
-                                            : kKernelSparse;
-    const void *fn = path_kernel_symbol<T, D, EST>(one, kind);
-    // more workgroups than fit at once only queue behind the resident ones
-    const int occ = occupancy(ctx, fn, block);
-    const int bpc = tune.blocks_per_cu > 0 ? std::min(tune.blocks_per_cu, occ) : occ;
     const ItemDesc<T> *d_items = reinterpret_cast<const ItemDesc<T> *>(dv + off_items);
     const DevProblem<T> *d_probs = reinterpret_cast<const DevProblem<T> *>(dv + off_probs);
     std::pair<hipEvent_t, hipEvent_t> ev{nullptr, nullptr};
@@ -848,21 +884,37 @@ pdd_status run_group(pdd_ctx *ctx, std::vector<HostItem *> &items, const pdd_tun
         L.n_seg = seg_n[launch];
         L.refill_mask = refill_mask<D>(tune);
         L.seg = reinterpret_cast<const uint32_t *>(dv + off_seg) + 2 * ctr_at[launch];
-        const uint64_t waves_needed = (len + 63) / 64;
-        const uint64_t blocks_needed = (waves_needed * 64 + block - 1) / block;
-        const int grid = (int)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)ctx->n_cu * bpc, blocks_needed));
         if (timed && b == 0) HIP_TRY(hipEventRecord(ev.first, s));
-        if (one) {  // the item and its problem travel as kernel arguments
-            OneItemArgs<T> A;
-            A.launch = L;
-            A.item = h_items[0];
-            A.prob = h_probs[0];
-            // the single item starts at slot 0; scratch records of this launch
-            // start at slot b
-            if (A.item.rec_launch) A.item.rec_base = b;
-            HIP_TRY((launch_path_kernel_one<T, D, EST>(A, grid, block, kind, s)));
+        if (len <= kGroupDirectSlots) {  // few paths: walked by groups of lanes from the start
+            HIP_TRY((launch_path_kernel_group<T, D, EST>(L, d_items, d_probs, group_grid<T>(ctx, len), kind, s)));
         } else {
-            HIP_TRY((launch_path_kernel<T, D, EST>(L, d_items, d_probs, grid, block, kind, s)));
+            const uint64_t waves_needed = (len + 63) / 64;
+            const uint64_t blocks_needed = (waves_needed * 64 + block - 1) / block;
+            const int grid = (int)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)ctx->n_cu * bpc, blocks_needed));
+            uint32_t *ctrs = static_cast<uint32_t *>(ctx->counters.ptr);
+            if (tail_cap) {
+                L.tail = ctx->tail.ptr;
+                L.tail_n = ctrs + n_ctr + ctr_at[launch];
+                L.tail_off = reinterpret_cast<const uint32_t *>(dv + off_tail) + ctr_at[launch] + launch;
+                L.tail_max = tail_max;
+            }
+            L.grab = ticket_size(tune, len, (uint64_t)grid * (block / 64));
+            if (one) {  // the item and its problem travel as kernel arguments
+                OneItemArgs<T> A;
+                A.launch = L;
+                A.item = h_items[0];
+                A.prob = h_probs[0];
+                // the single item starts at slot 0; scratch records of this launch
+                // start at slot b
+                if (A.item.rec_launch) A.item.rec_base = b;
+                HIP_TRY((launch_path_kernel_one<T, D, EST>(A, grid, block, kind, s)));
+            } else {
+                HIP_TRY((launch_path_kernel<T, D, EST>(L, d_items, d_probs, grid, block, kind, s)));
+            }
+            if (tail_cap) {  // then the longest walks, handed over
+                L.counter = ctrs + 2 * n_ctr + ctr_at[launch];
+                HIP_TRY((launch_path_kernel_group<T, D, EST>(L, d_items, d_probs, group_grid<T>(ctx, len), kind, s)));
+            }
         }
         if (timed && b + per_launch >= total) HIP_TRY(hipEventRecord(ev.second, s));
         // reduction of the nodes this launch touched: one launch for the items
@@ -1030,7 +1082,7 @@ void pdd_shutdown(pdd_ctx *ctx)
     (void)hipSetDevice(ctx->device);
     if (ctx->any_done) (void)hipEventSynchronize(ctx->done);
     if (ctx->any_staged) (void)hipEventSynchronize(ctx->staged);
-    for (DeviceBuffer *b : {&ctx->nodes, &ctx->starts, &ctx->acc, &ctx->counters, &ctx->rec, &ctx->partials,
+    for (DeviceBuffer *b : {&ctx->nodes, &ctx->starts, &ctx->tail, &ctx->acc, &ctx->counters, &ctx->rec, &ctx->partials,
                             &ctx->gather, &ctx->cells, &ctx->stage2, &ctx->stage2_lu, &ctx->stage2_resp})
         if (b->ptr) (void)hipFree(b->ptr);
     if (ctx->stage) (void)hipHostFree(ctx->stage);
