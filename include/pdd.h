@@ -453,19 +453,16 @@ typedef struct {
  * Every subdomain (the grid box between consecutive interfaces) is then solved
  * for (1/2) sigma^2 Lap v + b.grad v + c v = f with the values on its
  * boundary, by second-order finite differences on the grid (central second
- * and first differences, b, c, f of the problem in FP64) and a banded LU
- * factorisation without pivoting, one workgroup per subdomain. The factors
- * depend on the operator (sigma, b, c), the grid and the interfaces only, so
- * the context keeps those of its last call. Since a subdomain's solution is
- * affine in its boundary values, the context also keeps, per subdomain, its
- * solution for f with zero boundary values and its response to a unit value
- * at each row next to the boundary (computed from the factors; at most 2 GiB
- * in all, else every call substitutes): a call with the same operator, grid,
- * interfaces and problem (another set of nodal values) then only adds up
- * those columns, weighted by its boundary values, in a fixed order. The
- * result equals the direct solve to rounding (the same in a fresh context
- * and in a kept one, bit for bit); PDD_STAGE2_SUBSTITUTE=1 in the
- * environment makes every call substitute instead. `nodes` (host,
+ * and first differences, b, c, f of the problem in FP64) and block
+ * cyclic reduction without pivoting (block rows along the longer side, FP64).
+ * The eliminated blocks depend on the operator (sigma, b, c), the grid and
+ * the interfaces only, so the context keeps those of its last call: a call
+ * with the same operator, grid, interfaces and problem (another set of nodal
+ * values) then only substitutes its right side. Where the blocks would take
+ * more than 8 GiB or cannot be allocated, or with PDD_STAGE2_SUBSTITUTE=1 in the environment, a
+ * banded LU, one workgroup per subdomain, takes their place. The result
+ * equals a direct solve to rounding (the same in a fresh context and in a
+ * kept one, bit for bit). `nodes` (host,
  * n_nodes x 2) are the interface nodes and `values` (host) their nodal
  * values; a node may lie on several lines. Synchronous (the interpolation
  * weights are solved on the host once the boundary values are on the

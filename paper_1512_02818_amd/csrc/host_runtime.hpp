@@ -136,15 +136,11 @@ struct pdd_ctx {
     pdd::DeviceBuffer nodes, starts, acc, counters, rec, partials, gather, cells;
     pdd::DeviceBuffer tail;    // walking paths handed over between path kernels of a launch
     pdd::DeviceBuffer stage2;  // second stage: tables and stencils
-    // LU factors of the last second stage's subdomain matrices, and what they
-    // factor (the operator, the grid, the interfaces): a call with the same
-    // ones only eliminates its right sides
-    pdd::DeviceBuffer stage2_lu;
+    // factors of the last second stage's subdomain matrices, and what they
+    // factor (the operator, the grid, the interfaces, and how): a call with the
+    // same ones only solves for its right sides
+    pdd::DeviceBuffer stage2_factor;
     std::vector<double> stage2_key;
-    // the subdomains' response columns to their boundary values (and to f),
-    // kept with their key: the factors' key and the problem's serial number
-    pdd::DeviceBuffer stage2_resp;
-    std::vector<double> stage2_resp_key;
     void *stage = nullptr;
     size_t stage_cap = 0;
     void *readback = nullptr;  // pinned host copy of pilot statistics

@@ -1083,7 +1083,7 @@ void pdd_shutdown(pdd_ctx *ctx)
     if (ctx->any_done) (void)hipEventSynchronize(ctx->done);
     if (ctx->any_staged) (void)hipEventSynchronize(ctx->staged);
     for (DeviceBuffer *b : {&ctx->nodes, &ctx->starts, &ctx->tail, &ctx->acc, &ctx->counters, &ctx->rec, &ctx->partials,
-                            &ctx->gather, &ctx->cells, &ctx->stage2, &ctx->stage2_lu, &ctx->stage2_resp})
+                            &ctx->gather, &ctx->cells, &ctx->stage2, &ctx->stage2_factor})
         if (b->ptr) (void)hipFree(b->ptr);
     if (ctx->stage) (void)hipHostFree(ctx->stage);
     if (ctx->readback) (void)hipHostFree(ctx->readback);
@@ -1769,76 +1769,61 @@ pdd_status pdd_stage2(pdd_problem *problem, const pdd_partition *part, const dou
             t_all.insert(t_all.end(), t.begin(), t.end());
             lam_all.insert(lam_all.end(), lam.begin(), lam.end());
         }
-    // the rows of every subdomain next to its boundary, and the layout of its
-    // response columns (nb + 1 columns of its unknowns)
-    std::vector<Stage2Resp> resp_tab(boxes.size());
-    std::vector<uint32_t> rb;
-    uint64_t resp_values = 0;
-    int32_t max_cols = 0;
-    bool use_resp = true;
+    // blocks of the cyclic reduction, up to 8 GiB (2.3 million unknowns) and
+    // where the device has them; else banded LU (as every call with
+    // PDD_STAGE2_SUBSTITUTE=1 in the environment, which the tests use to check
+    // the two ways against each other)
+    std::vector<Stage2Cr> cr_tab(boxes.size());
+    uint64_t cr_values = 0;
+    int32_t max_L = 0, max_w = 0;
+    for (const SubBox &b : boxes) max_L = std::max(max_L, b.L), max_w = std::max(max_w, b.w);
+    const uint64_t wp = (uint64_t)(max_w + 15) / 16 * 16;
     for (size_t q = 0; q < boxes.size(); ++q) {
-        const SubBox &bx = boxes[q];
-        const uint64_t nq = (uint64_t)bx.w * bx.L;
-        resp_tab[q].rb_at = rb.size();
-        for (uint64_t r = 0; r < nq; ++r) {
-            const int sl = (int)(r / bx.w), f = (int)(r % bx.w);
-            const int i = bx.i0 + 1 + (bx.fast_x ? f : sl), j = bx.j0 + 1 + (bx.fast_x ? sl : f);
-            if (i - 1 == bx.i0 || i + 1 == bx.i1 || j - 1 == bx.j0 || j + 1 == bx.j1) rb.push_back((uint32_t)r);
-        }
-        resp_tab[q].nb = (int32_t)(rb.size() - resp_tab[q].rb_at);
-        resp_tab[q].out_at = resp_values;
-        resp_values += (uint64_t)(resp_tab[q].nb + 1) * nq;
-        max_cols = std::max(max_cols, resp_tab[q].nb + 1);
-        use_resp = use_resp && resp_tab[q].nb <= kStage2MaxBoundaryRows;
+        const uint64_t rows = (uint64_t)boxes[q].L;
+        uint64_t pairs = 0;
+        for (uint64_t m = rows >> 1; m; m >>= 1) pairs += m;
+        cr_tab[q].at = cr_values;
+        cr_tab[q].mn = cr_values + rows * 3 * wp * wp;
+        cr_values += (rows * 3 + pairs * 4) * wp * wp;
     }
-    // response columns up to 2 GiB; beyond, every call substitutes (as every
-    // call does with PDD_STAGE2_SUBSTITUTE=1 in the environment, which the
-    // tests use to check the two ways against each other)
     const char *force_subst = std::getenv("PDD_STAGE2_SUBSTITUTE");
-    use_resp = use_resp && resp_values * sizeof(double) <= (2ull << 30) &&
-               !(force_subst && force_subst[0] == '1');
-    // device tables: lines | t | lam | boxes | response layout | boundary rows | stencils | aux
+    bool use_cr = cr_values * sizeof(double) <= (8ull << 30) && !(force_subst && force_subst[0] == '1');
+    // device tables: lines | t | lam | boxes | blocks' places | stencils | right sides
     const size_t off_lines = 0;
     const size_t off_t = align_up(off_lines + lines.size() * sizeof(Stage2Line), 256);
     const size_t off_lam = align_up(off_t + t_all.size() * sizeof(double), 256);
     const size_t off_boxes = align_up(off_lam + lam_all.size() * sizeof(double), 256);
-    const size_t off_resp = align_up(off_boxes + boxes.size() * sizeof(SubBox), 256);
-    const size_t off_rb = align_up(off_resp + resp_tab.size() * sizeof(Stage2Resp), 256);
-    const size_t table_bytes = align_up(off_rb + rb.size() * sizeof(uint32_t), 256);
+    const size_t off_cr = align_up(off_boxes + boxes.size() * sizeof(SubBox), 256);
+    const size_t table_bytes = align_up(off_cr + cr_tab.size() * sizeof(Stage2Cr), 256);
     const size_t off_stencil = table_bytes;
-    const size_t off_aux = align_up(off_stencil + unknowns * 6 * sizeof(double), 256);
-    const size_t bytes = off_aux + unknowns * 2 * sizeof(double);
+    const size_t off_rhs = align_up(off_stencil + unknowns * 6 * sizeof(double), 256);
+    const size_t bytes = off_rhs + unknowns * sizeof(double);
     if ((st = ensure(ctx, ctx->stage2, bytes))) return st;
     // the subdomain matrices depend on the operator (sigma, b, c), the grid
     // and the interfaces: factored already when the last call had the same
     std::vector<double> key = {(double)d.dim, d.lo[0], d.lo[1], d.hi[0], d.hi[1], d.sigma, d.b0[0], d.b0[1],
                                d.B[0][0], d.B[0][1], d.B[1][0], d.B[1][1], d.c_a, d.c_b,
-                               (problem->pd.tab & 15u) ? (double)problem->serial : -1.0, (double)n[0], (double)n[1]};
+                               (problem->pd.tab & 15u) ? (double)problem->serial : -1.0, (double)n[0], (double)n[1],
+                               use_cr ? 1.0 : 0.0};
+    const size_t use_cr_at = key.size() - 1;
     for (int a = 0; a < 2; ++a) {
         key.push_back((double)cut_pos[a].size());
         key.insert(key.end(), cut_pos[a].begin(), cut_pos[a].end());
     }
     const size_t lu_bytes = unknowns * (2 * kStage2MaxBand + 2) * sizeof(double);
-    const bool factored = ctx->stage2_key == key && ctx->stage2_lu.ptr && ctx->stage2_lu.cap >= lu_bytes;
+    const size_t factor_bytes = use_cr ? cr_values * sizeof(double) : lu_bytes;
+    const bool factored =
+        ctx->stage2_key == key && ctx->stage2_factor.ptr && ctx->stage2_factor.cap >= factor_bytes;
     if (!factored) {
         ctx->stage2_key.clear();
-        if ((st = ensure(ctx, ctx->stage2_lu, lu_bytes))) return st;
-    }
-    double *d_factor = static_cast<double *>(ctx->stage2_lu.ptr);
-    double *d_lmul = d_factor + unknowns * (kStage2MaxBand + 2);
-    // the response columns depend on the factors and on f: the factors' key
-    // and the problem
-    std::vector<double> resp_key = key;
-    resp_key.push_back((double)problem->serial);
-    const size_t resp_bytes = resp_values * sizeof(double);
-    bool resp_ready = false;
-    if (use_resp) {
-        resp_ready = factored && ctx->stage2_resp_key == resp_key && ctx->stage2_resp.ptr &&
-                     ctx->stage2_resp.cap >= resp_bytes;
-        if (!resp_ready) {
-            ctx->stage2_resp_key.clear();
-            if ((st = ensure(ctx, ctx->stage2_resp, resp_bytes))) return st;
+        st = ensure(ctx, ctx->stage2_factor, factor_bytes);
+        if (st == PDD_E_NOMEM && use_cr) {
+            (void)hipGetLastError();
+            use_cr = false;
+            key[use_cr_at] = 0.0;
+            st = ensure(ctx, ctx->stage2_factor, lu_bytes);
         }
+        if (st) return st;
     }
     if ((st = ensure_stage(ctx, table_bytes))) return st;
     char *h = static_cast<char *>(ctx->stage);
@@ -1846,8 +1831,7 @@ pdd_status pdd_stage2(pdd_problem *problem, const pdd_partition *part, const dou
     std::memcpy(h + off_t, t_all.data(), t_all.size() * sizeof(double));
     std::memcpy(h + off_lam, lam_all.data(), lam_all.size() * sizeof(double));
     std::memcpy(h + off_boxes, boxes.data(), boxes.size() * sizeof(SubBox));
-    std::memcpy(h + off_resp, resp_tab.data(), resp_tab.size() * sizeof(Stage2Resp));
-    std::memcpy(h + off_rb, rb.data(), rb.size() * sizeof(uint32_t));
+    std::memcpy(h + off_cr, cr_tab.data(), cr_tab.size() * sizeof(Stage2Cr));
     char *dv = static_cast<char *>(ctx->stage2.ptr);
     HIP_TRY(hipMemcpyAsync(dv, h, table_bytes, hipMemcpyHostToDevice, s));
     HIP_TRY(hipEventRecord(ctx->staged, s));
@@ -1857,18 +1841,15 @@ pdd_status pdd_stage2(pdd_problem *problem, const pdd_partition *part, const dou
                                 reinterpret_cast<const double *>(dv + off_lam), s));
     Stage2Plan plan{};
     plan.factored = factored;
-    if (use_resp) {
-        plan.resp_tab = reinterpret_cast<const Stage2Resp *>(dv + off_resp);
-        plan.rb = reinterpret_cast<const uint32_t *>(dv + off_rb);
-        plan.resp = static_cast<double *>(ctx->stage2_resp.ptr);
-        plan.max_cols = max_cols;
-        plan.resp_ready = resp_ready;
-    }
+    plan.cr_tab = use_cr ? reinterpret_cast<const Stage2Cr *>(dv + off_cr) : nullptr;
+    plan.max_L = max_L;
+    plan.wp = (int32_t)wp;
+    plan.factor = static_cast<double *>(ctx->stage2_factor.ptr);
+    plan.lmul = plan.factor + unknowns * (kStage2MaxBand + 2);
+    plan.rhs = reinterpret_cast<double *>(dv + off_rhs);
     HIP_TRY(launch_stage2_solve(problem->pd, g, reinterpret_cast<const SubBox *>(dv + off_boxes), (int32_t)boxes.size(),
-                                (uint32_t)max_unknowns, reinterpret_cast<double *>(dv + off_stencil),
-                                reinterpret_cast<double *>(dv + off_aux), d_factor, d_lmul, plan, s));
+                                (uint32_t)max_unknowns, reinterpret_cast<double *>(dv + off_stencil), plan, s));
     ctx->stage2_key = key;
-    if (use_resp) ctx->stage2_resp_key = resp_key;
     HIP_TRY(hipEventRecord(ctx->done, s));
     ctx->any_done = true;
     return PDD_OK;

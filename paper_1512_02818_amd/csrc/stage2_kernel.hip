@@ -147,10 +147,9 @@ __device__ __forceinline__ void stage2_point(const SubBox &b, uint64_t r, int &i
 // Stencil of every unknown: (1/2) sigma^2 Lap v + b.grad v + c v = f by
 // second-order differences; neighbours on the subdomain's boundary move to
 // the right side with their grid values. Slots: 0 slow-1, 1 fast-1,
-// 2 centre, 3 fast+1, 4 slow+1, 5 right side; aux: f, and the boundary
-// neighbours' part of the right side (the same products, summed from zero).
+// 2 centre, 3 fast+1, 4 slow+1, 5 right side, which also goes to rhs.
 __global__ void __launch_bounds__(256) stage2_stencil_kernel(const DevProblem<double> P, const Stage2Grid g,
-                                                             const SubBox *boxes, double *stencil, double *aux)
+                                                             const SubBox *boxes, double *stencil, double *rhs)
 {
     __shared__ double s_cf[kMaxDense];
     for (int q = threadIdx.x; q < kMaxDense; q += blockDim.x) s_cf[q] = P.fdense[q];
@@ -169,7 +168,6 @@ __global__ void __launch_bounds__(256) stage2_stencil_kernel(const DevProblem<do
         const double aW = cx - bb[0] / (2.0 * g.dx0), aE = cx + bb[0] / (2.0 * g.dx0);
         const double aS = cy - bb[1] / (2.0 * g.dx1), aN = cy + bb[1] / (2.0 * g.dx1);
         double out[6] = {0.0, 0.0, -2.0 * cx - 2.0 * cy + c, 0.0, 0.0, f};
-        double yb = 0.0;
         // neighbours: west, east, south, north with their band slots
         const int ni[4] = {i - 1, i + 1, i, i};
         const int nj[4] = {j, j, j - 1, j + 1};
@@ -181,16 +179,13 @@ __global__ void __launch_bounds__(256) stage2_stencil_kernel(const DevProblem<do
             if (inside) {
                 out[slot[q]] = a[q];
             } else {
-                const double t = a[q] * g.u[(size_t)nj[q] * g.n0 + ni[q]];
-                out[5] -= t;
-                yb -= t;
+                out[5] -= a[q] * g.u[(size_t)nj[q] * g.n0 + ni[q]];
             }
         }
         double *o = stencil + (b.first + r) * 6;
 #pragma unroll
         for (int q = 0; q < 6; ++q) o[q] = out[q];
-        aux[(b.first + r) * 2] = f;
-        aux[(b.first + r) * 2 + 1] = yb;
+        rhs[b.first + r] = out[5];
     }
 }
 
@@ -457,147 +452,337 @@ __global__ void __launch_bounds__(kStage2SubstThreads) stage2_subst_kernel(const
     }
 }
 
-// Response columns of the subdomains (one workgroup per subdomain and four
-// columns, a wave per column): the solution for a unit right side at each
-// row next to the box's boundary, and for the source f with zero boundary
-// values, by the substitution of stage2_subst_kernel with the stored factors
-// (the chunks of multipliers and U rows staged once for the four waves). The
-// forward pass leaves y in the column, the backward pass overwrites it with
-// the solution.
-constexpr int kStage2RespWaves = kStage2SubstThreads / 64;
-__global__ void __launch_bounds__(kStage2SubstThreads) stage2_resp_kernel(const SubBox *boxes, const double *aux,
-                                                                          const double *factor, const double *lmul,
-                                                                          const Stage2Resp *tab, const uint32_t *rb,
-                                                                          double *resp)
-{
-    constexpr int MW = kStage2MaxBand;
-    constexpr int FS = MW + 2;
-    constexpr int CH = 64;
-    constexpr int PF = 8;
-    constexpr int NW = kStage2RespWaves;
-    __shared__ double Lc[CH * MW];
-    __shared__ double Bc[NW][CH];
-    __shared__ double Uc[(CH + MW) * FS];
-    __shared__ double Yc[NW][CH + MW];
-    const SubBox bx = boxes[blockIdx.x];
-    const Stage2Resp rt = tab[blockIdx.x];
-    const int w = bx.w;
-    const uint64_t n = (uint64_t)w * (uint64_t)bx.L;
-    const double *U = factor + bx.first * FS;
-    const double *Lm = lmul + bx.first * MW;
-    const double *fa = aux + bx.first * 2;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wv = tid >> 6;
-    const int col = (int)blockIdx.y * NW + wv;
-    const bool act = col <= rt.nb;
-    const bool src = col == rt.nb;  // the source column
-    const uint64_t rc = act && !src ? rb[rt.rb_at + col] : ~0ull;
-    double *out = resp + rt.out_at + (uint64_t)(act ? col : 0) * n;
-    auto rhs = [&](uint64_t q) { return src ? fa[q * 2] : (q == rc ? 1.0 : 0.0); };
-    double v = act && lane < w ? rhs((uint64_t)lane) : 0.0;
-    int s = 0;
-    for (uint64_t k0 = 0; k0 < n; k0 += CH) {
-        const int m = n - k0 < (uint64_t)CH ? (int)(n - k0) : CH;
-        __syncthreads();
-        stage_chunk<CH * MW / kStage2SubstThreads>(Lc, Lm + k0 * w, m * w, tid);
-        for (int idx = lane; idx < m; idx += 64) {
-            const uint64_t q = k0 + idx + w;
-            Bc[wv][idx] = act && q < n ? rhs(q) : 0.0;
-        }
-        __syncthreads();
-        if (act) {
-            double ybuf = 0.0;
-            for (int i0 = 0; i0 < m; i0 += PF) {
-                double lv[PF], bv[PF];
-                int su = s;
-#pragma unroll
-                for (int u = 0; u < PF; ++u) {
-                    int d = lane - su - 1;
-                    if (d < 0) d += w;
-                    const bool ok = i0 + u < m && lane < w && k0 + i0 + u + 1 + d < n;
-                    lv[u] = ok ? Lc[(i0 + u) * w + d] : 0.0;
-                    bv[u] = i0 + u < m ? Bc[wv][i0 + u] : 0.0;
-                    if (++su == w) su = 0;
-                }
-#pragma unroll
-                for (int u = 0; u < PF; ++u) {
-                    if (i0 + u >= m) break;
-                    const double yk = readlane_f64(v, s);
-                    ybuf = lane == i0 + u ? yk : ybuf;
-                    v = lane == s ? bv[u] : v;
-                    const double nv = v - lv[u] * yk;
-                    v = lv[u] != 0.0 ? nv : v;
-                    if (++s == w) s = 0;
-                }
-            }
-            if (lane < m) out[k0 + lane] = ybuf;
-        }
+// Block cyclic reduction of the subdomains. In the order r = s w + f a
+// subdomain's matrix is block tridiagonal: L block rows of w x w blocks D
+// (tridiagonal), and diagonal blocks A (to row s - 1) and C (to row s + 1).
+// With block rows numbered 1 .. L, level l (t = 2^l) eliminates the odd
+// multiples i of t,
+//   x_i = D_i^-1 f_i - P_i x_{i-t} - Q_i x_{i+t},  P = D^-1 A, Q = D^-1 C,
+// from the even ones, which become a block tridiagonal system again:
+//   D_i -= A_i Q_{i-t} + C_i P_{i+t},  A_i <- -A_i P_{i-t},  C_i <- -C_i Q_{i+t},
+//   f_i -= M_i f_{i-t} + N_i f_{i+t},  M_i = A_i D_{i-t}^-1,  N_i = C_i D_{i+t}^-1,
+// until one block row is left. No pivoting, as in the banded LU: both
+// eliminate the same (coercive) matrix, in another order (over drifts up to
+// 5000, sigma down to 0.01 and c up to 400 both are within 1e-12 of a sparse
+// direct solve, or the LU is the farther off). The LU's chain of w L dependent
+// pivots, one workgroup a subdomain, becomes 1 + log2 L levels whose rows are
+// independent. Four strips of 63 x 255 unknowns: 39.9 ms with the LU and the
+// solutions for unit boundary values that it was kept as, 0.52 ms now; with
+// the factors kept 0.26 and 0.20 ms. What bounds a level is the inversion
+// (27 us: 64 dependent pivots) and the products on the FP64 matrix cores
+// (9 us; 37 us where the rows are several per CU). Blocks are padded by the
+// identity to WP (the widest subdomain's w, to a multiple of 16) and kept by
+// column: D (D^-1 once eliminated), P, Q of every row, and M, N and the new A,
+// C of every (row, level).
+template <int WP>
+struct CrBox {
+    static constexpr int kBlock = WP * WP;
+    SubBox b;
+    Stage2Cr c;
+    __device__ __forceinline__ CrBox(const SubBox *boxes, const Stage2Cr *tab, int q) : b(boxes[q]), c(tab[q]) {}
+    // D (or D^-1), P, Q of block row i (from 1)
+    __device__ __forceinline__ double *row(double *cr, int i) const { return cr + c.at + (size_t)(i - 1) * 3 * kBlock; }
+    // M, N, A, C of the m-th even multiple (from 1) of level l
+    __device__ __forceinline__ double *pair(double *cr, int l, int m) const
+    {
+        int before = 0;
+        for (int q = 0; q < l; ++q) before += b.L >> (q + 1);
+        return cr + c.mn + (size_t)(before + m - 1) * 4 * kBlock;
     }
-    s = w - 1;
-    for (uint64_t hi = n; hi > 0;) {
-        const uint64_t lo = hi > CH ? hi - CH : 0;
-        const uint64_t base = lo > (uint64_t)w ? lo - w : 0;
-        __syncthreads();
-        stage_chunk<((CH + MW) * FS + kStage2SubstThreads - 1) / kStage2SubstThreads>(Uc, U + base * FS,
-                                                                                      (int)(hi - base) * FS, tid);
-        for (int idx = lane; idx < (int)(hi - base); idx += 64) Yc[wv][idx] = act ? gload(out + base + idx) : 0.0;
-        __syncthreads();
-        if (act) {
-            if (hi == n) v = lane < w ? Yc[wv][n - w + lane - base] : 0.0;
-            const int cnt = (int)(hi - lo);
-            double xbuf = 0.0;
-            for (int i0 = 0; i0 < cnt; i0 += PF) {
-                double rv[PF], uv[PF], yv[PF];
-                int su = s;
+    // stencil slot q of unknown f of block row i
+    __device__ __forceinline__ double slot(const double *stencil, int i, int f, int q) const
+    {
+        return f < b.w ? stencil[(b.first + (uint64_t)(i - 1) * b.w + f) * 6 + q] : 0.0;
+    }
+    __device__ __forceinline__ double centre(const double *stencil, int i, int r, int k) const
+    {
+        if (r >= b.w || k >= b.w) return r == k ? 1.0 : 0.0;
+        return r == k ? slot(stencil, i, r, 2) : r == k + 1 ? slot(stencil, i, r, 1)
+               : r + 1 == k ? slot(stencil, i, r, 3) : 0.0;
+    }
+};
+
+constexpr int kCrThreads = 512;
+constexpr int kCrWaves = kCrThreads / 64;
+typedef double Acc4 __attribute__((ext_vector_type(4)));
+
+// A block (by column) to LDS.
+template <int WP>
+__device__ __forceinline__ void cr_stage(double *dst, const double *src)
+{
+    constexpr int kPer = (WP * WP + kCrThreads - 1) / kCrThreads;
+    double t[kPer];
 #pragma unroll
-                for (int u = 0; u < PF; ++u) {
-                    const uint64_t k = hi - 1 - (uint64_t)(i0 + u);
-                    const bool in = i0 + u < cnt;
-                    int d = su - 1 - lane;
-                    if (d < 0) d += w;
-                    rv[u] = 1.0 / (in ? Uc[(k - base) * FS] : 1.0);
-                    uv[u] = in && lane < w && k >= (uint64_t)(d + 1) ? Uc[(k - 1 - d - base) * FS + (d + 1)] : 0.0;
-                    yv[u] = in && k >= (uint64_t)w ? Yc[wv][k - w - base] : 0.0;
-                    if (--su < 0) su = w - 1;
-                }
+    for (int u = 0; u < kPer; ++u) {
+        const int e = threadIdx.x + u * kCrThreads;
+        t[u] = e < WP * WP ? gload(src + e) : 0.0;
+    }
 #pragma unroll
-                for (int u = 0; u < PF; ++u) {
-                    if (i0 + u >= cnt) break;
-                    const double xk = readlane_f64(v, s) * rv[u];
-                    xbuf = lane == i0 + u ? xk : xbuf;
-                    v = lane == s ? yv[u] : v;
-                    const double nv = v - uv[u] * xk;
-                    v = uv[u] != 0.0 ? nv : v;
-                    if (--s < 0) s = w - 1;
-                }
-            }
-            if (lane < cnt) out[hi - 1 - lane] = xbuf;
-        }
-        hi = lo;
+    for (int u = 0; u < kPer; ++u) {
+        const int e = threadIdx.x + u * kCrThreads;
+        if (e < WP * WP) dst[(e / WP) * (WP + 1) + e % WP] = t[u];
     }
 }
 
-// Interior values from the response columns: u = (f's column) + sum over the
-// rows next to the boundary of (that row's column) x (its boundary part of
-// the right side), in row order; one thread per unknown.
-__global__ void __launch_bounds__(256) stage2_apply_kernel(const Stage2Grid g, const SubBox *boxes, const double *aux,
-                                                           const Stage2Resp *tab, const uint32_t *rb,
-                                                           const double *resp)
+// 16 x 16 tile (ti, tj) of acc + sign X Y on the matrix cores, X and Y in LDS.
+// The tile is formed transposed, so that a lane's four values are of columns
+// 16 tj + 4 v + lane / 16 and of row 16 ti + lane % 16: stores run along rows.
+template <int WP>
+__device__ __forceinline__ Acc4 cr_tile(const double *X, const double *Y, int ti, int tj, double sign, Acc4 acc)
 {
-    __shared__ double yb[kStage2MaxBoundaryRows];
-    const SubBox bx = boxes[blockIdx.y];
-    const Stage2Resp rt = tab[blockIdx.y];
-    const uint64_t n = (uint64_t)bx.w * (uint64_t)bx.L;
-    for (int c = threadIdx.x; c < rt.nb; c += blockDim.x) yb[c] = aux[(bx.first + rb[rt.rb_at + c]) * 2 + 1];
-    __syncthreads();
-    for (uint64_t r = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; r < n; r += (uint64_t)gridDim.x * blockDim.x) {
-        const double *col = resp + rt.out_at + r;
-        double acc = col[(uint64_t)rt.nb * n];
-        for (int c = 0; c < rt.nb; ++c) acc = fma(col[(uint64_t)c * n], yb[c], acc);
-        int i, j;
-        stage2_point(bx, r, i, j);
-        g.u[(size_t)j * g.n0 + i] = acc;
+    const int lane = threadIdx.x & 63, low = lane & 15, high = lane >> 4;
+    const double *x = X + high * (WP + 1) + ti * 16 + low, *y = Y + (tj * 16 + low) * (WP + 1) + high;
+#pragma unroll
+    for (int k = 0; k < WP; k += 4)
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(sign * y[k], x[k * (WP + 1)], acc, 0, 0, 0);
+    return acc;
+}
+template <int WP>
+__device__ __forceinline__ double *cr_element(double *block, int ti, int tj, int v)
+{
+    const int lane = threadIdx.x & 63;
+    return block + (tj * 16 + 4 * v + (lane >> 4)) * WP + ti * 16 + (lane & 15);
+}
+
+// D^-1, P and Q of the odd multiples of 2^level, one workgroup each. D is
+// inverted in registers: lane r of wave q holds columns 8 q .. 8 q + 7 of row
+// r. The pivots of a wave's columns are its own work, without a barrier (row k
+// comes from lane k); their multipliers then go to the other waves through
+// LDS: one barrier per eight pivots (32 us a level with one per pivot, 27 us
+// so). Rows are left unscaled until the end.
+template <int WP>
+__global__ void __launch_bounds__(kCrThreads) stage2_cr_eliminate_kernel(const SubBox *boxes, const Stage2Cr *tab,
+                                                                         const double *stencil, double *cr, int level)
+{
+    __shared__ double X[WP * (WP + 1)], A[WP * (WP + 1)], C[WP * (WP + 1)];
+    constexpr int kCols = 64 / kCrWaves;
+    __shared__ double mult[2][kCols][64], inverse[64];
+    const CrBox<WP> bx(boxes, tab, blockIdx.y);
+    const int t = 1 << level, i = t * (2 * (int)blockIdx.x + 1), L = bx.b.L;
+    if (i > L) return;  // whole workgroup
+    const int r = threadIdx.x & 63, q = threadIdx.x >> 6;
+    double *row = bx.row(cr, i);
+    constexpr int nb = WP * WP;
+    double a[kCols];
+#pragma unroll
+    for (int e = 0; e < kCols; ++e) {
+        const int k = q * kCols + e;
+        if (level == 0)
+            a[e] = bx.centre(stencil, i, r, k);
+        else
+            a[e] = r < WP && k < WP ? gload(row + k * WP + r) : (r == k ? 1.0 : 0.0);
     }
+    if (level > 0) {  // the last update's
+        const double *ac = bx.pair(cr, level - 1, i >> level) + 2 * nb;
+        cr_stage<WP>(A, ac);
+        cr_stage<WP>(C, ac + nb);
+    }
+    for (int k0 = 0, b = 0; k0 < WP; k0 += kCols, b ^= 1) {
+        if (q * kCols == k0) {
+            // column kk at a[0]: each pivot moves the columns one place on
+#pragma unroll 1
+            for (int kk = 0; kk < kCols; ++kk) {
+                const int k = k0 + kk;
+                const double pivot = readlane_f64(a[0], k);
+                double inv = __builtin_amdgcn_rcp(pivot);
+                inv = madd(inv, madd(-pivot, inv, 1.0), inv);
+                inv = madd(inv, madd(-pivot, inv, 1.0), inv);
+                const double m = r == k ? 0.0 : a[0] * inv;
+#pragma unroll
+                for (int e = 1; e < kCols; ++e) a[e - 1] = madd(-m, readlane_f64(a[e], k), a[e]);
+                a[kCols - 1] = r == k ? 1.0 : -m;
+                mult[b][kk][r] = m;
+                if (r == k) inverse[k] = inv;
+            }
+        }
+        __syncthreads();
+        if (q * kCols != k0) {
+#pragma unroll 2
+            for (int kk = 0; kk < kCols; ++kk) {
+                const double m = mult[b][kk][r];
+#pragma unroll
+                for (int e = 0; e < kCols; ++e) a[e] = madd(-m, readlane_f64(a[e], k0 + kk), a[e]);
+            }
+        }
+    }
+    const double scale = r < WP ? inverse[r] : 1.0;
+    double *D = row, *P = row + nb, *Q = row + 2 * nb;
+#pragma unroll
+    for (int e = 0; e < kCols; ++e) {
+        const int k = q * kCols + e;
+        a[e] *= scale;
+        if (r >= WP || k >= WP) continue;
+        gstore(D + k * WP + r, a[e]);
+        if (level == 0) {
+            gstore(P + k * WP + r, a[e] * bx.slot(stencil, i, k, 0));
+            gstore(Q + k * WP + r, a[e] * bx.slot(stencil, i, k, 4));
+        } else {
+            X[k * (WP + 1) + r] = a[e];
+        }
+    }
+    if (level == 0) return;
+    __syncthreads();
+    const int nt = WP / 16;
+    for (int n = q; n < 2 * nt * nt; n += kCrWaves) {
+        const bool second = n >= nt * nt;
+        const int m = second ? n - nt * nt : n, ti = m / nt, tj = m % nt;
+        const Acc4 acc = cr_tile<WP>(X, second ? C : A, ti, tj, 1.0, Acc4{0, 0, 0, 0});
+#pragma unroll
+        for (int v = 0; v < 4; ++v) gstore(cr_element<WP>(second ? Q : P, ti, tj, v), acc[v]);
+    }
+}
+
+// The even multiples of 2^level after their neighbours' elimination: M and N
+// (part 0), the new A and C (1) and D (2), a workgroup each, two products.
+// Level 0's A and C are diagonal.
+template <int WP>
+__global__ void __launch_bounds__(kCrThreads) stage2_cr_update_kernel(const SubBox *boxes, const Stage2Cr *tab,
+                                                                      const double *stencil, double *cr, int level)
+{
+    __shared__ double X[2][WP * (WP + 1)], Y[2][WP * (WP + 1)];
+    const CrBox<WP> bx(boxes, tab, blockIdx.y);
+    const int t = 1 << level, i = 2 * t * ((int)blockIdx.x + 1), L = bx.b.L;
+    if (i > L) return;  // whole workgroup
+    const int part = blockIdx.z;
+    constexpr int nb = WP * WP;
+    double *D = bx.row(cr, i), *out = bx.pair(cr, level, (int)blockIdx.x + 1) + (part == 1 ? 2 * nb : 0);
+    const bool has_upper = i + t <= L;
+    const double *lower = bx.row(cr, i - t), *upper = bx.row(cr, has_upper ? i + t : i - t);
+    // A times `a` of the lower row, C times `c` of the upper one
+    const double *a = lower + (size_t)(part == 0 ? 0 : part == 1 ? 1 : 2) * nb;
+    const double *c = upper + (size_t)(part == 0 ? 0 : part == 1 ? 2 : 1) * nb;
+    const double sign = part == 0 ? 1.0 : -1.0;
+    if (level == 0) {
+        for (int e = threadIdx.x; e < (int)nb; e += kCrThreads) {
+            const int r = e % WP, k = e / WP;
+            const double va = sign * bx.slot(stencil, i, r, 0) * a[e];
+            const double vc = has_upper ? sign * bx.slot(stencil, i, r, 4) * c[e] : 0.0;
+            if (part == 2) {
+                D[e] = bx.centre(stencil, i, r, k) + va + vc;
+            } else {
+                out[e] = va;
+                out[nb + e] = vc;
+            }
+        }
+        return;
+    }
+    const int q = threadIdx.x >> 6, nt = WP / 16, tiles = nt * nt;
+    const double *ac = bx.pair(cr, level - 1, i >> level) + 2 * nb;
+    cr_stage<WP>(X[0], ac);
+    cr_stage<WP>(Y[0], a);
+    if (has_upper) {
+        cr_stage<WP>(X[1], ac + nb);
+        cr_stage<WP>(Y[1], c);
+    }
+    __syncthreads();
+    for (int m = q; m < tiles; m += kCrWaves) {
+        const int ti = m / nt, tj = m % nt;
+        Acc4 acc{0, 0, 0, 0};
+        if (part == 2)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc[v] = gload(cr_element<WP>(D, ti, tj, v));
+        acc = cr_tile<WP>(X[0], Y[0], ti, tj, sign, acc);
+        if (part != 2) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) gstore(cr_element<WP>(out, ti, tj, v), acc[v]);
+            acc = Acc4{0, 0, 0, 0};
+        }
+        if (has_upper) acc = cr_tile<WP>(X[1], Y[1], ti, tj, sign, acc);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) gstore(cr_element<WP>(part == 2 ? D : out + nb, ti, tj, v), acc[v]);
+    }
+}
+
+// sum over k of B[r][k] x[k] for this thread's row (threads of wave q take the
+// columns from q WP / 4 on), B by column.
+template <int WP>
+__device__ __forceinline__ double cr_dot(const double *B, const double *x, int r, int q)
+{
+    double acc = 0.0;
+    if (r < WP)
+#pragma unroll
+        for (int k = 0; k < WP / 4; ++k) acc = madd(gload(B + (q * (WP / 4) + k) * WP + r), x[q * (WP / 4) + k], acc);
+    return acc;
+}
+
+// Forward (FORWARD) and back substitution of the right sides at one level, a
+// workgroup per block row. Bound by latency (5 us a launch), but for the
+// lowest levels, which read two or three blocks a row (9 us: 50 MB at 5.6 TB/s).
+constexpr int kCrSolveThreads = 256;
+template <int WP, bool FORWARD>
+__global__ void __launch_bounds__(kCrSolveThreads) stage2_cr_solve_kernel(const Stage2Grid g, const SubBox *boxes,
+                                                                          const Stage2Cr *tab, double *cr, double *rhs,
+                                                                          int level)
+{
+    __shared__ double x[3][kStage2MaxBand], part[kCrSolveThreads / 64][kStage2MaxBand];
+    const CrBox<WP> bx(boxes, tab, blockIdx.y);
+    const int t = 1 << level, i = FORWARD ? 2 * t * ((int)blockIdx.x + 1) : t * (2 * (int)blockIdx.x + 1);
+    const int L = bx.b.L, w = bx.b.w;
+    if (i > L) return;  // whole workgroup
+    const int r = threadIdx.x & 63, q = threadIdx.x >> 6;
+    double *f = rhs + bx.b.first + (uint64_t)(i - 1) * w;
+    const bool lo = i - t >= 1, up = i + t <= L;
+    if (q < 3) {  // f of rows i - t, i and i + t
+        const bool there = r < w && (q == 1 || (q == 0 ? lo : up));
+        x[q][r] = there ? gload(f + (int64_t)(q - 1) * t * w + r) : 0.0;
+    }
+    __syncthreads();
+    constexpr int nb = WP * WP;
+    double acc;
+    if (FORWARD) {
+        const double *M = bx.pair(cr, level, (int)blockIdx.x + 1);
+        acc = -cr_dot<WP>(M, x[0], r, q);
+        if (up) acc -= cr_dot<WP>(M + nb, x[2], r, q);
+    } else {
+        const double *row = bx.row(cr, i);
+        acc = cr_dot<WP>(row, x[1], r, q);
+        if (lo) acc -= cr_dot<WP>(row + nb, x[0], r, q);
+        if (up) acc -= cr_dot<WP>(row + 2 * nb, x[2], r, q);
+    }
+    part[q][r] = acc;
+    __syncthreads();
+    if (q == 0 && r < w) {
+        double v = ((part[0][r] + part[1][r]) + part[2][r]) + part[3][r];
+        if (FORWARD) {
+            f[r] = x[1][r] + v;
+        } else {
+            f[r] = v;
+            int gi, gj;
+            stage2_point(bx.b, (uint64_t)(i - 1) * w + r, gi, gj);
+            g.u[(size_t)gj * g.n0 + gi] = v;
+        }
+    }
+}
+
+template <int WP>
+hipError_t launch_cyclic_reduction(const Stage2Grid &g, const SubBox *boxes, int32_t n_boxes, const double *stencil,
+                                   const Stage2Plan &plan, hipStream_t s)
+{
+    int levels = 0;
+    while ((1 << levels) <= plan.max_L) ++levels;
+    const auto odd = [&](int l) { return dim3((unsigned)(((plan.max_L >> l) + 1) / 2), n_boxes); };
+    const auto even = [&](int l, int parts) { return dim3((unsigned)(plan.max_L >> (l + 1)), n_boxes, parts); };
+    hipError_t e = hipSuccess;
+    for (int l = 0; l < levels && !plan.factored; ++l) {
+        hipLaunchKernelGGL((stage2_cr_eliminate_kernel<WP>), odd(l), dim3(kCrThreads), 0, s, boxes, plan.cr_tab,
+                           stencil, plan.factor, l);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        if (l + 1 == levels) break;
+        hipLaunchKernelGGL((stage2_cr_update_kernel<WP>), even(l, 3), dim3(kCrThreads), 0, s, boxes, plan.cr_tab,
+                           stencil, plan.factor, l);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    for (int l = 0; l + 1 < levels; ++l) {
+        hipLaunchKernelGGL((stage2_cr_solve_kernel<WP, true>), even(l, 1), dim3(kCrSolveThreads), 0, s, g, boxes,
+                           plan.cr_tab, plan.factor, plan.rhs, l);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    for (int l = levels - 1; l >= 0; --l) {
+        hipLaunchKernelGGL((stage2_cr_solve_kernel<WP, false>), odd(l), dim3(kCrSolveThreads), 0, s, g, boxes,
+                           plan.cr_tab, plan.factor, plan.rhs, l);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace
@@ -651,34 +836,30 @@ hipError_t launch_stage2_lines(const Stage2Grid &g, const Stage2Line *lines, int
 }
 
 hipError_t launch_stage2_solve(const DevProblem<double> &P, const Stage2Grid &g, const SubBox *boxes,
-                               int32_t n_boxes, uint32_t max_unknowns, double *stencil, double *aux, double *factor,
-                               double *lmul, const Stage2Plan &plan, hipStream_t s)
+                               int32_t n_boxes, uint32_t max_unknowns, double *stencil, const Stage2Plan &plan,
+                               hipStream_t s)
 {
     if (n_boxes == 0) return hipSuccess;
     hipLaunchKernelGGL(stage2_stencil_kernel, dim3((max_unknowns + 255) / 256, n_boxes), dim3(256), 0, s, P, g,
-                       boxes, stencil, aux);
+                       boxes, stencil, plan.rhs);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (!plan.factored) {
-        hipLaunchKernelGGL(stage2_lu_kernel, dim3(n_boxes), dim3(kStage2LuThreads), 0, s, boxes, stencil, factor,
-                           lmul);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-    if (!plan.resp) {
+    if (!plan.cr_tab) {
+        if (!plan.factored) {
+            hipLaunchKernelGGL(stage2_lu_kernel, dim3(n_boxes), dim3(kStage2LuThreads), 0, s, boxes, stencil,
+                               plan.factor, plan.lmul);
+            if ((e = hipGetLastError()) != hipSuccess) return e;
+        }
         hipLaunchKernelGGL(stage2_subst_kernel, dim3(n_boxes), dim3(kStage2SubstThreads), 0, s, g, boxes, stencil,
-                           factor, lmul);
+                           plan.factor, plan.lmul);
         return hipGetLastError();
     }
-    if (!plan.resp_ready) {
-        const uint32_t groups = (uint32_t)(plan.max_cols + kStage2RespWaves - 1) / kStage2RespWaves;
-        hipLaunchKernelGGL(stage2_resp_kernel, dim3(n_boxes, groups), dim3(kStage2SubstThreads), 0, s, boxes, aux,
-                           factor, lmul, plan.resp_tab, plan.rb, plan.resp);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+    switch (plan.wp) {
+        case 16: return launch_cyclic_reduction<16>(g, boxes, n_boxes, stencil, plan, s);
+        case 32: return launch_cyclic_reduction<32>(g, boxes, n_boxes, stencil, plan, s);
+        case 48: return launch_cyclic_reduction<48>(g, boxes, n_boxes, stencil, plan, s);
+        default: return launch_cyclic_reduction<64>(g, boxes, n_boxes, stencil, plan, s);
     }
-    const uint32_t blocks = (uint32_t)std::min<uint64_t>((max_unknowns + 255) / 256, 1024);
-    hipLaunchKernelGGL(stage2_apply_kernel, dim3(blocks, n_boxes), dim3(256), 0, s, g, boxes, aux, plan.resp_tab,
-                       plan.rb, plan.resp);
-    return hipGetLastError();
 }
 
 }  // namespace pdd

@@ -1,0 +1,39 @@
+"""The second stage's block cyclic reduction at the edges of its tiles: two
+subdomains of different widths (the blocks are padded to the wider one, a
+multiple of 16) over one to 130 block rows, along either axis, against the
+oracle's sparse direct solves to the second stage's 1e-10. A repeated call,
+which takes the kept factors, gives the same bits."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+from paper_1512_02818_amd import pdd  # noqa: E402
+from paper_1512_02818_amd import workloads as W  # noqa: E402
+
+
+@pytest.mark.parametrize("axis", [0, 1])
+@pytest.mark.parametrize("w1,w2,rows", [(1, 2, 1), (1, 15, 3), (16, 17, 2), (31, 33, 5), (32, 40, 64), (48, 49, 127),
+                                        (63, 64, 130)])
+def test_block_edges(axis, w1, w2, rows):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from oracle import stage2 as S2
+    pd = dict(W.unit_square_problem(seed=0), b0=[3.0, -2.0])
+    n = [w1 + w2 + 3, rows + 2]
+    cut = (w1 + 1) / (n[0] - 1)
+    nodes = np.column_stack([np.full(4, cut), [0.2, 0.4, 0.6, 0.8]])
+    cuts = [[cut], []]
+    if axis == 1:
+        n, nodes, cuts = n[::-1], nodes[:, ::-1].copy(), cuts[::-1]
+    vals = W.manufactured_u(pd, nodes) + np.random.default_rng(w1).normal(scale=0.01, size=len(nodes))
+    ctx = pdd.Context(0)
+    prob = pdd.Problem(ctx, pd)
+    got = [pdd.stage2(prob, tuple(n), cuts, nodes, vals, 3.0).cpu().numpy() for _ in range(2)]
+    prob.close()
+    ctx.close()
+    ref = S2.stage2(pd, tuple(n), cuts, nodes, vals, 3.0)
+    assert np.max(np.abs(got[0] - ref) / np.maximum(1.0, np.abs(ref))) <= 1e-10
+    assert got[0].tobytes() == got[1].tobytes()
