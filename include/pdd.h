@@ -462,11 +462,9 @@ typedef struct {
  * more than 8 GiB or cannot be allocated, or with PDD_STAGE2_SUBSTITUTE=1 in the environment, a
  * banded LU, one workgroup per subdomain, takes their place. The result
  * equals a direct solve to rounding (the same in a fresh context and in a
- * kept one, bit for bit). `nodes` (host,
- * n_nodes x 2) are the interface nodes and `values` (host) their nodal
- * values; a node may lie on several lines. Synchronous (the interpolation
- * weights are solved on the host once the boundary values are on the
- * device); u is complete when the call returns. Errors: PDD_E_INVALID for
+ * kept one, bit for bit). `nodes` (host, n_nodes x 2) are the interface nodes
+ * and `values` (host) their nodal values; a node may lie on several lines.
+ * Synchronous; u is complete when the call returns. Errors: PDD_E_INVALID for
  * NULL pointers, a bad grid or shape parameter, an interface off the grid
  * lines or given twice, a node off every interface or outside the box, a
  * singular interpolation system; PDD_E_UNSUPPORTED for a problem that is not

@@ -331,14 +331,24 @@ struct SubBox {
 constexpr int kStage2MaxBand = 64;  // shorter interior side of a subdomain, at most
 // One interface line for the interpolation: axis d (the line is x_d = const at
 // grid index k), m data points at coordinates t[0..m-1] along the other axis
-// with multiquadric weights lam[0..m-1] (at offset `at` in the tables).
+// with multiquadric weights lam[0..m-1] (at offset `at` in the tables; before
+// the weights are solved for: the data points' values). `matrix`: offset of
+// its system's m x (m + 1) doubles in launch_stage2_weights' buffer, where m >
+// kStage2MaxLdsNodes.
 struct Stage2Line {
     int32_t d, k, m, pad;
-    uint64_t at;
+    uint64_t at, matrix;
     double eps;
 };
+constexpr int kStage2MaxLdsNodes = 136;
 // Physical-boundary values g of the grid (every point of the box's edges).
 hipError_t launch_stage2_boundary(const DevProblem<double> &P, const Stage2Grid &g, hipStream_t s);
+// The lines' multiquadric weights from their values; the values at a line's
+// ends are taken from u's boundary first. marks[q] (host memory that
+// the device can write): 1 where line q's system is singular (its weights are
+// zero then), else 0.
+hipError_t launch_stage2_weights(const Stage2Grid &g, const Stage2Line *lines, int32_t n_lines, const double *t,
+                                 double *lam, double *matrices, int32_t *marks, hipStream_t s);
 // Interface lines: the multiquadric interpolants at the grid points of each
 // line between the box's edges; a point where an axis-0 and an axis-1 line
 // cross takes the mean of the two.

@@ -1710,64 +1710,31 @@ pdd_status pdd_stage2(pdd_problem *problem, const pdd_partition *part, const dou
     g.half_s2 = 0.5 * d.sigma * d.sigma;
     // physical boundary first: the ends of every interface line carry g
     HIP_TRY(launch_stage2_boundary(problem->pd, g, s));
-    const size_t grid_bytes = (size_t)n[0] * n[1] * sizeof(double);
     pdd_status st;
-    if ((st = ensure_stage(ctx, grid_bytes))) return st;
-    double *hg = static_cast<double *>(ctx->stage);
-    HIP_TRY(hipMemcpyAsync(hg, u, grid_bytes, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    // multiquadric weights of every line (host: small dense systems)
+    // every line's data points: its ends (their values are filled in on the
+    // device) and its nodes
     std::vector<Stage2Line> lines;
-    std::vector<double> t_all, lam_all;
+    std::vector<double> t_all, z_all, line_pos;
+    size_t weights_values = 0;  // of the systems too large for LDS
     for (int a = 0; a < 2; ++a)
         for (size_t q = 0; q < cut_pos[a].size(); ++q) {
-            const int e = 1 - a, k = cut_idx[a][q];
-            std::vector<double> t, z;
-            t.push_back(d.lo[e]);
-            z.push_back(a == 0 ? hg[k] : hg[(size_t)k * n[0]]);
+            const int e = 1 - a;
+            Stage2Line L{};
+            L.d = a, L.k = cut_idx[a][q], L.at = t_all.size(), L.eps = part->rbf_eps;
+            t_all.push_back(d.lo[e]);
+            z_all.push_back(0.0);
             for (int64_t i = 0; i < n_nodes; ++i)
                 if (on_line(nodes[2 * i + a], cut_pos[a][q])) {
-                    t.push_back(nodes[2 * i + e]);
-                    z.push_back(values[i]);
+                    t_all.push_back(nodes[2 * i + e]);
+                    z_all.push_back(values[i]);
                 }
-            t.push_back(d.hi[e]);
-            z.push_back(a == 0 ? hg[(size_t)(n[1] - 1) * n[0] + k] : hg[(size_t)k * n[0] + n[0] - 1]);
-            const int m = (int)t.size();
-            // Phi lam = z by Gaussian elimination with partial pivoting
-            std::vector<double> M((size_t)m * m);
-            for (int r = 0; r < m; ++r)
-                for (int c = 0; c < m; ++c) {
-                    const double ee = part->rbf_eps * (t[r] - t[c]);
-                    M[(size_t)r * m + c] = std::sqrt(1.0 + ee * ee);
-                }
-            std::vector<double> lam = z;
-            for (int c = 0; c < m; ++c) {
-                int p = c;
-                for (int r = c + 1; r < m; ++r)
-                    if (std::fabs(M[(size_t)r * m + c]) > std::fabs(M[(size_t)p * m + c])) p = r;
-                if (M[(size_t)p * m + c] == 0.0)
-                    return fail(PDD_E_INVALID, "interpolation system of interface %g is singular (repeated nodes?)",
-                                cut_pos[a][q]);
-                if (p != c) {
-                    for (int cc = 0; cc < m; ++cc) std::swap(M[(size_t)p * m + cc], M[(size_t)c * m + cc]);
-                    std::swap(lam[p], lam[c]);
-                }
-                for (int r = c + 1; r < m; ++r) {
-                    const double l = M[(size_t)r * m + c] / M[(size_t)c * m + c];
-                    for (int cc = c; cc < m; ++cc) M[(size_t)r * m + cc] -= l * M[(size_t)c * m + cc];
-                    lam[r] -= l * lam[c];
-                }
-            }
-            for (int r = m - 1; r >= 0; --r) {
-                double acc = lam[r];
-                for (int cc = r + 1; cc < m; ++cc) acc -= M[(size_t)r * m + cc] * lam[cc];
-                lam[r] = acc / M[(size_t)r * m + r];
-            }
-            Stage2Line L{};
-            L.d = a, L.k = k, L.m = m, L.at = t_all.size(), L.eps = part->rbf_eps;
+            t_all.push_back(d.hi[e]);
+            z_all.push_back(0.0);
+            L.m = (int)(t_all.size() - L.at);
+            L.matrix = weights_values;
+            if (L.m > kStage2MaxLdsNodes) weights_values += (size_t)L.m * (L.m + 1);
             lines.push_back(L);
-            t_all.insert(t_all.end(), t.begin(), t.end());
-            lam_all.insert(lam_all.end(), lam.begin(), lam.end());
+            line_pos.push_back(cut_pos[a][q]);
         }
     // blocks of the cyclic reduction, up to 8 GiB (2.3 million unknowns) and
     // where the device has them; else banded LU (as every call with
@@ -1788,16 +1755,19 @@ pdd_status pdd_stage2(pdd_problem *problem, const pdd_partition *part, const dou
     }
     const char *force_subst = std::getenv("PDD_STAGE2_SUBSTITUTE");
     bool use_cr = cr_values * sizeof(double) <= (8ull << 30) && !(force_subst && force_subst[0] == '1');
-    // device tables: lines | t | lam | boxes | blocks' places | stencils | right sides
+    // device tables: lines | t | values, then weights | boxes | blocks' places |
+    // stencils | right sides | large lines' matrices; the lines' marks stay in the
+    // staging buffer
     const size_t off_lines = 0;
     const size_t off_t = align_up(off_lines + lines.size() * sizeof(Stage2Line), 256);
     const size_t off_lam = align_up(off_t + t_all.size() * sizeof(double), 256);
-    const size_t off_boxes = align_up(off_lam + lam_all.size() * sizeof(double), 256);
+    const size_t off_boxes = align_up(off_lam + z_all.size() * sizeof(double), 256);
     const size_t off_cr = align_up(off_boxes + boxes.size() * sizeof(SubBox), 256);
     const size_t table_bytes = align_up(off_cr + cr_tab.size() * sizeof(Stage2Cr), 256);
     const size_t off_stencil = table_bytes;
     const size_t off_rhs = align_up(off_stencil + unknowns * 6 * sizeof(double), 256);
-    const size_t bytes = off_rhs + unknowns * sizeof(double);
+    const size_t off_weights = align_up(off_rhs + unknowns * sizeof(double), 256);
+    const size_t bytes = off_weights + weights_values * sizeof(double);
     if ((st = ensure(ctx, ctx->stage2, bytes))) return st;
     // the subdomain matrices depend on the operator (sigma, b, c), the grid
     // and the interfaces: factored already when the last call had the same
@@ -1825,20 +1795,26 @@ pdd_status pdd_stage2(pdd_problem *problem, const pdd_partition *part, const dou
         }
         if (st) return st;
     }
-    if ((st = ensure_stage(ctx, table_bytes))) return st;
+    if ((st = ensure_stage(ctx, table_bytes + lines.size() * sizeof(int32_t)))) return st;
     char *h = static_cast<char *>(ctx->stage);
     std::memcpy(h + off_lines, lines.data(), lines.size() * sizeof(Stage2Line));
     std::memcpy(h + off_t, t_all.data(), t_all.size() * sizeof(double));
-    std::memcpy(h + off_lam, lam_all.data(), lam_all.size() * sizeof(double));
+    std::memcpy(h + off_lam, z_all.data(), z_all.size() * sizeof(double));
     std::memcpy(h + off_boxes, boxes.data(), boxes.size() * sizeof(SubBox));
     std::memcpy(h + off_cr, cr_tab.data(), cr_tab.size() * sizeof(Stage2Cr));
     char *dv = static_cast<char *>(ctx->stage2.ptr);
     HIP_TRY(hipMemcpyAsync(dv, h, table_bytes, hipMemcpyHostToDevice, s));
+    const Stage2Line *dv_lines = reinterpret_cast<const Stage2Line *>(dv + off_lines);
+    const double *dv_t = reinterpret_cast<const double *>(dv + off_t);
+    double *dv_lam = reinterpret_cast<double *>(dv + off_lam);
+    int32_t *marks = reinterpret_cast<int32_t *>(h + table_bytes);
+    void *dv_marks = nullptr;
+    HIP_TRY(hipHostGetDevicePointer(&dv_marks, marks, 0));
+    HIP_TRY(launch_stage2_weights(g, dv_lines, (int32_t)lines.size(), dv_t, dv_lam,
+                                  reinterpret_cast<double *>(dv + off_weights), static_cast<int32_t *>(dv_marks), s));
     HIP_TRY(hipEventRecord(ctx->staged, s));
     ctx->any_staged = true;
-    HIP_TRY(launch_stage2_lines(g, reinterpret_cast<const Stage2Line *>(dv + off_lines), (int32_t)lines.size(),
-                                reinterpret_cast<const double *>(dv + off_t),
-                                reinterpret_cast<const double *>(dv + off_lam), s));
+    HIP_TRY(launch_stage2_lines(g, dv_lines, (int32_t)lines.size(), dv_t, dv_lam, s));
     Stage2Plan plan{};
     plan.factored = factored;
     plan.cr_tab = use_cr ? reinterpret_cast<const Stage2Cr *>(dv + off_cr) : nullptr;
@@ -1852,6 +1828,11 @@ pdd_status pdd_stage2(pdd_problem *problem, const pdd_partition *part, const dou
     ctx->stage2_key = key;
     HIP_TRY(hipEventRecord(ctx->done, s));
     ctx->any_done = true;
+    HIP_TRY(hipEventSynchronize(ctx->done));
+    for (size_t q = 0; q < lines.size(); ++q)
+        if (marks[q])
+            return fail(PDD_E_INVALID, "interpolation system of interface %g is singular (repeated nodes?)",
+                        line_pos[q]);
     return PDD_OK;
 }
 

@@ -1,6 +1,7 @@
 // Kernels of the outer iteration that evaluate the problem's coefficients: the
 // residual of a gridded u~ and the second stage of PDD.
 #include <algorithm>
+#include <type_traits>
 
 #include "path_walk.hpp"
 
@@ -106,6 +107,129 @@ __device__ __forceinline__ double multiquadric(const double *t, const double *la
     return acc;
 }
 
+// A lane's double, read by every lane (wave-uniform result).
+__device__ __forceinline__ double readlane_f64(double v, int lane)
+{
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, lane);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), lane);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// The largest of v over the wave (NaN apart), by way of the rows of 16 lanes.
+__device__ __forceinline__ double wave_max(double v)
+{
+    const auto step = [&v](auto ctrl) {
+        const uint64_t b = __builtin_bit_cast(uint64_t, v);
+        const int lo = (int)(uint32_t)b, hi = (int)(uint32_t)(b >> 32);
+        const uint32_t l = (uint32_t)__builtin_amdgcn_update_dpp(lo, lo, decltype(ctrl)::value, 0xf, 0xf, false);
+        const uint32_t h = (uint32_t)__builtin_amdgcn_update_dpp(hi, hi, decltype(ctrl)::value, 0xf, 0xf, false);
+        v = fmax(v, __builtin_bit_cast(double, (uint64_t)h << 32 | l));
+    };
+    step(std::integral_constant<int, 0x111>{});  // from 1, 2, 4 and 8 lanes before
+    step(std::integral_constant<int, 0x112>{});
+    step(std::integral_constant<int, 0x114>{});
+    step(std::integral_constant<int, 0x118>{});
+    step(std::integral_constant<int, 0x142>{});  // the last lane of a row to the next row
+    step(std::integral_constant<int, 0x143>{});  // lane 31 to the upper half
+    return readlane_f64(v, 63);
+}
+
+// Multiquadric weights of one line, one workgroup each: Phi lam = z by Gaussian
+// elimination with partial pivoting, Phi and, as its last column, z in LDS up to
+// kStage2MaxLdsNodes data points (149 KB), else in `matrices`. The elimination's
+// operations on each element, and its pivots, are those of the textbook loop.
+// Bound by its chain of pivots, three barriers and a division each. 14 lines of
+// 114 points: a second stage of 257^2 points with kept factors took 2.1 ms with
+// the systems solved on the host and takes 0.45 ms (three lines of 8 points:
+// 0.20 ms either way).
+constexpr int kWeightsThreads = 1024;
+__device__ __forceinline__ void solve_weights(double *M, double *z, const double *t, double eps, int m, int32_t *mark)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    constexpr int kWaves = kWeightsThreads / 64;
+    const size_t ld = m + 1;
+    for (int r = wave; r < m; r += kWaves)
+        for (int c = lane; c <= m; c += 64) {
+            const double ee = eps * (t[r] - (c < m ? t[c] : 0.0));
+            M[r * ld + c] = c < m ? sqrt(1.0 + ee * ee) : z[r];
+        }
+    __syncthreads();
+    for (int c = 0; c < m; ++c) {
+        // the largest |entry| of the column from the diagonal on, the first of
+        // equals; every wave finds it for itself
+        double best = -1.0;
+        for (int r = c + lane; r < m; r += 64) best = fmax(best, fabs(M[r * ld + c]));
+        best = wave_max(best);
+        int p = c;
+        for (int r0 = c; r0 < m; r0 += 64) {
+            const int r = r0 + lane;
+            const uint64_t hit = __ballot(r < m && fabs(M[(r < m ? r : c) * ld + c]) == best);
+            if (hit) {
+                p = r0 + __builtin_ctzll(hit);
+                break;
+            }
+        }
+        const double pivot = M[p * ld + c];
+        __syncthreads();
+        if (pivot == 0.0) {  // every wave alike
+            for (int r = threadIdx.x; r < m; r += kWeightsThreads) z[r] = 0.0;
+            if (threadIdx.x == 0) *mark = 1;
+            return;
+        }
+        // rows c and p change places; their multipliers take the entries of
+        // column c below the diagonal (row p's is of the row that came there)
+        if (threadIdx.x < kWeightsThreads / 2) {
+            for (int cc = c + 1 + threadIdx.x; cc <= m; cc += kWeightsThreads / 2) {
+                const double v = M[p * ld + cc];
+                M[p * ld + cc] = M[c * ld + cc];
+                M[c * ld + cc] = v;
+            }
+        } else {
+            for (int r = c + threadIdx.x - kWeightsThreads / 2; r < m; r += kWeightsThreads / 2) {
+                if (r == c && p != c) continue;
+                const double v = M[(r == p ? c : r) * ld + c];
+                if (r == p) M[c * ld + c] = pivot;
+                if (r > c) M[r * ld + c] = v / pivot;
+            }
+        }
+        __syncthreads();
+        for (int cc = c + 1 + lane; cc <= m; cc += 64) {
+            const double top = M[c * ld + cc];
+            for (int r = c + 1 + wave; r < m; r += kWaves) M[r * ld + cc] -= M[r * ld + c] * top;
+        }
+        __syncthreads();
+    }
+    for (int r = m - 1; r >= 0; --r) {
+        if (wave * 64 > r) {
+            __syncthreads();
+            continue;
+        }
+        const double x = M[r * ld + m] / M[r * ld + r];
+        if (threadIdx.x == 0) z[r] = x;
+        for (int rr = threadIdx.x; rr < r; rr += kWeightsThreads) M[rr * ld + m] -= M[rr * ld + r] * x;
+        __syncthreads();
+    }
+}
+__global__ void __launch_bounds__(kWeightsThreads) stage2_weights_kernel(const Stage2Grid g, const Stage2Line *lines,
+                                                                         const double *t, double *lam,
+                                                                         double *matrices, int32_t *marks)
+{
+    __shared__ double s_M[kStage2MaxLdsNodes * (kStage2MaxLdsNodes + 1)];
+    const Stage2Line L = lines[blockIdx.x];
+    double *z = lam + L.at;
+    if (threadIdx.x == 0) {
+        marks[blockIdx.x] = 0;
+        z[0] = g.u[L.d == 0 ? (size_t)L.k : (size_t)L.k * g.n0];
+        z[L.m - 1] = g.u[L.d == 0 ? (size_t)(g.n1 - 1) * g.n0 + L.k : (size_t)L.k * g.n0 + g.n0 - 1];
+    }
+    __syncthreads();
+    if (L.m <= kStage2MaxLdsNodes)
+        solve_weights(s_M, z, t + L.at, L.eps, L.m, marks + blockIdx.x);
+    else
+        solve_weights(matrices + L.matrix, z, t + L.at, L.eps, L.m, marks + blockIdx.x);
+}
+
 // One workgroup row per line (blockIdx.y); the points of the line strictly
 // between the box's edges.
 __global__ void __launch_bounds__(256) stage2_lines_kernel(const Stage2Grid g, const Stage2Line *lines, int32_t n_lines,
@@ -199,15 +323,6 @@ __device__ __forceinline__ double stage2_entry(const double *st, int w, int e)
     if (e == w + 1) v += st[3];
     if (e == 2 * w) v += st[4];
     return v;
-}
-
-// A lane's double, read by every lane (wave-uniform result).
-__device__ __forceinline__ double readlane_f64(double v, int lane)
-{
-    const uint64_t b = (uint64_t)__double_as_longlong(v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, lane);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), lane);
-    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
 // Banded LU without pivoting (the stencil matrices are diagonally dominant
@@ -822,6 +937,15 @@ hipError_t launch_stage2_boundary(const DevProblem<double> &P, const Stage2Grid 
 {
     const int total = 2 * g.n0 + 2 * (g.n1 - 2);
     hipLaunchKernelGGL(stage2_boundary_kernel, dim3((total + 255) / 256), dim3(256), 0, s, P, g);
+    return hipGetLastError();
+}
+
+hipError_t launch_stage2_weights(const Stage2Grid &g, const Stage2Line *lines, int32_t n_lines, const double *t,
+                                 double *lam, double *matrices, int32_t *marks, hipStream_t s)
+{
+    if (n_lines == 0) return hipSuccess;
+    hipLaunchKernelGGL(stage2_weights_kernel, dim3(n_lines), dim3(kWeightsThreads), 0, s, g, lines, t, lam, matrices,
+                       marks);
     return hipGetLastError();
 }
 
