@@ -231,14 +231,16 @@ struct ReduceArgs {
     int32_t has_phi, has_e;
     const uint32_t *node_item;
     const FinalItem *fitems;
-    // segments longer than kReduceChunk paths are split: chunk c of node
-    // node_lo + b is reduced by workgroup (b, c) into partials[b * n_chunks +
-    // c], and the chunks are then merged into acc in chunk order
+    // set where a segment is longer than kReduceChunk paths: those are reduced
+    // by chunks into partials (reduce_partials of them) and then merged into
+    // acc in a fixed order
     NodeAcc *partials;
-    uint32_t n_chunks;
+    int32_t split;
 };
 
-constexpr uint64_t kReduceChunk = 1ull << 16;
+constexpr uint64_t kReduceChunk = 1ull << 12;
+// Workgroups and partials of a split reduction of `slots` paths of n_nodes nodes.
+constexpr uint64_t reduce_partials(uint64_t slots, uint64_t n_nodes) { return slots / kReduceChunk + n_nodes; }
 
 struct FinalizeArgs {
     const NodeAcc *acc;
@@ -305,7 +307,7 @@ hipError_t launch_grid_points_strided(const S *data, uint64_t n_points, T *out, 
 template <class S, class T, int D>
 hipError_t launch_grid_cells_strided(const S *data, const int32_t *n, T *cells, uint32_t stride, uint32_t off,
                                      hipStream_t s);
-hipError_t launch_reduce(const ReduceArgs &a, uint32_t n_blocks, hipStream_t s);
+hipError_t launch_reduce(const ReduceArgs &a, uint32_t n_nodes, hipStream_t s);
 // r = f - ((1/2) sigma^2 Lap u + b.grad u + c u) at the points of grid g (u in
 // g->data, r in g's dtype and layout), by second-order differences.
 hipError_t launch_grid_residual(const DevProblem<double> &P, double sigma, const pdd_grid *g, void *r, hipStream_t s);

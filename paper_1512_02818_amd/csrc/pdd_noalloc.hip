@@ -90,14 +90,9 @@ pdd_status run_noalloc(pdd_ctx *ctx, const HostItem &it, const pdd_tuning &tune,
     const uint32_t n = (uint32_t)it.n_nodes;
     uint64_t per_launch = std::min<uint64_t>(kNaRecSlots, std::max<uint64_t>(total, 1));
     if (tune.max_launch_paths > 0) per_launch = std::min<uint64_t>(per_launch, (uint64_t)tune.max_launch_paths);
-    // chunk partials of one launch: at most (nodes it touches) x (chunks of
-    // the longest piece of a node), known before anything is enqueued
-    if (N > kReduceChunk) {
-        const uint64_t nodes_max = (per_launch - 1) / N + 2;
-        const uint64_t chunks_max = (std::min<uint64_t>(N, per_launch) + kReduceChunk - 1) / kReduceChunk;
-        if (nodes_max * chunks_max * sizeof(NodeAcc) > kNaPartBytes)
-            return fail(PDD_E_INTERNAL, "no-alloc scratch: chunk partials do not fit");
-    }
+    // chunk partials of one launch, known before anything is enqueued
+    if (N > kReduceChunk && reduce_partials(per_launch, (per_launch - 1) / N + 2) * sizeof(NodeAcc) > kNaPartBytes)
+        return fail(PDD_E_INTERNAL, "no-alloc scratch: chunk partials do not fit");
     double *sc_phi = reinterpret_cast<double *>(base + kNaOffPhi);
     uint32_t *sc_steps = reinterpret_cast<uint32_t *>(base + kNaOffSteps);
     NodeAcc *acc = reinterpret_cast<NodeAcc *>(base + kNaOffAcc);
@@ -199,7 +194,7 @@ pdd_status run_noalloc(pdd_ctx *ctx, const HostItem &it, const pdd_tuning &tune,
         }
         // per-node sums of the nodes this launch touched
         // (node i holds slots [i N, (i + 1) N); the longest piece of a node in
-        // [b, b + len) sets the chunk count of the reduction)
+        // [b, b + len) says whether the reduction is split)
         const uint64_t e = b + len;
         const uint32_t n_lo = (uint32_t)(b / N), n_hi = (uint32_t)((e - 1) / N);
         uint64_t longest = len;
@@ -219,7 +214,7 @@ pdd_status run_noalloc(pdd_ctx *ctx, const HostItem &it, const pdd_tuning &tune,
         r.node_lo = n_lo;
         r.has_phi = 1;
         r.has_e = 0;
-        r.n_chunks = (uint32_t)std::max<uint64_t>(1, (longest + kReduceChunk - 1) / kReduceChunk);
+        r.split = longest > kReduceChunk;
         r.partials = partials;
         HIP_TRY(launch_reduce(r, n_hi - n_lo + 1, s));
     }

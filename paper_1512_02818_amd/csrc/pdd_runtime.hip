@@ -822,20 +822,20 @@ pdd_status run_group(pdd_ctx *ctx, std::vector<HostItem *> &items, const pdd_tun
         std::memcpy(&h_probs[p], sizeof(T) == 4 ? (const void *)&probs[p]->pf : (const void *)&probs[p]->pd,
                     sizeof(DevProblem<T>));
 
-    // chunk partials of long node segments (reduce kernel): sized for the
-    // longest node of the group before anything of the group is enqueued
+    // chunk partials of long node segments (reduce kernel): sized for any
+    // launch of the group before anything of it is enqueued
     uint64_t longest = 0;
     for (uint64_t i = 0; i < n_nodes_all; ++i) longest = std::max(longest, h_gstart[i + 1] - h_gstart[i]);
-    const uint64_t max_chunks = std::max<uint64_t>(1, (longest + kReduceChunk - 1) / kReduceChunk);
-    if (max_chunks > 1 && (st = ensure(ctx, ctx->partials, n_nodes_all * max_chunks * sizeof(NodeAcc)))) return st;
-    // chunks needed by nodes [n_lo, n_hi] of gs restricted to slots [a, b)
-    auto chunks_in = [&](const uint64_t *gs, uint32_t n_lo, uint32_t n_hi, uint64_t a, uint64_t b) {
-        uint64_t mx = 0;
+    if (longest > kReduceChunk &&
+        (st = ensure(ctx, ctx->partials, reduce_partials(per_launch, n_nodes_all) * sizeof(NodeAcc))))
+        return st;
+    // whether a node of [n_lo, n_hi] of gs has more than a chunk of slots [a, b)
+    auto split_in = [&](const uint64_t *gs, uint32_t n_lo, uint32_t n_hi, uint64_t a, uint64_t b) {
         for (uint32_t i = n_lo; i <= n_hi; ++i) {
             const uint64_t x = std::max(gs[i], a), y = std::min(gs[i + 1], b);
-            if (y > x) mx = std::max(mx, y - x);
+            if (y > x + kReduceChunk) return 1;
         }
-        return (uint32_t)std::max<uint64_t>(1, (mx + kReduceChunk - 1) / kReduceChunk);
+        return 0;
     };
 
     HIP_TRY(hipMemcpyAsync(dv, h, bytes, hipMemcpyHostToDevice, s));
@@ -937,7 +937,7 @@ pdd_status run_group(pdd_ctx *ctx, std::vector<HostItem *> &items, const pdd_tun
             r.has_e = HAS_E;
             r.node_item = d_nitem;
             r.fitems = d_fitems;
-            r.n_chunks = chunks_in(h_gstart, n_lo, n_hi, b, b + len);
+            r.split = split_in(h_gstart, n_lo, n_hi, b, b + len);
             r.partials = static_cast<NodeAcc *>(ctx->partials.ptr);
             HIP_TRY(launch_reduce(r, n_hi - n_lo + 1, s));
         }
@@ -962,7 +962,7 @@ pdd_status run_group(pdd_ctx *ctx, std::vector<HostItem *> &items, const pdd_tun
             r.node_lo = n_lo;
             r.has_phi = it.score_plain;
             r.has_e = HAS_E;
-            r.n_chunks = chunks_in(gs, n_lo, n_hi, lo, hi);
+            r.split = split_in(gs, n_lo, n_hi, lo, hi);
             r.partials = static_cast<NodeAcc *>(ctx->partials.ptr);
             HIP_TRY(launch_reduce(r, n_hi - n_lo + 1, s));
         }

@@ -2,12 +2,15 @@
 // (Sec. 2.2, eq. F:Statistical_error; Sec. 2.3, eqs. F:Variance_Reduction and
 // F:Rho).
 //
-// One workgroup per node segment of a launch. Each thread keeps Neumaier
-// (sum, compensation) pairs over a fixed stride of the segment; the pairs are
-// merged by a butterfly of wave shuffles and then across the waves through
-// LDS, always in the same order, and added to the node's accumulator, which
-// only this workgroup touches during the launch. The result is therefore the
-// same whichever lanes walked which paths.
+// One workgroup per node segment of a launch, or per chunk of it. Each thread
+// keeps Neumaier (sum, compensation) pairs over a fixed stride of the segment;
+// the pairs are merged by a butterfly of wave shuffles and then across the
+// waves through LDS, always in the same order, and added to the node's
+// accumulator, which only this workgroup touches during the launch. The result
+// is therefore the same whichever lanes walked which paths. A thread's sums are
+// one chain, so a chunk is short: 16 records a thread. (18 nodes of 1e5 paths
+// with correction records, 36 MB: 180 us in chunks of 65536, 20 us in chunks of
+// 4096, the merge included.)
 #include "pdd.h"
 #include "pdd_internal.hpp"
 
@@ -36,6 +39,21 @@ __device__ __forceinline__ Pair nmerge(Pair a, Pair b)
     return {t, (a.c + b.c) + err};
 }
 
+// Butterfly across the 64 lanes of the wave.
+__device__ __forceinline__ void wave_merge(Pair (&acc)[5], long long &steps, long long &capped)
+{
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+#pragma unroll
+        for (int q = 0; q < 5; ++q) {
+            Pair o{__shfl_xor(acc[q].s, off), __shfl_xor(acc[q].c, off)};
+            acc[q] = nmerge(acc[q], o);
+        }
+        steps += __shfl_xor(steps, off);
+        capped += __shfl_xor(capped, off);
+    }
+}
+
 constexpr int kReduceBlock = 256;
 
 // Node segment [lo, hi) of the launch and its number of chunks.
@@ -58,10 +76,32 @@ __device__ __forceinline__ uint32_t n_chunks_of(uint64_t lo, uint64_t hi)
     return hi > lo ? (uint32_t)((hi - lo + kReduceChunk - 1) / kReduceChunk) : 0u;
 }
 
-__global__ void __launch_bounds__(kReduceBlock) reduce_kernel(const ReduceArgs r)
+// The split launch's workgroups and partials run through the nodes' segments:
+// those of node_lo + b start at chunk_at(b). Enough for its chunks, as the
+// next segment starts where this one ends.
+__device__ __forceinline__ uint64_t chunk_at(const ReduceArgs &r, uint32_t b)
 {
-    const uint32_t node = r.node_lo + blockIdx.x;
-    const uint32_t chunk = blockIdx.y;
+    uint64_t lo, hi;
+    segment(r, r.node_lo + b, lo, hi);
+    return (lo - r.slot_begin) / kReduceChunk + b;
+}
+
+__global__ void __launch_bounds__(kReduceBlock) reduce_kernel(const ReduceArgs r, uint32_t n_nodes)
+{
+    uint32_t b = blockIdx.x, chunk = 0;
+    if (r.split) {  // the last b with chunk_at(b) <= this workgroup's number
+        uint32_t above = n_nodes;
+        b = 0;
+        while (above - b > 1) {
+            const uint32_t mid = b + (above - b) / 2;
+            if (chunk_at(r, mid) <= blockIdx.x)
+                b = mid;
+            else
+                above = mid;
+        }
+        chunk = (uint32_t)(blockIdx.x - chunk_at(r, b));
+    }
+    const uint32_t node = r.node_lo + b;
     int32_t has_phi = r.has_phi;
     if (r.node_item) {
         const FinalItem &fi = r.fitems[r.node_item[node]];
@@ -81,35 +121,35 @@ __global__ void __launch_bounds__(kReduceBlock) reduce_kernel(const ReduceArgs r
 
     Pair acc[5] = {{0, 0}, {0, 0}, {0, 0}, {0, 0}, {0, 0}};
     long long steps = 0, capped = 0;
-    for (uint64_t q = lo + threadIdx.x; q < hi; q += kReduceBlock) {
-        const uint64_t i = q - r.rec_base;
-        const uint32_t sw = r.rec_steps[i];
-        steps += sw & ~kCappedBit;
-        capped += sw >> 31;
-        double phi = 0.0, e = 0.0;
-        if (has_phi) {
-            phi = r.rec_phi[i];
-            nadd(acc[0], phi);
-            nadd(acc[1], phi * phi);
+    constexpr int kAhead = 4;  // records loaded ahead of their sums
+    for (uint64_t q = lo + threadIdx.x; q < hi; q += kAhead * kReduceBlock) {
+        uint32_t sw[kAhead];
+        double phi[kAhead], e[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const uint64_t at = q + u * kReduceBlock;
+            const uint64_t i = (at < hi ? at : q) - r.rec_base;
+            sw[u] = r.rec_steps[i];
+            phi[u] = has_phi ? r.rec_phi[i] : 0.0;
+            e[u] = r.has_e ? r.rec_e[i] : 0.0;
         }
-        if (r.has_e) {
-            e = r.rec_e[i];
-            nadd(acc[2], e);
-            nadd(acc[3], e * e);
-            if (has_phi) nadd(acc[4], phi * e);
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            if (q + u * kReduceBlock >= hi) break;
+            steps += sw[u] & ~kCappedBit;
+            capped += sw[u] >> 31;
+            if (has_phi) {
+                nadd(acc[0], phi[u]);
+                nadd(acc[1], phi[u] * phi[u]);
+            }
+            if (r.has_e) {
+                nadd(acc[2], e[u]);
+                nadd(acc[3], e[u] * e[u]);
+                if (has_phi) nadd(acc[4], phi[u] * e[u]);
+            }
         }
     }
-    // butterfly across the 64 lanes of the wave
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-#pragma unroll
-        for (int q = 0; q < 5; ++q) {
-            Pair o{__shfl_xor(acc[q].s, off), __shfl_xor(acc[q].c, off)};
-            acc[q] = nmerge(acc[q], o);
-        }
-        steps += __shfl_xor(steps, off);
-        capped += __shfl_xor(capped, off);
-    }
+    wave_merge(acc, steps, capped);
     __shared__ Pair part[kReduceBlock / 64][5];
     __shared__ long long part_i[kReduceBlock / 64][2];
     const int wave = threadIdx.x >> 6;
@@ -140,7 +180,7 @@ __global__ void __launch_bounds__(kReduceBlock) reduce_kernel(const ReduceArgs r
         p.capped = cp;
         p.n = (long long)(hi - lo);
         p.pad = 0;
-        r.partials[(size_t)blockIdx.x * r.n_chunks + chunk] = p;
+        r.partials[blockIdx.x] = p;
     }
     if (threadIdx.x == 0 && direct) {
         NodeAcc &A = r.acc[node];
@@ -166,36 +206,38 @@ __global__ void __launch_bounds__(kReduceBlock) reduce_kernel(const ReduceArgs r
     }
 }
 
-// Chunk partials of the split segments, merged into the node sums in chunk
-// order (one thread per node of the launch range).
-__global__ void merge_chunks_kernel(const ReduceArgs r, uint32_t n_nodes)
+// Chunk partials of the split segments, merged into the node sums: a wave per
+// node of the launch range, its lanes through the partials in chunk order.
+__global__ void __launch_bounds__(kReduceBlock) merge_chunks_kernel(const ReduceArgs r, uint32_t n_nodes)
 {
-    const uint32_t b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= n_nodes) return;
+    const uint32_t b = blockIdx.x * (kReduceBlock / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (b >= n_nodes) return;  // whole wave, as below
     const uint32_t node = r.node_lo + b;
     if (r.node_item && r.fitems[r.node_item[node]].own_reduce) return;
     uint64_t lo, hi;
     segment(r, node, lo, hi);
     const uint32_t nch = n_chunks_of(lo, hi);
     if (nch <= 1) return;
-    NodeAcc &A = r.acc[node];
-    Pair tot[5];
-    for (int q = 0; q < 5; ++q) tot[q] = {A.s[q], A.c[q]};
-    long long st = A.steps, cp = A.capped, n = A.n;
-    for (uint32_t c = 0; c < nch; ++c) {
-        const NodeAcc &p = r.partials[(size_t)b * r.n_chunks + c];
+    const NodeAcc *partials = r.partials + chunk_at(r, b);
+    Pair tot[5] = {{0, 0}, {0, 0}, {0, 0}, {0, 0}, {0, 0}};
+    long long steps = 0, capped = 0;
+    for (uint32_t c = lane; c < nch; c += 64) {
+        const NodeAcc &p = partials[c];
         for (int q = 0; q < 5; ++q) tot[q] = nmerge(tot[q], Pair{p.s[q], p.c[q]});
-        st += p.steps;
-        cp += p.capped;
-        n += p.n;
+        steps += p.steps;
+        capped += p.capped;
     }
+    wave_merge(tot, steps, capped);
+    if (lane) return;
+    NodeAcc &A = r.acc[node];
     for (int q = 0; q < 5; ++q) {
-        A.s[q] = tot[q].s;
-        A.c[q] = tot[q].c;
+        const Pair sum = nmerge(Pair{A.s[q], A.c[q]}, tot[q]);
+        A.s[q] = sum.s;
+        A.c[q] = sum.c;
     }
-    A.steps = st;
-    A.capped = cp;
-    A.n = n;
+    A.steps += steps;
+    A.capped += capped;
+    A.n += (long long)(hi - lo);
 }
 
 __device__ __forceinline__ double grid_at(const FinalItem &f, size_t i)
@@ -333,16 +375,19 @@ __global__ void zero_kernel(uint64_t *p, uint64_t n_words)
 
 }  // namespace
 
-hipError_t launch_reduce(const ReduceArgs &a, uint32_t n_blocks, hipStream_t s)
+hipError_t launch_reduce(const ReduceArgs &a, uint32_t n_nodes, hipStream_t s)
 {
-    if (n_blocks == 0) return hipSuccess;
-    const uint32_t nc = a.n_chunks > 0 ? a.n_chunks : 1;
-    hipLaunchKernelGGL(reduce_kernel, dim3(n_blocks, nc), dim3(kReduceBlock), 0, s, a);
-    if (nc > 1) {
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(merge_chunks_kernel, dim3((n_blocks + 255) / 256), dim3(256), 0, s, a, n_blocks);
+    if (n_nodes == 0) return hipSuccess;
+    if (!a.split) {
+        hipLaunchKernelGGL(reduce_kernel, dim3(n_nodes), dim3(kReduceBlock), 0, s, a, n_nodes);
+        return hipGetLastError();
     }
+    const uint64_t blocks = reduce_partials(a.slot_end - a.slot_begin, n_nodes);
+    hipLaunchKernelGGL(reduce_kernel, dim3((uint32_t)blocks), dim3(kReduceBlock), 0, s, a, n_nodes);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    constexpr uint32_t kNodes = kReduceBlock / 64;
+    hipLaunchKernelGGL(merge_chunks_kernel, dim3((n_nodes + kNodes - 1) / kNodes), dim3(kReduceBlock), 0, s, a, n_nodes);
     return hipGetLastError();
 }
 
