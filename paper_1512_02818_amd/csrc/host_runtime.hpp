@@ -133,7 +133,7 @@ struct pdd_ctx {
     hipEvent_t done = nullptr;    // end of the last solve
     hipEvent_t staged = nullptr;  // last copy out of the staging buffer
     bool any_done = false, any_staged = false;
-    pdd::DeviceBuffer nodes, starts, acc, counters, rec, partials, gather, cells;
+    pdd::DeviceBuffer nodes, starts, acc, rec, partials, gather, cells;
     pdd::DeviceBuffer tail;    // walking paths handed over between path kernels of a launch
     pdd::DeviceBuffer stage2;  // second stage: tables and stencils
     // factors of the last second stage's subdomain matrices, and what they

@@ -14,26 +14,39 @@
 namespace pdd {
 namespace {
 
-// Cell layout of a grid (see cell_values), values converted from S to T: one
-// thread per cell.
-template <class S, class T, int D>
-__global__ void grid_cells_kernel(const S *__restrict__ data, int n0, int n1, int n2, T *__restrict__ cells,
-                                  uint32_t stride, uint32_t off)
+// Cell layout of grids (see cell_values), values converted from S to T: one
+// thread per cell and grid (blockIdx.y).
+template <class S>
+struct CellGrids {
+    const S *data[3];
+};
+template <class S, class T, int D, class I>
+__device__ __forceinline__ void grid_cells(const S *__restrict__ data, I n0, I n1, I n2, T *__restrict__ cells,
+                                           uint32_t stride, uint32_t off)
 {
-    const uint64_t m0 = (uint64_t)(n0 - 1), m1 = (uint64_t)(n1 - 1), m2 = D == 3 ? (uint64_t)(n2 - 1) : 1;
-    const uint64_t n_cells = m0 * m1 * m2;
-    for (uint64_t c = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; c < n_cells;
-         c += (uint64_t)gridDim.x * blockDim.x) {
-        const uint64_t i = c % m0, j = (c / m0) % m1, k = c / (m0 * m1);
-        T *out = cells + c * stride + off;
+    const I m0 = n0 - 1, m1 = n1 - 1, n_cells = m0 * m1 * (D == 3 ? n2 - 1 : 1);
+    for (I c = blockIdx.x * (I)blockDim.x + threadIdx.x; c < n_cells; c += (I)gridDim.x * blockDim.x) {
+        const I i = c % m0, jk = c / m0, j = D == 3 ? jk % m1 : jk, k = D == 3 ? jk / m1 : 0;
+        T *out = cells + (uint64_t)c * stride + off;
 #pragma unroll
         for (int dz = 0; dz < (D == 3 ? 2 : 1); ++dz)
 #pragma unroll
             for (int dy = 0; dy < 2; ++dy)
 #pragma unroll
-                for (int dx = 0; dx < 2; ++dx)
-                    out[(dz * 2 + dy) * 2 + dx] = (T)data[((k + dz) * (uint64_t)n1 + (j + dy)) * (uint64_t)n0 + i + dx];
+                for (int dx = 0; dx < 2; ++dx) out[(dz * 2 + dy) * 2 + dx] = (T)data[((k + dz) * n1 + (j + dy)) * n0 + i + dx];
     }
+}
+template <class S, class T, int D>
+__global__ void grid_cells_kernel(const CellGrids<S> g, int n0, int n1, int n2, T *__restrict__ cells,
+                                  uint32_t stride, uint32_t off)
+{
+    const S *data = g.data[blockIdx.y];
+    off += blockIdx.y << D;
+    // (2^30 points: a thread's next cell still fits in 32 bits)
+    if ((uint64_t)n0 * n1 * n2 < (1ull << 30))
+        grid_cells<S, T, D, uint32_t>(data, n0, n1, n2, cells, stride, off);
+    else
+        grid_cells<S, T, D, uint64_t>(data, n0, n1, n2, cells, stride, off);
 }
 
 // Point values of a grid converted from S to T into every stride-th slot (a
@@ -390,21 +403,30 @@ const void *path_kernel_symbol(bool one, int kind)
 }
 
 template <class S, class T, int D>
-hipError_t launch_grid_cells_strided(const S *data, const int32_t *n, T *cells, uint32_t stride, uint32_t off,
-                                     hipStream_t s)
+hipError_t launch_cells(const CellGrids<S> &g, int n_grids, const int32_t *n, T *cells, uint32_t stride, uint32_t off,
+                        hipStream_t s)
 {
     const uint64_t n_cells = cell_values<T>(n, D) >> D;
     if (n_cells == 0) return hipSuccess;
     const uint64_t blocks = std::min<uint64_t>((n_cells + 255) / 256, 4096);
-    hipLaunchKernelGGL((grid_cells_kernel<S, T, D>), dim3((uint32_t)blocks), dim3(256), 0, s, data, n[0], n[1],
-                       D == 3 ? n[2] : 2, cells, stride, off);
+    hipLaunchKernelGGL((grid_cells_kernel<S, T, D>), dim3((uint32_t)blocks, n_grids), dim3(256), 0, s, g, n[0], n[1],
+                       D == 3 ? n[2] : 1, cells, stride, off);
     return hipGetLastError();
 }
 
 template <class S, class T, int D>
-hipError_t launch_grid_cells(const S *data, const int32_t *n, T *cells, hipStream_t s)
+hipError_t launch_grid_cells_strided(const S *data, const int32_t *n, T *cells, uint32_t stride, uint32_t off,
+                                     hipStream_t s)
 {
-    return launch_grid_cells_strided<S, T, D>(data, n, cells, 1u << D, 0u, s);
+    return launch_cells<S, T, D>(CellGrids<S>{{data, nullptr, nullptr}}, 1, n, cells, stride, off, s);
+}
+
+template <class T, int D>
+hipError_t launch_grid_cells(const T *const *data, int n_grids, const int32_t *n, T *cells, hipStream_t s)
+{
+    CellGrids<T> g{};
+    for (int c = 0; c < n_grids; ++c) g.data[c] = data[c];
+    return launch_cells<T, T, D>(g, n_grids, n, cells, (uint32_t)(n_grids << D), 0u, s);
 }
 
 template <class S, class T>
@@ -427,9 +449,12 @@ template hipError_t launch_grid_points_strided<double, double>(const double *, u
                                                                uint32_t, hipStream_t);
 
 #define PDD_GRID_CELLS(S, T, D) \
-    template hipError_t launch_grid_cells<S, T, D>(const S *, const int32_t *, T *, hipStream_t); \
     template hipError_t launch_grid_cells_strided<S, T, D>(const S *, const int32_t *, T *, uint32_t, uint32_t, \
                                                             hipStream_t);
+template hipError_t launch_grid_cells<float, 2>(const float *const *, int, const int32_t *, float *, hipStream_t);
+template hipError_t launch_grid_cells<float, 3>(const float *const *, int, const int32_t *, float *, hipStream_t);
+template hipError_t launch_grid_cells<double, 2>(const double *const *, int, const int32_t *, double *, hipStream_t);
+template hipError_t launch_grid_cells<double, 3>(const double *const *, int, const int32_t *, double *, hipStream_t);
 PDD_GRID_CELLS(float, float, 2)
 PDD_GRID_CELLS(float, float, 3)
 PDD_GRID_CELLS(double, double, 2)

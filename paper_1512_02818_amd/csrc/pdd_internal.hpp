@@ -213,6 +213,16 @@ struct FinalItem {
     double up_lo[3], up_inv[3];
 };
 
+struct FinalizeArgs {
+    const NodeAcc *acc;
+    const double *nodes;  // group nodes, dim doubles each
+    uint32_t n_nodes;     // group nodes
+    int32_t dim;
+    int32_t has_e;
+    const uint32_t *node_item;
+    const FinalItem *fitems;
+};
+
 // One workgroup per node from node_lo on; node i covers slots
 // [node_start[i], node_start[i+1]) (or uniform_n each) clipped to
 // [slot_begin, slot_end); records of slot q sit at q - rec_base. With
@@ -236,21 +246,16 @@ struct ReduceArgs {
     // acc in a fixed order
     NodeAcc *partials;
     int32_t split;
+    // set where one launch holds every path of every node, from node 0 on: the
+    // nodes' sums then start from their items' and end as their statistics
+    // without launches of their own before and after (acc is not used)
+    int32_t whole;
+    FinalizeArgs stats;
 };
 
 constexpr uint64_t kReduceChunk = 1ull << 12;
 // Workgroups and partials of a split reduction of `slots` paths of n_nodes nodes.
 constexpr uint64_t reduce_partials(uint64_t slots, uint64_t n_nodes) { return slots / kReduceChunk + n_nodes; }
-
-struct FinalizeArgs {
-    const NodeAcc *acc;
-    const double *nodes;  // group nodes, dim doubles each
-    uint32_t n_nodes;     // group nodes
-    int32_t dim;
-    int32_t has_e;
-    const uint32_t *node_item;
-    const FinalItem *fitems;
-};
 
 // One item's statistics to copy into a contiguous buffer: n entries from src
 // to dst + at (so that many items come back to the host in one copy).
@@ -295,11 +300,12 @@ hipError_t launch_path_kernel_group(const LaunchArgs &l, const ItemDesc<T> *item
                                     int grid, int kind, hipStream_t s);
 template <class T, int D, int EST>
 const void *path_kernel_symbol(bool one, int kind);
-// Fills `cells` (cell_values entries) from the point values of a grid,
-// converted from S to T.
-template <class S, class T, int D>
-hipError_t launch_grid_cells(const S *data, const int32_t *n, T *cells, hipStream_t s);
-// The same into records of `stride` values per cell, at offset `off` in each.
+// Fills `cells` from the point values of n_grids (<= 3) grids of the same
+// points: a record of n_grids x 2^D values per cell, grid c's at c 2^D.
+template <class T, int D>
+hipError_t launch_grid_cells(const T *const *data, int n_grids, const int32_t *n, T *cells, hipStream_t s);
+// One grid, converted from S to T, into records of `stride` values per cell, at
+// offset `off` in each.
 // out[p stride + off] = data[p] converted from S to T, p < n_points.
 template <class S, class T>
 hipError_t launch_grid_points_strided(const S *data, uint64_t n_points, T *out, uint32_t stride, uint32_t off,

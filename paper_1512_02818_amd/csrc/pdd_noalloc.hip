@@ -154,7 +154,16 @@ pdd_status run_noalloc(pdd_ctx *ctx, const HostItem &it, const pdd_tuning &tune,
     if ((st = store(&fi, sizeof fi, d_final, s))) return st;
     if ((st = store(seg, sizeof seg, d_seg, s))) return st;
     HIP_TRY(launch_zero(nitem, ((size_t)n * sizeof(uint32_t) + 7) & ~size_t(7), s));
-    HIP_TRY(launch_init_acc(acc, n, nitem, d_final, s));
+    FinalizeArgs f{};
+    f.acc = acc;
+    f.nodes = d_nodes;
+    f.n_nodes = n;
+    f.dim = D;
+    f.has_e = 0;
+    f.node_item = nitem;
+    f.fitems = d_final;
+    const bool whole = total > 0 && total <= per_launch;  // one launch (see run_group)
+    if (!whole) HIP_TRY(launch_init_acc(acc, n, nitem, d_final, s));
 
     const bool one = kOneItemKernel<T, D, kEstPlain>;
     const int kind = !specialised(it)   ? kKernelGeneric
@@ -216,17 +225,13 @@ pdd_status run_noalloc(pdd_ctx *ctx, const HostItem &it, const pdd_tuning &tune,
         r.has_e = 0;
         r.split = longest > kReduceChunk;
         r.partials = partials;
+        r.node_item = nitem;
+        r.fitems = d_final;
+        r.whole = whole;
+        r.stats = f;
         HIP_TRY(launch_reduce(r, n_hi - n_lo + 1, s));
     }
-    FinalizeArgs f{};
-    f.acc = acc;
-    f.nodes = d_nodes;
-    f.n_nodes = n;
-    f.dim = D;
-    f.has_e = 0;
-    f.node_item = nitem;
-    f.fitems = d_final;
-    HIP_TRY(launch_finalize(f, s));
+    if (!whole) HIP_TRY(launch_finalize(f, s));
     return PDD_OK;
 }
 

@@ -587,11 +587,12 @@ pdd_status run_group(pdd_ctx *ctx, std::vector<HostItem *> &items, const pdd_tun
     const size_t n_ctr = (size_t)ctr_at[n_launch] + 2;
     // three counters per queue: its slots taken, its paths handed over to the
     // group-walk kernel, and those taken there
-    const size_t ctr_bytes = (3 * n_ctr * sizeof(uint32_t) + 7) & ~size_t(7);  // cleared in 8-byte words
+    const size_t ctr_bytes = 3 * n_ctr * sizeof(uint32_t);
 
     // staged upload: nodes | global node starts | item node starts | kernel
     // items | problems | node -> item | per-item post-processing entries |
-    // queue ranges | per-node RNG table of merged items
+    // queue ranges | per-node RNG table of merged items | handed-over paths'
+    // regions | queue counters (zero)
     const size_t off_nodes = 0;
     const size_t off_gstart = align_up(off_nodes + n_nodes_all * D * sizeof(double), 256);
     const size_t off_istart = align_up(off_gstart + (n_nodes_all + 1) * sizeof(uint64_t), 256);
@@ -602,7 +603,8 @@ pdd_status run_group(pdd_ctx *ctx, std::vector<HostItem *> &items, const pdd_tun
     const size_t off_seg = align_up(off_fitems + n_items * sizeof(FinalItem), 256);
     const size_t off_rng = align_up(off_seg + n_ctr * 2 * sizeof(uint32_t), 256);
     const size_t off_tail = align_up(off_rng + (any_merged ? n_nodes_all * 4 * sizeof(uint32_t) : 0), 256);
-    const size_t bytes = align_up(off_tail + (n_ctr + n_launch) * sizeof(uint32_t), 256);
+    const size_t off_ctr = align_up(off_tail + (n_ctr + n_launch) * sizeof(uint32_t), 256);
+    const size_t bytes = align_up(off_ctr + ctr_bytes, 256);
 
     // launch shape: the path kernel's, and how its walks end
     const int block = tune.block;
@@ -638,7 +640,6 @@ pdd_status run_group(pdd_ctx *ctx, std::vector<HostItem *> &items, const pdd_tun
     }
     if ((st = ensure(ctx, ctx->nodes, bytes))) return st;
     if ((st = ensure(ctx, ctx->acc, n_nodes_all * sizeof(NodeAcc)))) return st;
-    if ((st = ensure(ctx, ctx->counters, ctr_bytes))) return st;
     const bool need_phi = std::any_of(items.begin(), items.end(), [](HostItem *i) { return i->score_plain && !i->caller_records; });
     constexpr bool HAS_E = EST != kEstPlain;
     const size_t per_slot = sizeof(uint32_t) + (need_phi ? 8 : 0) + (HAS_E ? 8 : 0);
@@ -702,6 +703,7 @@ pdd_status run_group(pdd_ctx *ctx, std::vector<HostItem *> &items, const pdd_tun
             h_seg[2 * (ctr_at[l] + k) + 1] = (uint32_t)(std::max(lo, hi) - b);
         }
     }
+    std::memset(h + off_ctr, 0, ctr_bytes);
     // regions of the handed-over paths, per launch: as many as its waves may
     // hand over per item, scaled down to the buffer
     uint32_t *h_tail = reinterpret_cast<uint32_t *>(h + off_tail);
@@ -844,19 +846,26 @@ pdd_status run_group(pdd_ctx *ctx, std::vector<HostItem *> &items, const pdd_tun
     const uint32_t *d_nitem = reinterpret_cast<const uint32_t *>(dv + off_nitem);
     const FinalItem *d_fitems = reinterpret_cast<const FinalItem *>(dv + off_fitems);
     NodeAcc *d_acc = static_cast<NodeAcc *>(ctx->acc.ptr);
+    FinalizeArgs f{};
+    f.acc = d_acc;
+    f.nodes = reinterpret_cast<const double *>(dv + off_nodes);
+    f.n_nodes = (uint32_t)n_nodes_all;
+    f.dim = D;
+    f.has_e = HAS_E;
+    f.node_item = d_nitem;
+    f.fitems = d_fitems;
+    // one launch whose records are all in the scratch: its reduction starts and
+    // ends the nodes' sums itself (a launch less before it and one after, 4 us
+    // each of a small solve's 180)
+    const bool whole = n_launch == 1 && std::none_of(items.begin(), items.end(),
+                                                     [](const HostItem *i) { return i->caller_records; });
     // zero sums, or the earlier paths' sums of accumulating items
-    HIP_TRY(launch_init_acc(d_acc, (uint32_t)n_nodes_all, d_nitem, d_fitems, s));
-    HIP_TRY(launch_zero(ctx->counters.ptr, ctr_bytes, s));
+    if (!whole) HIP_TRY(launch_init_acc(d_acc, (uint32_t)n_nodes_all, d_nitem, d_fitems, s));
     for (size_t k = 0; k < cell_grid.size(); ++k) {
-        if (EST == kEstIto) {
-            for (int c = 0; c < D; ++c)
-                HIP_TRY((launch_grid_cells_strided<T, T, D>(static_cast<const T *>(cell_grid[k][c].data),
-                                                             cell_grid[k]->n, d_cells + cell_off[k],
-                                                             (uint32_t)(D << D), (uint32_t)(c << D), s)));
-        } else {
-            HIP_TRY((launch_grid_cells<T, T, D>(static_cast<const T *>(cell_grid[k]->data), cell_grid[k]->n,
-                                             d_cells + cell_off[k], s)));
-        }
+        const T *data[3] = {};
+        const int grids = EST == kEstIto ? D : 1;
+        for (int c = 0; c < grids; ++c) data[c] = static_cast<const T *>(cell_grid[k][c].data);
+        HIP_TRY((launch_grid_cells<T, D>(data, grids, cell_grid[k]->n, d_cells + cell_off[k], s)));
     }
 
     const ItemDesc<T> *d_items = reinterpret_cast<const ItemDesc<T> *>(dv + off_items);
@@ -871,6 +880,7 @@ pdd_status run_group(pdd_ctx *ctx, std::vector<HostItem *> &items, const pdd_tun
             HIP_TRY(hipEventCreate(&ev.second));
         }
     }
+    uint32_t *const counters = reinterpret_cast<uint32_t *>(dv + off_ctr);
     uint32_t launch = 0;
     for (uint64_t b = 0; b < total; b += per_launch, ++launch) {
         const uint64_t len = std::min(per_launch, total - b);
@@ -879,7 +889,7 @@ pdd_status run_group(pdd_ctx *ctx, std::vector<HostItem *> &items, const pdd_tun
         L.launch_slots = (uint32_t)len;
         L.n_items = n_k;
         L.grab = tune.grab;
-        L.counter = static_cast<uint32_t *>(ctx->counters.ptr) + ctr_at[launch];
+        L.counter = counters + ctr_at[launch];
         L.item_lo = (int32_t)seg_lo[launch];
         L.n_seg = seg_n[launch];
         L.refill_mask = refill_mask<D>(tune);
@@ -891,10 +901,9 @@ pdd_status run_group(pdd_ctx *ctx, std::vector<HostItem *> &items, const pdd_tun
             const uint64_t waves_needed = (len + 63) / 64;
             const uint64_t blocks_needed = (waves_needed * 64 + block - 1) / block;
             const int grid = (int)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)ctx->n_cu * bpc, blocks_needed));
-            uint32_t *ctrs = static_cast<uint32_t *>(ctx->counters.ptr);
             if (tail_cap) {
                 L.tail = ctx->tail.ptr;
-                L.tail_n = ctrs + n_ctr + ctr_at[launch];
+                L.tail_n = counters + n_ctr + ctr_at[launch];
                 L.tail_off = reinterpret_cast<const uint32_t *>(dv + off_tail) + ctr_at[launch] + launch;
                 L.tail_max = tail_max;
             }
@@ -912,7 +921,7 @@ pdd_status run_group(pdd_ctx *ctx, std::vector<HostItem *> &items, const pdd_tun
                 HIP_TRY((launch_path_kernel<T, D, EST>(L, d_items, d_probs, grid, block, kind, s)));
             }
             if (tail_cap) {  // then the longest walks, handed over
-                L.counter = ctrs + 2 * n_ctr + ctr_at[launch];
+                L.counter = counters + 2 * n_ctr + ctr_at[launch];
                 HIP_TRY((launch_path_kernel_group<T, D, EST>(L, d_items, d_probs, group_grid<T>(ctx, len), kind, s)));
             }
         }
@@ -921,9 +930,11 @@ pdd_status run_group(pdd_ctx *ctx, std::vector<HostItem *> &items, const pdd_tun
         // whose records are in the scratch, one per item with caller records
         const uint64_t *d_gstart = reinterpret_cast<const uint64_t *>(dv + off_gstart);
         if (any_scratch) {
-            const uint32_t n_lo = (uint32_t)(std::upper_bound(h_gstart, h_gstart + n_nodes_all + 1, b) - h_gstart - 1);
-            const uint32_t n_hi =
-                (uint32_t)(std::upper_bound(h_gstart, h_gstart + n_nodes_all + 1, b + len - 1) - h_gstart - 1);
+            uint32_t n_lo = 0, n_hi = (uint32_t)n_nodes_all - 1;
+            if (!whole) {
+                n_lo = (uint32_t)(std::upper_bound(h_gstart, h_gstart + n_nodes_all + 1, b) - h_gstart - 1);
+                n_hi = (uint32_t)(std::upper_bound(h_gstart, h_gstart + n_nodes_all + 1, b + len - 1) - h_gstart - 1);
+            }
             ReduceArgs r{};
             r.rec_phi = sc_phi;
             r.rec_e = sc_e;
@@ -938,6 +949,8 @@ pdd_status run_group(pdd_ctx *ctx, std::vector<HostItem *> &items, const pdd_tun
             r.node_item = d_nitem;
             r.fitems = d_fitems;
             r.split = split_in(h_gstart, n_lo, n_hi, b, b + len);
+            r.whole = whole;
+            r.stats = f;
             r.partials = static_cast<NodeAcc *>(ctx->partials.ptr);
             HIP_TRY(launch_reduce(r, n_hi - n_lo + 1, s));
         }
@@ -968,15 +981,7 @@ pdd_status run_group(pdd_ctx *ctx, std::vector<HostItem *> &items, const pdd_tun
         }
     }
     if (timed && total) ctx->timed.push_back(ev);
-    FinalizeArgs f{};
-    f.acc = d_acc;
-    f.nodes = reinterpret_cast<const double *>(dv + off_nodes);
-    f.n_nodes = (uint32_t)n_nodes_all;
-    f.dim = D;
-    f.has_e = HAS_E;
-    f.node_item = d_nitem;
-    f.fitems = d_fitems;
-    HIP_TRY(launch_finalize(f, s));
+    if (!whole) HIP_TRY(launch_finalize(f, s));
     return PDD_OK;
 }
 
@@ -1082,7 +1087,7 @@ void pdd_shutdown(pdd_ctx *ctx)
     (void)hipSetDevice(ctx->device);
     if (ctx->any_done) (void)hipEventSynchronize(ctx->done);
     if (ctx->any_staged) (void)hipEventSynchronize(ctx->staged);
-    for (DeviceBuffer *b : {&ctx->nodes, &ctx->starts, &ctx->tail, &ctx->acc, &ctx->counters, &ctx->rec, &ctx->partials,
+    for (DeviceBuffer *b : {&ctx->nodes, &ctx->starts, &ctx->tail, &ctx->acc, &ctx->rec, &ctx->partials,
                             &ctx->gather, &ctx->cells, &ctx->stage2, &ctx->stage2_factor})
         if (b->ptr) (void)hipFree(b->ptr);
     if (ctx->stage) (void)hipHostFree(ctx->stage);

@@ -76,6 +76,129 @@ __device__ __forceinline__ uint32_t n_chunks_of(uint64_t lo, uint64_t hi)
     return hi > lo ? (uint32_t)((hi - lo + kReduceChunk - 1) / kReduceChunk) : 0u;
 }
 
+// Starting sums of group node i: zero, or for an accumulating solve the
+// statistics of the earlier paths.
+__device__ __forceinline__ NodeAcc starting_sums(const FinalItem &fi, uint32_t i)
+{
+    NodeAcc a;
+    if (fi.accumulate) {
+        const pdd_node_stats &p = fi.out[i - fi.gnode];
+        for (int q = 0; q < 5; ++q) {
+            a.s[q] = p.sums[2 * q];
+            a.c[q] = p.sums[2 * q + 1];
+        }
+        a.n = p.n;
+        a.steps = p.steps_sum;
+        a.capped = p.n_capped;
+    } else {
+        for (int q = 0; q < 5; ++q) a.s[q] = a.c[q] = 0.0;
+        a.n = a.steps = a.capped = 0;
+    }
+    a.pad = 0;
+    return a;
+}
+
+__device__ __forceinline__ double grid_at(const FinalItem &f, size_t i)
+{
+    return f.up_f64 ? static_cast<const double *>(f.up_data)[i]
+                    : (double)static_cast<const float *>(f.up_data)[i];
+}
+
+__device__ double interp_node(const FinalItem &g, int dim, const double *x)
+{
+    int i[3] = {0, 0, 0};
+    double w[3] = {0, 0, 0};
+    for (int d = 0; d < dim; ++d) {
+        const double t = (x[d] - g.up_lo[d]) * g.up_inv[d];
+        const double fl = floor(t);
+        int id = (int)fl;
+        if (fl < 0.0) id = 0;
+        if (fl > (double)(g.up_n[d] - 2)) id = g.up_n[d] - 2;
+        double wd = t - (double)id;
+        wd = wd < 0.0 ? 0.0 : (wd > 1.0 ? 1.0 : wd);
+        i[d] = id;
+        w[d] = wd;
+    }
+    const size_t nx = g.up_n[0], ny = g.up_n[1];
+    if (dim == 2) {
+        const size_t r0 = (size_t)i[1] * nx + i[0], r1 = r0 + nx;
+        return (1.0 - w[1]) * ((1.0 - w[0]) * grid_at(g, r0) + w[0] * grid_at(g, r0 + 1)) +
+               w[1] * ((1.0 - w[0]) * grid_at(g, r1) + w[0] * grid_at(g, r1 + 1));
+    }
+    double acc = 0.0;
+    for (int dz = 0; dz < 2; ++dz) {
+        double layer = 0.0;
+        for (int dy = 0; dy < 2; ++dy) {
+            const size_t row = ((size_t)(i[2] + dz) * ny + (i[1] + dy)) * nx + i[0];
+            layer += (dy ? w[1] : 1.0 - w[1]) *
+                     ((1.0 - w[0]) * grid_at(g, row) + w[0] * grid_at(g, row + 1));
+        }
+        acc += (dz ? w[2] : 1.0 - w[2]) * layer;
+    }
+    return acc;
+}
+
+// The statistics of group node i from its sums.
+__device__ void write_stats(const FinalizeArgs &f, uint32_t i, const NodeAcc &A)
+{
+    const FinalItem &fi = f.fitems[f.node_item[i]];
+    const bool has_phi = fi.has_phi != 0;
+    pdd_node_stats st;
+    const double nan = __builtin_nan("");
+    st.n = A.n;
+    st.n_capped = A.capped;
+    st.steps_sum = A.steps;
+    for (int q = 0; q < 5; ++q) {
+        st.sums[2 * q] = A.s[q];
+        st.sums[2 * q + 1] = A.c[q];
+    }
+    st.mean = st.var = st.stderr_ = st.mean_steps = nan;
+    st.mean_plain = st.var_plain = st.cov = st.rho = st.vr = st.vr_opt = nan;
+    if (A.n > 0) {
+        const double n = (double)A.n;
+        const double Sp = A.s[0] + A.c[0], Sp2 = A.s[1] + A.c[1];
+        const double Se = A.s[2] + A.c[2], Se2 = A.s[3] + A.c[3], Spe = A.s[4] + A.c[4];
+        st.mean_steps = (double)A.steps / n;
+        if (has_phi) {
+            st.mean_plain = Sp / n;
+            st.var_plain = A.n > 1 ? (Sp2 - Sp * Sp / n) / (n - 1.0) : nan;
+        }
+        if (!f.has_e) {
+            st.mean = st.mean_plain;
+            st.var = st.var_plain;
+            st.stderr_ = sqrt(st.var / n);
+        } else {
+            st.mean = (fi.up_data ? interp_node(fi, f.dim, f.nodes + (size_t)i * f.dim) : 0.0) + Se / n;
+            st.var = A.n > 1 ? (Se2 - Se * Se / n) / (n - 1.0) : nan;
+            st.stderr_ = sqrt(st.var / n);
+            if (has_phi) {
+                // xi = u_prev(x0) + e - phi is the pathwise control variate
+                // (Ito items: xi = e - phi); the constant enters neither cov nor rho
+                const double cpe = A.n > 1 ? (Spe - Sp * Se / n) / (n - 1.0) : nan;
+                const double vxi = st.var + st.var_plain - 2.0 * cpe;
+                st.cov = cpe - st.var_plain;
+                st.rho = st.cov / sqrt(st.var_plain * vxi);
+                st.vr = st.var_plain / st.var;
+                st.vr_opt = 1.0 / (1.0 - st.rho * st.rho);
+            }
+        }
+    }
+    fi.out[i - fi.gnode] = st;
+}
+
+// A node's sums before a launch of r, and after it.
+__device__ __forceinline__ NodeAcc sums_before(const ReduceArgs &r, uint32_t node)
+{
+    return r.whole ? starting_sums(r.fitems[r.node_item[node]], node) : r.acc[node];
+}
+__device__ __forceinline__ void sums_after(const ReduceArgs &r, uint32_t node, const NodeAcc &A)
+{
+    if (r.whole)
+        write_stats(r.stats, node, A);
+    else
+        r.acc[node] = A;
+}
+
 // The split launch's workgroups and partials run through the nodes' segments:
 // those of node_lo + b start at chunk_at(b). Enough for its chunks, as the
 // next segment starts where this one ends.
@@ -183,7 +306,7 @@ __global__ void __launch_bounds__(kReduceBlock) reduce_kernel(const ReduceArgs r
         r.partials[blockIdx.x] = p;
     }
     if (threadIdx.x == 0 && direct) {
-        NodeAcc &A = r.acc[node];
+        NodeAcc A = sums_before(r, node);
         Pair tot[5];
 #pragma unroll
         for (int q = 0; q < 5; ++q) tot[q] = {A.s[q], A.c[q]};
@@ -203,6 +326,7 @@ __global__ void __launch_bounds__(kReduceBlock) reduce_kernel(const ReduceArgs r
         A.steps = st;
         A.capped = cp;
         A.n += (long long)(hi > lo ? hi - lo : 0);
+        sums_after(r, node, A);
     }
 }
 
@@ -229,7 +353,7 @@ __global__ void __launch_bounds__(kReduceBlock) merge_chunks_kernel(const Reduce
     }
     wave_merge(tot, steps, capped);
     if (lane) return;
-    NodeAcc &A = r.acc[node];
+    NodeAcc A = sums_before(r, node);
     for (int q = 0; q < 5; ++q) {
         const Pair sum = nmerge(Pair{A.s[q], A.c[q]}, tot[q]);
         A.s[q] = sum.s;
@@ -238,121 +362,19 @@ __global__ void __launch_bounds__(kReduceBlock) merge_chunks_kernel(const Reduce
     A.steps += steps;
     A.capped += capped;
     A.n += (long long)(hi - lo);
-}
-
-__device__ __forceinline__ double grid_at(const FinalItem &f, size_t i)
-{
-    return f.up_f64 ? static_cast<const double *>(f.up_data)[i]
-                    : (double)static_cast<const float *>(f.up_data)[i];
-}
-
-__device__ double interp_node(const FinalItem &g, int dim, const double *x)
-{
-    int i[3] = {0, 0, 0};
-    double w[3] = {0, 0, 0};
-    for (int d = 0; d < dim; ++d) {
-        const double t = (x[d] - g.up_lo[d]) * g.up_inv[d];
-        const double fl = floor(t);
-        int id = (int)fl;
-        if (fl < 0.0) id = 0;
-        if (fl > (double)(g.up_n[d] - 2)) id = g.up_n[d] - 2;
-        double wd = t - (double)id;
-        wd = wd < 0.0 ? 0.0 : (wd > 1.0 ? 1.0 : wd);
-        i[d] = id;
-        w[d] = wd;
-    }
-    const size_t nx = g.up_n[0], ny = g.up_n[1];
-    if (dim == 2) {
-        const size_t r0 = (size_t)i[1] * nx + i[0], r1 = r0 + nx;
-        return (1.0 - w[1]) * ((1.0 - w[0]) * grid_at(g, r0) + w[0] * grid_at(g, r0 + 1)) +
-               w[1] * ((1.0 - w[0]) * grid_at(g, r1) + w[0] * grid_at(g, r1 + 1));
-    }
-    double acc = 0.0;
-    for (int dz = 0; dz < 2; ++dz) {
-        double layer = 0.0;
-        for (int dy = 0; dy < 2; ++dy) {
-            const size_t row = ((size_t)(i[2] + dz) * ny + (i[1] + dy)) * nx + i[0];
-            layer += (dy ? w[1] : 1.0 - w[1]) *
-                     ((1.0 - w[0]) * grid_at(g, row) + w[0] * grid_at(g, row + 1));
-        }
-        acc += (dz ? w[2] : 1.0 - w[2]) * layer;
-    }
-    return acc;
+    sums_after(r, node, A);
 }
 
 __global__ void finalize_kernel(const FinalizeArgs f)
 {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= f.n_nodes) return;
-    const NodeAcc &A = f.acc[i];
-    const FinalItem &fi = f.fitems[f.node_item[i]];
-    const bool has_phi = fi.has_phi != 0;
-    pdd_node_stats st;
-    const double nan = __builtin_nan("");
-    st.n = A.n;
-    st.n_capped = A.capped;
-    st.steps_sum = A.steps;
-    for (int q = 0; q < 5; ++q) {
-        st.sums[2 * q] = A.s[q];
-        st.sums[2 * q + 1] = A.c[q];
-    }
-    st.mean = st.var = st.stderr_ = st.mean_steps = nan;
-    st.mean_plain = st.var_plain = st.cov = st.rho = st.vr = st.vr_opt = nan;
-    if (A.n > 0) {
-        const double n = (double)A.n;
-        const double Sp = A.s[0] + A.c[0], Sp2 = A.s[1] + A.c[1];
-        const double Se = A.s[2] + A.c[2], Se2 = A.s[3] + A.c[3], Spe = A.s[4] + A.c[4];
-        st.mean_steps = (double)A.steps / n;
-        if (has_phi) {
-            st.mean_plain = Sp / n;
-            st.var_plain = A.n > 1 ? (Sp2 - Sp * Sp / n) / (n - 1.0) : nan;
-        }
-        if (!f.has_e) {
-            st.mean = st.mean_plain;
-            st.var = st.var_plain;
-            st.stderr_ = sqrt(st.var / n);
-        } else {
-            st.mean = (fi.up_data ? interp_node(fi, f.dim, f.nodes + (size_t)i * f.dim) : 0.0) + Se / n;
-            st.var = A.n > 1 ? (Se2 - Se * Se / n) / (n - 1.0) : nan;
-            st.stderr_ = sqrt(st.var / n);
-            if (has_phi) {
-                // xi = u_prev(x0) + e - phi is the pathwise control variate
-                // (Ito items: xi = e - phi); the constant enters neither cov nor rho
-                const double cpe = A.n > 1 ? (Spe - Sp * Se / n) / (n - 1.0) : nan;
-                const double vxi = st.var + st.var_plain - 2.0 * cpe;
-                st.cov = cpe - st.var_plain;
-                st.rho = st.cov / sqrt(st.var_plain * vxi);
-                st.vr = st.var_plain / st.var;
-                st.vr_opt = 1.0 / (1.0 - st.rho * st.rho);
-            }
-        }
-    }
-    fi.out[i - fi.gnode] = st;
+    if (i < f.n_nodes) write_stats(f, i, f.acc[i]);
 }
 
-// Starting sums: zero, or for an accumulating solve the statistics of the
-// earlier paths.
 __global__ void init_acc_kernel(NodeAcc *acc, uint32_t n, const uint32_t *node_item, const FinalItem *fitems)
 {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const FinalItem &fi = fitems[node_item[i]];
-    NodeAcc a;
-    if (fi.accumulate) {
-        const pdd_node_stats &p = fi.out[i - fi.gnode];
-        for (int q = 0; q < 5; ++q) {
-            a.s[q] = p.sums[2 * q];
-            a.c[q] = p.sums[2 * q + 1];
-        }
-        a.n = p.n;
-        a.steps = p.steps_sum;
-        a.capped = p.n_capped;
-    } else {
-        for (int q = 0; q < 5; ++q) a.s[q] = a.c[q] = 0.0;
-        a.n = a.steps = a.capped = 0;
-    }
-    a.pad = 0;
-    acc[i] = a;
+    if (i < n) acc[i] = starting_sums(fitems[node_item[i]], i);
 }
 
 // One workgroup per item, copying its statistics word by word.

@@ -1,7 +1,8 @@
 """The reduction's chunks (4,096 paths) at their edges: nodes of one path more
 or less than a chunk, of none and of more chunks than a wave has lanes, in one
 launch and in launches that cut them, against exact sums of the records: to
-1e-12 of the summed magnitudes, the counts exactly."""
+1e-12 of the summed magnitudes, the counts exactly. Without the caller's
+records (one launch then reduces and ends the statistics at once), the same bits."""
 import math
 
 import numpy as np
@@ -27,6 +28,8 @@ def test_chunk_edges(counts, cap):
     rec = pdd.alloc_records(int(counts.sum()))
     st = pdd.stats_to_numpy(pdd.solve_nodes(prob, nodes, dt=4e-3, n_paths_per_node=counts, records=rec,
                                             tuning=(256, 0, 64, cap)))
+    scratch = pdd.stats_to_numpy(pdd.solve_nodes(prob, nodes, dt=4e-3, n_paths_per_node=counts, tuning=(256, 0, 64, cap)))
+    assert scratch.tobytes() == st.tobytes()
     phis, words = rec["phi"].cpu().numpy(), rec["steps"].cpu().numpy().view(np.uint32)
     prob.close()
     ctx.close()
