@@ -14,30 +14,36 @@ using pdd::fail;
 namespace {
 
 // Derivative along one axis at a point whose index along that axis is a (of
-// n): central inside, three-point one-sided at the two ends; s is the
+// n): central inside, three-point one-sided at the two ends; st is the
 // point's stride along the axis, two_dx twice the spacing.
-template <class S>
-__device__ __forceinline__ S axis_derivative(const S *__restrict__ u, uint64_t p, uint64_t s, int a, int n, S two_dx)
+template <class S, class I>
+__device__ __forceinline__ S axis_derivative(const S *__restrict__ u, I p, S u0, I st, int a, int n, S two_dx)
 {
-    if (a == 0) return ((S)-3 * u[p] + (S)4 * u[p + s] - u[p + 2 * s]) / two_dx;
-    if (a == n - 1) return ((S)3 * u[p] - (S)4 * u[p - s] + u[p - 2 * s]) / two_dx;
-    return (u[p + s] - u[p - s]) / two_dx;
+    const bool low = a == 0, high = a == n - 1;
+    // the point before and the point after, or at an end the next two inwards
+    const S v1 = u[low ? p + st : p - st];
+    const S v2 = u[low ? p + 2 * st : high ? p - 2 * st : p + st];
+    const S d = low ? (S)-3 * u0 + (S)4 * v1 - v2 : high ? (S)3 * u0 - (S)4 * v1 + v2 : v2 - v1;
+    return d / two_dx;
 }
 
 // One thread per grid point (x fastest, so neighbouring threads read
-// neighbouring values), all dim components.
-template <class S, int D>
-__global__ void grid_gradient_kernel(const S *__restrict__ u, int n0, int n1, int n2, S dx0, S dx1, S dx2,
-                                     S *__restrict__ g0, S *__restrict__ g1, S *__restrict__ g2)
+// neighbouring values), all dim components. I: the type that holds a point's
+// number (64-bit divisions cost a third of the time: 129^3 FP32 14.4 and 11.2
+// us, 34 MB). Bound by memory: 2049^2 FP64 20 us, 101 MB.
+template <class S, int D, class I>
+__global__ void __launch_bounds__(256) grid_gradient_kernel(const S *__restrict__ u, int n0, int n1, int n2, S dx0, S dx1,
+                                                            S dx2, S *__restrict__ g0, S *__restrict__ g1,
+                                                            S *__restrict__ g2)
 {
-    const uint64_t m01 = (uint64_t)n0 * n1;
-    const uint64_t total = m01 * (D == 3 ? (uint64_t)n2 : 1);
-    for (uint64_t p = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; p < total;
-         p += (uint64_t)gridDim.x * blockDim.x) {
-        const int i = (int)(p % n0), j = (int)((p / n0) % n1);
-        g0[p] = axis_derivative<S>(u, p, 1, i, n0, dx0);
-        g1[p] = axis_derivative<S>(u, p, (uint64_t)n0, j, n1, dx1);
-        if (D == 3) g2[p] = axis_derivative<S>(u, p, m01, (int)(p / m01), n2, dx2);
+    const I m01 = (I)n0 * n1, total = m01 * (D == 3 ? n2 : 1);
+    for (I p = blockIdx.x * (I)blockDim.x + threadIdx.x; p < total; p += (I)gridDim.x * blockDim.x) {
+        const I jk = p / n0;
+        const int k = D == 3 ? (int)(jk / n1) : 0, i = (int)(p - jk * n0), j = D == 3 ? (int)(jk - (I)k * n1) : (int)jk;
+        const S u0 = u[p];
+        g0[p] = axis_derivative<S, I>(u, p, u0, 1, i, n0, dx0);
+        g1[p] = axis_derivative<S, I>(u, p, u0, (I)n0, j, n1, dx1);
+        if (D == 3) g2[p] = axis_derivative<S, I>(u, p, u0, m01, k, n2, dx2);
     }
 }
 
@@ -49,9 +55,11 @@ hipError_t launch_gradient(const pdd_grid *g, void *const *out, hipStream_t s)
     const uint64_t blocks = std::min<uint64_t>((total + 255) / 256, 16384);
     S two_dx[3] = {0, 0, 0};
     for (int d = 0; d < D; ++d) two_dx[d] = (S)(2.0 * ((g->hi[d] - g->lo[d]) / (g->n[d] - 1)));
-    hipLaunchKernelGGL((grid_gradient_kernel<S, D>), dim3((uint32_t)blocks), dim3(256), 0, s,
-                       static_cast<const S *>(g->data), g->n[0], g->n[1], n2, two_dx[0], two_dx[1], two_dx[2],
-                       static_cast<S *>(out[0]), static_cast<S *>(out[1]), static_cast<S *>(D == 3 ? out[2] : out[1]));
+    // (2^31: a thread's next point still fits in 32 bits)
+    const auto kernel = total < (1ull << 31) ? grid_gradient_kernel<S, D, uint32_t> : grid_gradient_kernel<S, D, uint64_t>;
+    hipLaunchKernelGGL(kernel, dim3((uint32_t)blocks), dim3(256), 0, s, static_cast<const S *>(g->data), g->n[0], g->n[1],
+                       n2, two_dx[0], two_dx[1], two_dx[2], static_cast<S *>(out[0]), static_cast<S *>(out[1]),
+                       static_cast<S *>(D == 3 ? out[2] : out[1]));
     return hipGetLastError();
 }
 

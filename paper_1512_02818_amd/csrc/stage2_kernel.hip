@@ -12,27 +12,33 @@ namespace {
 // its points, b, c, f from the problem (FP64), the derivatives of u by
 // second-order differences (central inside; three-point one-sided first and
 // four-point one-sided second derivatives at the ends of each axis).
-template <class S>
-__device__ __forceinline__ double fd_first(const S *__restrict__ u, uint64_t p, uint64_t s, int a, int n, double dx)
+// First and second derivative along one axis at point p, whose index there is
+// a of n (stride st): central inside, one-sided at the two ends.
+template <class S, class I>
+__device__ __forceinline__ void fd(const S *__restrict__ u, I p, double u0, I st, int a, int n, double dx, double &first,
+                                   double &second)
 {
-    if (a == 0) return (-3.0 * (double)u[p] + 4.0 * (double)u[p + s] - (double)u[p + 2 * s]) / (2.0 * dx);
-    if (a == n - 1) return (3.0 * (double)u[p] - 4.0 * (double)u[p - s] + (double)u[p - 2 * s]) / (2.0 * dx);
-    return ((double)u[p + s] - (double)u[p - s]) / (2.0 * dx);
+    const bool low = a == 0, high = a == n - 1;
+    // the point before and the point after, or at an end the next two inwards
+    const double v1 = (double)u[low ? p + st : p - st];
+    const double v2 = (double)u[low ? p + 2 * st : high ? p - 2 * st : p + st];
+    double n1 = v2 - v1, n2 = v2 - 2.0 * u0 + v1;
+    if (low || high) {
+        const double v3 = (double)u[low ? p + 3 * st : p - 3 * st];
+        n1 = low ? -3.0 * u0 + 4.0 * v1 - v2 : 3.0 * u0 - 4.0 * v1 + v2;
+        n2 = 2.0 * u0 - 5.0 * v1 + 4.0 * v2 - v3;
+    }
+    first = n1 / (2.0 * dx);
+    second = n2 / (dx * dx);
 }
 
-template <class S>
-__device__ __forceinline__ double fd_second(const S *__restrict__ u, uint64_t p, uint64_t s, int a, int n, double dx)
-{
-    if (a == 0)
-        return (2.0 * (double)u[p] - 5.0 * (double)u[p + s] + 4.0 * (double)u[p + 2 * s] - (double)u[p + 3 * s]) /
-               (dx * dx);
-    if (a == n - 1)
-        return (2.0 * (double)u[p] - 5.0 * (double)u[p - s] + 4.0 * (double)u[p - 2 * s] - (double)u[p - 3 * s]) /
-               (dx * dx);
-    return ((double)u[p + s] - 2.0 * (double)u[p] + (double)u[p - s]) / (dx * dx);
-}
-
-template <class S, int D>
+// I: the type that holds a point's number (a division by a 64-bit grid size
+// costs more than the derivatives). TAB: the problem has tabulated coefficients
+// or trig arguments that need the library's reduction. Bound by the source's
+// FP64 functions. 513^2 FP64 points 8.3 us, 5.4 us with 32-bit numbers, all
+// loads first and the analytic form; 2049^2 61 and 41 us (67 MB: 14 us at the
+// rate of a copy); 129^3 FP32 131 and 87 us.
+template <class S, int D, class I, bool TAB>
 __global__ void __launch_bounds__(256) grid_residual_kernel(const DevProblem<double> P, const S *__restrict__ u,
                                                             int n0, int n1, int n2, double lo0, double lo1,
                                                             double lo2, double dx0, double dx1, double dx2,
@@ -41,29 +47,53 @@ __global__ void __launch_bounds__(256) grid_residual_kernel(const DevProblem<dou
     __shared__ double s_cf[kMaxDense];
     for (int q = threadIdx.x; q < kMaxDense; q += blockDim.x) s_cf[q] = P.fdense[q];
     __syncthreads();
-    const uint64_t m01 = (uint64_t)n0 * n1;
-    const uint64_t total = m01 * (D == 3 ? (uint64_t)n2 : 1);
+    const I m01 = (I)n0 * n1, total = m01 * (D == 3 ? n2 : 1);
     const int nn[3] = {n0, n1, n2};
     MathOf<double> mt;
     mt.init();
     const double lo[3] = {lo0, lo1, lo2}, dx[3] = {dx0, dx1, dx2};
-    const uint64_t st[3] = {1, (uint64_t)n0, m01};
-    for (uint64_t p = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; p < total;
-         p += (uint64_t)gridDim.x * blockDim.x) {
-        const int idx[3] = {(int)(p % n0), (int)((p / n0) % n1), D == 3 ? (int)(p / m01) : 0};
-        double x[D];
+    const I st[3] = {1, (I)n0, m01};
+    for (I p = blockIdx.x * (I)blockDim.x + threadIdx.x; p < total; p += (I)gridDim.x * blockDim.x) {
+        const I jk = p / n0;
+        const int k = D == 3 ? (int)(jk / n1) : 0;
+        const int idx[3] = {(int)(p - jk * n0), D == 3 ? (int)(jk - (I)k * n1) : (int)jk, k};
+        const double u0 = (double)u[p];
+        double x[D], first[D], second[D];
 #pragma unroll
-        for (int d = 0; d < D; ++d) x[d] = lo[d] + (double)idx[d] * dx[d];
+        for (int d = 0; d < D; ++d) {
+            x[d] = lo[d] + (double)idx[d] * dx[d];
+            fd<S, I>(u, p, u0, st[d], idx[d], nn[d], dx[d], first[d], second[d]);
+        }
         double b[D], c, f = 0.0;
-        coefficients<double, D, true>(mt, P, x, b, c, f, true, s_cf, P.tab);
+        coefficients<double, D, TAB>(mt, P, x, b, c, f, true, s_cf, TAB ? P.tab : 0u);
         double lap = 0.0, adv = 0.0;
 #pragma unroll
         for (int d = 0; d < D; ++d) {
-            lap += fd_second<S>(u, p, st[d], idx[d], nn[d], dx[d]);
-            adv += b[d] * fd_first<S>(u, p, st[d], idx[d], nn[d], dx[d]);
+            lap += second[d];
+            adv += b[d] * first[d];
         }
-        r[p] = (S)(f - (half_s2 * lap + adv + c * (double)u[p]));
+        r[p] = (S)(f - (half_s2 * lap + adv + c * u0));
     }
+}
+
+template <class S, int D, bool TAB>
+hipError_t launch_residual(const DevProblem<double> &P, double sigma, const pdd_grid *g, void *r, hipStream_t s)
+{
+    const int n2 = D == 3 ? g->n[2] : 1;
+    const uint64_t total = (uint64_t)g->n[0] * g->n[1] * n2;
+    // four workgroups per CU: what a wave loads before its first point (the
+    // problem, the functions' coefficients) is shared by more points (2049^2
+    // points 49 us with a workgroup per 256 points, 41 us so)
+    const uint32_t blocks = (uint32_t)std::min<uint64_t>((total + 255) / 256, 1024);
+    double dx[3] = {0, 0, 0};
+    for (int d = 0; d < D; ++d) dx[d] = (g->hi[d] - g->lo[d]) / (g->n[d] - 1);
+    // (2^31: a thread's next point still fits in 32 bits)
+    const auto kernel = total < (1ull << 31) ? grid_residual_kernel<S, D, uint32_t, TAB>
+                                               : grid_residual_kernel<S, D, uint64_t, TAB>;
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, s, P, static_cast<const S *>(g->data), g->n[0], g->n[1], n2,
+                       g->lo[0], g->lo[1], D == 3 ? g->lo[2] : 0.0, dx[0], dx[1], dx[2], 0.5 * sigma * sigma,
+                       static_cast<S *>(r));
+    return hipGetLastError();
 }
 
 // Second stage (the subdomain-BVP step of Alg. A:IterPDD) on a 2D box cut by
@@ -904,33 +934,12 @@ hipError_t launch_cyclic_reduction(const Stage2Grid &g, const SubBox *boxes, int
 
 hipError_t launch_grid_residual(const DevProblem<double> &P, double sigma, const pdd_grid *g, void *r, hipStream_t s)
 {
-    const int D = g->dim;
-    const int n2 = D == 3 ? g->n[2] : 1;
-    const uint64_t total = (uint64_t)g->n[0] * g->n[1] * n2;
-    const uint32_t blocks = (uint32_t)std::min<uint64_t>((total + 255) / 256, 16384);
-    double dx[3] = {0, 0, 0};
-    for (int d = 0; d < D; ++d) dx[d] = (g->hi[d] - g->lo[d]) / (g->n[d] - 1);
-    const double h2 = 0.5 * sigma * sigma;
-    if (g->dtype == PDD_DTYPE_F32) {
-        const float *u = static_cast<const float *>(g->data);
-        float *out = static_cast<float *>(r);
-        if (D == 2)
-            hipLaunchKernelGGL((grid_residual_kernel<float, 2>), dim3(blocks), dim3(256), 0, s, P, u, g->n[0], g->n[1],
-                               n2, g->lo[0], g->lo[1], 0.0, dx[0], dx[1], 0.0, h2, out);
-        else
-            hipLaunchKernelGGL((grid_residual_kernel<float, 3>), dim3(blocks), dim3(256), 0, s, P, u, g->n[0], g->n[1],
-                               n2, g->lo[0], g->lo[1], g->lo[2], dx[0], dx[1], dx[2], h2, out);
-    } else {
-        const double *u = static_cast<const double *>(g->data);
-        double *out = static_cast<double *>(r);
-        if (D == 2)
-            hipLaunchKernelGGL((grid_residual_kernel<double, 2>), dim3(blocks), dim3(256), 0, s, P, u, g->n[0],
-                               g->n[1], n2, g->lo[0], g->lo[1], 0.0, dx[0], dx[1], 0.0, h2, out);
-        else
-            hipLaunchKernelGGL((grid_residual_kernel<double, 3>), dim3(blocks), dim3(256), 0, s, P, u, g->n[0],
-                               g->n[1], n2, g->lo[0], g->lo[1], g->lo[2], dx[0], dx[1], dx[2], h2, out);
-    }
-    return hipGetLastError();
+    const bool tab = P.tab != 0 || P.big_trig;
+    if (g->dtype == PDD_DTYPE_F32)
+        return g->dim == 2 ? (tab ? launch_residual<float, 2, true> : launch_residual<float, 2, false>)(P, sigma, g, r, s)
+                           : (tab ? launch_residual<float, 3, true> : launch_residual<float, 3, false>)(P, sigma, g, r, s);
+    return g->dim == 2 ? (tab ? launch_residual<double, 2, true> : launch_residual<double, 2, false>)(P, sigma, g, r, s)
+                       : (tab ? launch_residual<double, 3, true> : launch_residual<double, 3, false>)(P, sigma, g, r, s);
 }
 
 hipError_t launch_stage2_boundary(const DevProblem<double> &P, const Stage2Grid &g, hipStream_t s)
