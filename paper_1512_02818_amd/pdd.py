@@ -310,7 +310,9 @@ def grid_struct(gd: dict, tensor) -> Grid:
 def _stream_handle(stream):
     import torch
     if stream is None:
-        stream = torch.cuda.current_stream()
+        # the current stream's handle without the object that
+        # torch.cuda.current_stream() makes for it (3 us of a call)
+        return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
     return C.c_void_p(stream.cuda_stream)
 
 
