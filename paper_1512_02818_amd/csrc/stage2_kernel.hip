@@ -612,13 +612,14 @@ __global__ void __launch_bounds__(kStage2SubstThreads) stage2_subst_kernel(const
 // direct solve, or the LU is the farther off). The LU's chain of w L dependent
 // pivots, one workgroup a subdomain, becomes 1 + log2 L levels whose rows are
 // independent. Four strips of 63 x 255 unknowns: 39.9 ms with the LU and the
-// solutions for unit boundary values that it was kept as, 0.52 ms now; with
-// the factors kept 0.26 and 0.20 ms. What bounds a level is the inversion
-// (27 us: 64 dependent pivots) and the products on the FP64 matrix cores
+// solutions for unit boundary values that it was kept as, 0.45 ms now; with
+// the factors kept 0.26 and 0.19 ms. What bounds a level is the inversion
+// (24 us: 64 dependent pivots) and the products on the FP64 matrix cores
 // (9 us; 37 us where the rows are several per CU). Blocks are padded by the
 // identity to WP (the widest subdomain's w, to a multiple of 16) and kept by
 // column: D (D^-1 once eliminated), P, Q of every row, and M, N and the new A,
-// C of every (row, level).
+// C of every (row, level); level 0, whose A and C are diagonal, has no P, Q, M
+// and N (stored all the same they took 32 us of 0.48 ms).
 template <int WP>
 struct CrBox {
     static constexpr int kBlock = WP * WP;
@@ -647,7 +648,7 @@ struct CrBox {
     }
 };
 
-constexpr int kCrThreads = 512;
+constexpr int kCrThreads = 1024;
 constexpr int kCrWaves = kCrThreads / 64;
 typedef double Acc4 __attribute__((ext_vector_type(4)));
 
@@ -689,17 +690,19 @@ __device__ __forceinline__ double *cr_element(double *block, int ti, int tj, int
     return block + (tj * 16 + 4 * v + (lane >> 4)) * WP + ti * 16 + (lane & 15);
 }
 
-// D^-1, P and Q of the odd multiples of 2^level, one workgroup each. D is
-// inverted in registers: lane r of wave q holds columns 8 q .. 8 q + 7 of row
-// r. The pivots of a wave's columns are its own work, without a barrier (row k
-// comes from lane k); their multipliers then go to the other waves through
-// LDS: one barrier per eight pivots (32 us a level with one per pivot, 27 us
-// so). Rows are left unscaled until the end.
-template <int WP>
+// D^-1, P and Q (D^-1 alone at the FIRST level) of the odd multiples of
+// 2^level, one workgroup each. D is inverted in registers: lane r of wave q
+// holds columns 4 q .. 4 q + 3 of row r. The pivots of a wave's columns are its
+// own work, without a barrier (row k comes from lane k); their multipliers then
+// go to the other waves through LDS: one barrier per four pivots. (32 us a
+// level with one per pivot, 27 us with eight waves of eight columns, 24 us so.)
+// Rows are left unscaled until the end.
+template <int WP, bool FIRST>
 __global__ void __launch_bounds__(kCrThreads) stage2_cr_eliminate_kernel(const SubBox *boxes, const Stage2Cr *tab,
                                                                          const double *stencil, double *cr, int level)
 {
-    __shared__ double X[WP * (WP + 1)], A[WP * (WP + 1)], C[WP * (WP + 1)];
+    constexpr int kLds = FIRST ? 1 : WP * (WP + 1);
+    __shared__ double X[kLds], A[kLds], C[kLds];
     constexpr int kCols = 64 / kCrWaves;
     __shared__ double mult[2][kCols][64], inverse[64];
     const CrBox<WP> bx(boxes, tab, blockIdx.y);
@@ -712,12 +715,12 @@ __global__ void __launch_bounds__(kCrThreads) stage2_cr_eliminate_kernel(const S
 #pragma unroll
     for (int e = 0; e < kCols; ++e) {
         const int k = q * kCols + e;
-        if (level == 0)
+        if (FIRST)
             a[e] = bx.centre(stencil, i, r, k);
         else
             a[e] = r < WP && k < WP ? gload(row + k * WP + r) : (r == k ? 1.0 : 0.0);
     }
-    if (level > 0) {  // the last update's
+    if (!FIRST) {  // the last update's
         const double *ac = bx.pair(cr, level - 1, i >> level) + 2 * nb;
         cr_stage<WP>(A, ac);
         cr_stage<WP>(C, ac + nb);
@@ -758,14 +761,9 @@ __global__ void __launch_bounds__(kCrThreads) stage2_cr_eliminate_kernel(const S
         a[e] *= scale;
         if (r >= WP || k >= WP) continue;
         gstore(D + k * WP + r, a[e]);
-        if (level == 0) {
-            gstore(P + k * WP + r, a[e] * bx.slot(stencil, i, k, 0));
-            gstore(Q + k * WP + r, a[e] * bx.slot(stencil, i, k, 4));
-        } else {
-            X[k * (WP + 1) + r] = a[e];
-        }
+        if (!FIRST) X[k * (WP + 1) + r] = a[e];
     }
-    if (level == 0) return;
+    if (FIRST) return;
     __syncthreads();
     const int nt = WP / 16;
     for (int n = q; n < 2 * nt * nt; n += kCrWaves) {
@@ -777,12 +775,42 @@ __global__ void __launch_bounds__(kCrThreads) stage2_cr_eliminate_kernel(const S
     }
 }
 
-// The even multiples of 2^level after their neighbours' elimination: M and N
-// (part 0), the new A and C (1) and D (2), a workgroup each, two products.
-// Level 0's A and C are diagonal.
+// The even multiples of 2 after level 0, whose A and C are diagonal: all from
+// the neighbours' D^-1, element by element.
+template <int WP>
+__global__ void __launch_bounds__(kCrThreads) stage2_cr_first_update_kernel(const SubBox *boxes, const Stage2Cr *tab,
+                                                                            const double *stencil, double *cr)
+{
+    __shared__ double al[WP], cl[WP], ai[WP], ci[WP], au[WP], cu[WP];
+    const CrBox<WP> bx(boxes, tab, blockIdx.y);
+    const int i = 2 * ((int)blockIdx.x + 1);
+    if (i > bx.b.L) return;  // whole workgroup
+    const bool has_upper = i + 1 <= bx.b.L;
+    if (threadIdx.x < WP) {
+        const int r = threadIdx.x;
+        al[r] = bx.slot(stencil, i - 1, r, 0), cl[r] = bx.slot(stencil, i - 1, r, 4);
+        ai[r] = bx.slot(stencil, i, r, 0), ci[r] = bx.slot(stencil, i, r, 4);
+        au[r] = has_upper ? bx.slot(stencil, i + 1, r, 0) : 0.0, cu[r] = has_upper ? bx.slot(stencil, i + 1, r, 4) : 0.0;
+    }
+    __syncthreads();
+    constexpr int nb = WP * WP;
+    const double *lower = bx.row(cr, i - 1), *upper = bx.row(cr, has_upper ? i + 1 : i - 1);
+    double *D = bx.row(cr, i), *ac = bx.pair(cr, 0, (int)blockIdx.x + 1) + 2 * nb;
+    for (int e = threadIdx.x; e < nb; e += kCrThreads) {
+        const int r = e % WP, k = e / WP;
+        const double va = ai[r] * gload(lower + e), vc = has_upper ? ci[r] * gload(upper + e) : 0.0;
+        gstore(D + e, bx.centre(stencil, i, r, k) - va * cl[k] - vc * au[k]);
+        gstore(ac + e, -(va * al[k]));
+        gstore(ac + nb + e, -(vc * cu[k]));
+    }
+}
+
+// The even multiples of 2^level, level > 0, after their neighbours'
+// elimination: M and N (part 0), the new A and C (1) and D (2), a workgroup
+// each, two products.
 template <int WP>
 __global__ void __launch_bounds__(kCrThreads) stage2_cr_update_kernel(const SubBox *boxes, const Stage2Cr *tab,
-                                                                      const double *stencil, double *cr, int level)
+                                                                      double *cr, int level)
 {
     __shared__ double X[2][WP * (WP + 1)], Y[2][WP * (WP + 1)];
     const CrBox<WP> bx(boxes, tab, blockIdx.y);
@@ -797,20 +825,6 @@ __global__ void __launch_bounds__(kCrThreads) stage2_cr_update_kernel(const SubB
     const double *a = lower + (size_t)(part == 0 ? 0 : part == 1 ? 1 : 2) * nb;
     const double *c = upper + (size_t)(part == 0 ? 0 : part == 1 ? 2 : 1) * nb;
     const double sign = part == 0 ? 1.0 : -1.0;
-    if (level == 0) {
-        for (int e = threadIdx.x; e < (int)nb; e += kCrThreads) {
-            const int r = e % WP, k = e / WP;
-            const double va = sign * bx.slot(stencil, i, r, 0) * a[e];
-            const double vc = has_upper ? sign * bx.slot(stencil, i, r, 4) * c[e] : 0.0;
-            if (part == 2) {
-                D[e] = bx.centre(stencil, i, r, k) + va + vc;
-            } else {
-                out[e] = va;
-                out[nb + e] = vc;
-            }
-        }
-        return;
-    }
     const int q = threadIdx.x >> 6, nt = WP / 16, tiles = nt * nt;
     const double *ac = bx.pair(cr, level - 1, i >> level) + 2 * nb;
     cr_stage<WP>(X[0], ac);
@@ -852,11 +866,11 @@ __device__ __forceinline__ double cr_dot(const double *B, const double *x, int r
 
 // Forward (FORWARD) and back substitution of the right sides at one level, a
 // workgroup per block row. Bound by latency (5 us a launch), but for the
-// lowest levels, which read two or three blocks a row (9 us: 50 MB at 5.6 TB/s).
+// lowest levels (6 to 9 us).
 constexpr int kCrSolveThreads = 256;
 template <int WP, bool FORWARD>
 __global__ void __launch_bounds__(kCrSolveThreads) stage2_cr_solve_kernel(const Stage2Grid g, const SubBox *boxes,
-                                                                          const Stage2Cr *tab, double *cr, double *rhs,
+                                                                          const Stage2Cr *tab, const double *stencil, double *cr, double *rhs,
                                                                           int level)
 {
     __shared__ double x[3][kStage2MaxBand], part[kCrSolveThreads / 64][kStage2MaxBand];
@@ -874,7 +888,14 @@ __global__ void __launch_bounds__(kCrSolveThreads) stage2_cr_solve_kernel(const 
     __syncthreads();
     constexpr int nb = WP * WP;
     double acc;
-    if (FORWARD) {
+    if (FORWARD && level == 0) {  // M = A D^-1, N = C D^-1 of the neighbours
+        acc = -bx.slot(stencil, i, r, 0) * cr_dot<WP>(bx.row(cr, i - 1), x[0], r, q);
+        if (up) acc -= bx.slot(stencil, i, r, 4) * cr_dot<WP>(bx.row(cr, i + 1), x[2], r, q);
+    } else if (level == 0) {  // P = D^-1 A, Q = D^-1 C
+        if (q == 0) x[1][r] -= bx.slot(stencil, i, r, 0) * x[0][r] + bx.slot(stencil, i, r, 4) * x[2][r];
+        __syncthreads();
+        acc = cr_dot<WP>(bx.row(cr, i), x[1], r, q);
+    } else if (FORWARD) {
         const double *M = bx.pair(cr, level, (int)blockIdx.x + 1);
         acc = -cr_dot<WP>(M, x[0], r, q);
         if (up) acc -= cr_dot<WP>(M + nb, x[2], r, q);
@@ -909,22 +930,26 @@ hipError_t launch_cyclic_reduction(const Stage2Grid &g, const SubBox *boxes, int
     const auto even = [&](int l, int parts) { return dim3((unsigned)(plan.max_L >> (l + 1)), n_boxes, parts); };
     hipError_t e = hipSuccess;
     for (int l = 0; l < levels && !plan.factored; ++l) {
-        hipLaunchKernelGGL((stage2_cr_eliminate_kernel<WP>), odd(l), dim3(kCrThreads), 0, s, boxes, plan.cr_tab,
-                           stencil, plan.factor, l);
+        const auto eliminate = l == 0 ? stage2_cr_eliminate_kernel<WP, true> : stage2_cr_eliminate_kernel<WP, false>;
+        hipLaunchKernelGGL(eliminate, odd(l), dim3(kCrThreads), 0, s, boxes, plan.cr_tab, stencil, plan.factor, l);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if (l + 1 == levels) break;
-        hipLaunchKernelGGL((stage2_cr_update_kernel<WP>), even(l, 3), dim3(kCrThreads), 0, s, boxes, plan.cr_tab,
-                           stencil, plan.factor, l);
+        if (l == 0)
+            hipLaunchKernelGGL((stage2_cr_first_update_kernel<WP>), even(0, 1), dim3(kCrThreads), 0, s, boxes,
+                               plan.cr_tab, stencil, plan.factor);
+        else
+            hipLaunchKernelGGL((stage2_cr_update_kernel<WP>), even(l, 3), dim3(kCrThreads), 0, s, boxes, plan.cr_tab,
+                               plan.factor, l);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     for (int l = 0; l + 1 < levels; ++l) {
         hipLaunchKernelGGL((stage2_cr_solve_kernel<WP, true>), even(l, 1), dim3(kCrSolveThreads), 0, s, g, boxes,
-                           plan.cr_tab, plan.factor, plan.rhs, l);
+                           plan.cr_tab, stencil, plan.factor, plan.rhs, l);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     for (int l = levels - 1; l >= 0; --l) {
         hipLaunchKernelGGL((stage2_cr_solve_kernel<WP, false>), odd(l), dim3(kCrSolveThreads), 0, s, g, boxes,
-                           plan.cr_tab, plan.factor, plan.rhs, l);
+                           plan.cr_tab, stencil, plan.factor, plan.rhs, l);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     return hipSuccess;
