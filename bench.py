@@ -73,12 +73,12 @@ FP32_PEAK_TFLOPS = 157.3
 
 
 def kernel_source_hash() -> str:
-    """sha256 over the path kernel's sources and build flags: HBM counters
+    """sha256 over the path kernels' sources and build flags: HBM counters
     taken for another version of the kernel are not reported."""
     import hashlib
     from paper_1512_02818_amd import build as B
     h = hashlib.sha256()
-    for name in ("path_kernel.hip", "pdd_internal.hpp"):
+    for name in ("path_kernel.hip", "path_walk.hpp", "group_kernel.hip", "pdd_internal.hpp"):
         with open(os.path.join(ROOT, "paper_1512_02818_amd", "csrc", name), "rb") as f:
             h.update(f.read())
     h.update(" ".join(B.FLAGS[:-1]).encode())  # the include path differs between machines
