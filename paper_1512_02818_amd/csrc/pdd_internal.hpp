@@ -353,8 +353,8 @@ constexpr int kStage2MaxLdsNodes = 136;
 hipError_t launch_stage2_boundary(const DevProblem<double> &P, const Stage2Grid &g, hipStream_t s);
 // The lines' multiquadric weights from their values; the values at a line's
 // ends are taken from u's boundary first. marks[q] (host memory that
-// the device can write): 1 where line q's system is singular (its weights are
-// zero then), else 0.
+// the device can write; zero before) is set to 1 where line q's system is
+// singular (its weights are zero then).
 hipError_t launch_stage2_weights(const Stage2Grid &g, const Stage2Line *lines, int32_t n_lines, const double *t,
                                  double *lam, double *matrices, int32_t *marks, hipStream_t s);
 // Interface lines: the multiquadric interpolants at the grid points of each

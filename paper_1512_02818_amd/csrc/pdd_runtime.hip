@@ -1808,28 +1808,38 @@ pdd_status pdd_stage2(pdd_problem *problem, const pdd_partition *part, const dou
     std::memcpy(h + off_boxes, boxes.data(), boxes.size() * sizeof(SubBox));
     std::memcpy(h + off_cr, cr_tab.data(), cr_tab.size() * sizeof(Stage2Cr));
     char *dv = static_cast<char *>(ctx->stage2.ptr);
-    HIP_TRY(hipMemcpyAsync(dv, h, table_bytes, hipMemcpyHostToDevice, s));
-    const Stage2Line *dv_lines = reinterpret_cast<const Stage2Line *>(dv + off_lines);
-    const double *dv_t = reinterpret_cast<const double *>(dv + off_t);
-    double *dv_lam = reinterpret_cast<double *>(dv + off_lam);
     int32_t *marks = reinterpret_cast<int32_t *>(h + table_bytes);
-    void *dv_marks = nullptr;
-    HIP_TRY(hipHostGetDevicePointer(&dv_marks, marks, 0));
-    HIP_TRY(launch_stage2_weights(g, dv_lines, (int32_t)lines.size(), dv_t, dv_lam,
-                                  reinterpret_cast<double *>(dv + off_weights), static_cast<int32_t *>(dv_marks), s));
-    HIP_TRY(hipEventRecord(ctx->staged, s));
-    ctx->any_staged = true;
-    HIP_TRY(launch_stage2_lines(g, dv_lines, (int32_t)lines.size(), dv_t, dv_lam, s));
-    Stage2Plan plan{};
-    plan.factored = factored;
-    plan.cr_tab = use_cr ? reinterpret_cast<const Stage2Cr *>(dv + off_cr) : nullptr;
-    plan.max_L = max_L;
-    plan.wp = (int32_t)wp;
-    plan.factor = static_cast<double *>(ctx->stage2_factor.ptr);
-    plan.lmul = plan.factor + unknowns * (kStage2MaxBand + 2);
-    plan.rhs = reinterpret_cast<double *>(dv + off_rhs);
-    HIP_TRY(launch_stage2_solve(problem->pd, g, reinterpret_cast<const SubBox *>(dv + off_boxes), (int32_t)boxes.size(),
-                                (uint32_t)max_unknowns, reinterpret_cast<double *>(dv + off_stencil), plan, s));
+    std::memset(marks, 0, lines.size() * sizeof(int32_t));
+    // the staging buffer is in use until the call's own wait at the end (an
+    // event behind the upload would hold the kernels up by 5 us)
+    auto enqueue = [&]() -> pdd_status {
+        HIP_TRY(hipMemcpyAsync(dv, h, table_bytes, hipMemcpyHostToDevice, s));
+        const Stage2Line *dv_lines = reinterpret_cast<const Stage2Line *>(dv + off_lines);
+        const double *dv_t = reinterpret_cast<const double *>(dv + off_t);
+        double *dv_lam = reinterpret_cast<double *>(dv + off_lam);
+        void *dv_marks = nullptr;
+        HIP_TRY(hipHostGetDevicePointer(&dv_marks, marks, 0));
+        HIP_TRY(launch_stage2_weights(g, dv_lines, (int32_t)lines.size(), dv_t, dv_lam,
+                                      reinterpret_cast<double *>(dv + off_weights), static_cast<int32_t *>(dv_marks),
+                                      s));
+        HIP_TRY(launch_stage2_lines(g, dv_lines, (int32_t)lines.size(), dv_t, dv_lam, s));
+        Stage2Plan plan{};
+        plan.factored = factored;
+        plan.cr_tab = use_cr ? reinterpret_cast<const Stage2Cr *>(dv + off_cr) : nullptr;
+        plan.max_L = max_L;
+        plan.wp = (int32_t)wp;
+        plan.factor = static_cast<double *>(ctx->stage2_factor.ptr);
+        plan.lmul = plan.factor + unknowns * (kStage2MaxBand + 2);
+        plan.rhs = reinterpret_cast<double *>(dv + off_rhs);
+        HIP_TRY(launch_stage2_solve(problem->pd, g, reinterpret_cast<const SubBox *>(dv + off_boxes),
+                                    (int32_t)boxes.size(), (uint32_t)max_unknowns,
+                                    reinterpret_cast<double *>(dv + off_stencil), plan, s));
+        return PDD_OK;
+    };
+    if ((st = enqueue())) {
+        (void)hipStreamSynchronize(s);
+        return st;
+    }
     ctx->stage2_key = key;
     HIP_TRY(hipEventRecord(ctx->done, s));
     ctx->any_done = true;

@@ -174,7 +174,8 @@ __device__ __forceinline__ double wave_max(double v)
 // the systems solved on the host and takes 0.45 ms (three lines of 8 points:
 // 0.20 ms either way).
 constexpr int kWeightsThreads = 1024;
-__device__ __forceinline__ void solve_weights(double *M, double *z, const double *t, double eps, int m, int32_t *mark)
+__device__ __forceinline__ void solve_weights(double *M, double *z, const double *first, const double *last,
+                                              const double *t, double eps, int m, int32_t *mark)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     constexpr int kWaves = kWeightsThreads / 64;
@@ -182,7 +183,7 @@ __device__ __forceinline__ void solve_weights(double *M, double *z, const double
     for (int r = wave; r < m; r += kWaves)
         for (int c = lane; c <= m; c += 64) {
             const double ee = eps * (t[r] - (c < m ? t[c] : 0.0));
-            M[r * ld + c] = c < m ? sqrt(1.0 + ee * ee) : z[r];
+            M[r * ld + c] = c < m ? sqrt(1.0 + ee * ee) : r == 0 ? *first : r == m - 1 ? *last : z[r];
         }
     __syncthreads();
     for (int c = 0; c < m; ++c) {
@@ -248,16 +249,13 @@ __global__ void __launch_bounds__(kWeightsThreads) stage2_weights_kernel(const S
     __shared__ double s_M[kStage2MaxLdsNodes * (kStage2MaxLdsNodes + 1)];
     const Stage2Line L = lines[blockIdx.x];
     double *z = lam + L.at;
-    if (threadIdx.x == 0) {
-        marks[blockIdx.x] = 0;
-        z[0] = g.u[L.d == 0 ? (size_t)L.k : (size_t)L.k * g.n0];
-        z[L.m - 1] = g.u[L.d == 0 ? (size_t)(g.n1 - 1) * g.n0 + L.k : (size_t)L.k * g.n0 + g.n0 - 1];
-    }
-    __syncthreads();
+    // the line's ends
+    const double *first = g.u + (L.d == 0 ? (size_t)L.k : (size_t)L.k * g.n0);
+    const double *last = g.u + (L.d == 0 ? (size_t)(g.n1 - 1) * g.n0 + L.k : (size_t)L.k * g.n0 + g.n0 - 1);
     if (L.m <= kStage2MaxLdsNodes)
-        solve_weights(s_M, z, t + L.at, L.eps, L.m, marks + blockIdx.x);
+        solve_weights(s_M, z, first, last, t + L.at, L.eps, L.m, marks + blockIdx.x);
     else
-        solve_weights(matrices + L.matrix, z, t + L.at, L.eps, L.m, marks + blockIdx.x);
+        solve_weights(matrices + L.matrix, z, first, last, t + L.at, L.eps, L.m, marks + blockIdx.x);
 }
 
 // One workgroup row per line (blockIdx.y); the points of the line strictly
@@ -852,72 +850,137 @@ __global__ void __launch_bounds__(kCrThreads) stage2_cr_update_kernel(const SubB
     }
 }
 
-// sum over k of B[r][k] x[k] for this thread's row (threads of wave q take the
-// columns from q WP / 4 on), B by column.
+// A row's substitution: 4 x kRow threads, thread r of quarter q takes the
+// columns of quarter q of each block it needs.
 template <int WP>
-__device__ __forceinline__ double cr_dot(const double *B, const double *x, int r, int q)
-{
-    double acc = 0.0;
-    if (r < WP)
-#pragma unroll
-        for (int k = 0; k < WP / 4; ++k) acc = madd(gload(B + (q * (WP / 4) + k) * WP + r), x[q * (WP / 4) + k], acc);
-    return acc;
-}
+struct CrSolve {
+    static constexpr int kRow = WP == 48 ? 64 : WP, kThreads = 4 * kRow, kPart = WP / 4;
+    double x[3][kRow], part[4][kRow];
 
-// Forward (FORWARD) and back substitution of the right sides at one level, a
-// workgroup per block row. Bound by latency (5 us a launch), but for the
-// lowest levels (6 to 9 us).
-constexpr int kCrSolveThreads = 256;
-template <int WP, bool FORWARD>
-__global__ void __launch_bounds__(kCrSolveThreads) stage2_cr_solve_kernel(const Stage2Grid g, const SubBox *boxes,
-                                                                          const Stage2Cr *tab, const double *stencil, double *cr, double *rhs,
-                                                                          int level)
-{
-    __shared__ double x[3][kStage2MaxBand], part[kCrSolveThreads / 64][kStage2MaxBand];
-    const CrBox<WP> bx(boxes, tab, blockIdx.y);
-    const int t = 1 << level, i = FORWARD ? 2 * t * ((int)blockIdx.x + 1) : t * (2 * (int)blockIdx.x + 1);
-    const int L = bx.b.L, w = bx.b.w;
-    if (i > L) return;  // whole workgroup
-    const int r = threadIdx.x & 63, q = threadIdx.x >> 6;
-    double *f = rhs + bx.b.first + (uint64_t)(i - 1) * w;
-    const bool lo = i - t >= 1, up = i + t <= L;
-    if (q < 3) {  // f of rows i - t, i and i + t
-        const bool there = r < w && (q == 1 || (q == 0 ? lo : up));
-        x[q][r] = there ? gload(f + (int64_t)(q - 1) * t * w + r) : 0.0;
+    // Quarter q of row r of a block (by column), and its product with x.
+    struct Piece {
+        double v[kPart];
+    };
+    __device__ static __forceinline__ Piece load(const double *B, int r, int q, bool there)
+    {
+        Piece p;
+#pragma unroll
+        for (int k = 0; k < kPart; ++k) p.v[k] = there && r < WP ? gload(B + (q * kPart + k) * WP + r) : 0.0;
+        return p;
     }
-    __syncthreads();
-    constexpr int nb = WP * WP;
-    double acc;
-    if (FORWARD && level == 0) {  // M = A D^-1, N = C D^-1 of the neighbours
-        acc = -bx.slot(stencil, i, r, 0) * cr_dot<WP>(bx.row(cr, i - 1), x[0], r, q);
-        if (up) acc -= bx.slot(stencil, i, r, 4) * cr_dot<WP>(bx.row(cr, i + 1), x[2], r, q);
-    } else if (level == 0) {  // P = D^-1 A, Q = D^-1 C
-        if (q == 0) x[1][r] -= bx.slot(stencil, i, r, 0) * x[0][r] + bx.slot(stencil, i, r, 4) * x[2][r];
-        __syncthreads();
-        acc = cr_dot<WP>(bx.row(cr, i), x[1], r, q);
-    } else if (FORWARD) {
-        const double *M = bx.pair(cr, level, (int)blockIdx.x + 1);
-        acc = -cr_dot<WP>(M, x[0], r, q);
-        if (up) acc -= cr_dot<WP>(M + nb, x[2], r, q);
-    } else {
-        const double *row = bx.row(cr, i);
-        acc = cr_dot<WP>(row, x[1], r, q);
-        if (lo) acc -= cr_dot<WP>(row + nb, x[0], r, q);
-        if (up) acc -= cr_dot<WP>(row + 2 * nb, x[2], r, q);
+    __device__ static __forceinline__ double dot(const Piece &p, const double *y, int q)
+    {
+        double acc = 0.0;
+#pragma unroll
+        for (int k = 0; k < kPart; ++k) acc = madd(p.v[k], y[q * kPart + k], acc);
+        return acc;
     }
-    part[q][r] = acc;
-    __syncthreads();
-    if (q == 0 && r < w) {
-        double v = ((part[0][r] + part[1][r]) + part[2][r]) + part[3][r];
+
+    // Forward (FORWARD) or back substitution of block row i at a level; every
+    // thread of the workgroup calls it, those of a team without a row with
+    // `active` false. The blocks are on their way before the right sides are
+    // waited for.
+    template <bool FORWARD>
+    __device__ __forceinline__ void row(const Stage2Grid &g, const CrBox<WP> &bx, const double *stencil, double *cr,
+                                        double *rhs, int level, int i, bool active, int r, int q)
+    {
+        const int t = 1 << level, L = bx.b.L, w = bx.b.w;
+        constexpr int nb = WP * WP;
+        const bool lo = active && i - t >= 1, up = active && i + t <= L;
+        double *f = rhs + bx.b.first + (int64_t)(i - 1) * w;
+        Piece b0, b1, b2;
         if (FORWARD) {
-            f[r] = x[1][r] + v;
+            // M, N; at level 0 A D^-1, C D^-1 of the neighbours
+            const double *M = active && level > 0 ? bx.pair(cr, level, i >> (level + 1)) : nullptr;
+            b0 = load(level > 0 ? M : bx.row(cr, i - 1), r, q, active);
+            b2 = load(level > 0 ? M + nb : bx.row(cr, i + 1), r, q, up);
         } else {
-            f[r] = v;
-            int gi, gj;
-            stage2_point(bx.b, (uint64_t)(i - 1) * w + r, gi, gj);
-            g.u[(size_t)gj * g.n0 + gi] = v;
+            // D^-1, P, Q; at level 0 P = D^-1 A, Q = D^-1 C
+            const double *D = bx.row(cr, i);
+            b1 = load(D, r, q, active);
+            b0 = load(D + nb, r, q, lo && level > 0);
+            b2 = load(D + 2 * nb, r, q, up && level > 0);
+        }
+        if (q < 3) {  // f of rows i - t, i and i + t
+            const bool there = r < w && (q == 1 ? active : q == 0 ? lo : up);
+            x[q][r] = there ? gload(f + (int64_t)(q - 1) * t * w + r) : 0.0;
+        }
+        const double sa = level == 0 && active ? bx.slot(stencil, i, r, 0) : 1.0;
+        const double sc = level == 0 && active ? bx.slot(stencil, i, r, 4) : 1.0;
+        __syncthreads();
+        double acc;
+        if (FORWARD) {
+            acc = -sa * dot(b0, x[0], q) - sc * dot(b2, x[2], q);
+        } else if (level == 0) {
+            if (q == 0) x[1][r] -= sa * x[0][r] + sc * x[2][r];
+            __syncthreads();
+            acc = dot(b1, x[1], q);
+        } else {
+            acc = dot(b1, x[1], q) - dot(b0, x[0], q) - dot(b2, x[2], q);
+        }
+        part[q][r] = acc;
+        __syncthreads();
+        if (q == 0 && r < w && active) {
+            double v = ((part[0][r] + part[1][r]) + part[2][r]) + part[3][r];
+            if (FORWARD) {
+                gstore(f + r, x[1][r] + v);
+            } else {
+                gstore(f + r, v);
+                int gi, gj;
+                stage2_point(bx.b, (uint64_t)(i - 1) * w + r, gi, gj);
+                g.u[(size_t)gj * g.n0 + gi] = v;
+            }
         }
     }
+};
+
+// Substitution at one level, a workgroup per block row. Bound by latency (4 to
+// 5 us a launch), but for the lowest levels (6 to 9 us).
+template <int WP, bool FORWARD>
+__global__ void __launch_bounds__(CrSolve<WP>::kThreads) stage2_cr_solve_kernel(const Stage2Grid g, const SubBox *boxes,
+                                                                                const Stage2Cr *tab,
+                                                                                const double *stencil, double *cr,
+                                                                                double *rhs, int level)
+{
+    __shared__ CrSolve<WP> s;
+    const CrBox<WP> bx(boxes, tab, blockIdx.y);
+    const int t = 1 << level, i = FORWARD ? 2 * t * ((int)blockIdx.x + 1) : t * (2 * (int)blockIdx.x + 1);
+    if (i > bx.b.L) return;  // whole workgroup
+    s.template row<FORWARD>(g, bx, stencil, cr, rhs, level, i, true, threadIdx.x % CrSolve<WP>::kRow,
+                            threadIdx.x / CrSolve<WP>::kRow);
+}
+
+// All levels from `first` on, forward and back, a workgroup per subdomain: for
+// the levels of few rows a launch each costs more than one CU's bandwidth.
+// Kept blocks, four strips at 65^2, 129^2, 257^2: 125, 135 and 165 us a call
+// with a launch for every level, 106, 125 and 153 us so.
+template <int WP>
+constexpr int kTopRows = WP == 16 ? 64 : WP == 32 ? 32 : 8;
+constexpr int kTopThreads = 1024;
+template <int WP>
+__global__ void __launch_bounds__(kTopThreads) stage2_cr_top_kernel(const Stage2Grid g, const SubBox *boxes,
+                                                                    const Stage2Cr *tab, const double *stencil,
+                                                                    double *cr, double *rhs, int first)
+{
+    constexpr int kTeam = CrSolve<WP>::kThreads, kTeams = kTopThreads / kTeam;
+    __shared__ CrSolve<WP> teams[kTeams];
+    const CrBox<WP> bx(boxes, tab, blockIdx.x);
+    const int L = bx.b.L, team = threadIdx.x / kTeam, r = threadIdx.x % CrSolve<WP>::kRow;
+    const int q = threadIdx.x % kTeam / CrSolve<WP>::kRow;
+    CrSolve<WP> &s = teams[team];
+    int l = first;
+    for (; (2 << l) <= L; ++l)
+        for (int m = 0; m < L >> (l + 1); m += kTeams) {
+            const int i = (m + team + 1) << (l + 1);
+            s.template row<true>(g, bx, stencil, cr, rhs, l, i, i <= L, r, q);
+            __syncthreads();
+        }
+    for (; l >= first; --l)
+        for (int m = 0; (2 * m + 1) << l <= L; m += kTeams) {
+            const int i = (2 * (m + team) + 1) << l;
+            s.template row<false>(g, bx, stencil, cr, rhs, l, i, i <= L, r, q);
+            __syncthreads();
+        }
 }
 
 template <int WP>
@@ -942,13 +1005,18 @@ hipError_t launch_cyclic_reduction(const Stage2Grid &g, const SubBox *boxes, int
                                plan.factor, l);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    for (int l = 0; l + 1 < levels; ++l) {
-        hipLaunchKernelGGL((stage2_cr_solve_kernel<WP, true>), even(l, 1), dim3(kCrSolveThreads), 0, s, g, boxes,
+    int top = 0;
+    while ((plan.max_L >> top) >= kTopRows<WP>) ++top;
+    for (int l = 0; l < top; ++l) {
+        hipLaunchKernelGGL((stage2_cr_solve_kernel<WP, true>), even(l, 1), dim3(CrSolve<WP>::kThreads), 0, s, g, boxes,
                            plan.cr_tab, stencil, plan.factor, plan.rhs, l);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    for (int l = levels - 1; l >= 0; --l) {
-        hipLaunchKernelGGL((stage2_cr_solve_kernel<WP, false>), odd(l), dim3(kCrSolveThreads), 0, s, g, boxes,
+    hipLaunchKernelGGL(stage2_cr_top_kernel<WP>, dim3(n_boxes), dim3(kTopThreads), 0, s, g, boxes, plan.cr_tab, stencil,
+                       plan.factor, plan.rhs, top);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    for (int l = top - 1; l >= 0; --l) {
+        hipLaunchKernelGGL((stage2_cr_solve_kernel<WP, false>), odd(l), dim3(CrSolve<WP>::kThreads), 0, s, g, boxes,
                            plan.cr_tab, stencil, plan.factor, plan.rhs, l);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
