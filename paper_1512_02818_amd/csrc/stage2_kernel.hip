@@ -610,8 +610,8 @@ __global__ void __launch_bounds__(kStage2SubstThreads) stage2_subst_kernel(const
 // direct solve, or the LU is the farther off). The LU's chain of w L dependent
 // pivots, one workgroup a subdomain, becomes 1 + log2 L levels whose rows are
 // independent. Four strips of 63 x 255 unknowns: 39.9 ms with the LU and the
-// solutions for unit boundary values that it was kept as, 0.45 ms now; with
-// the factors kept 0.26 and 0.19 ms. What bounds a level is the inversion
+// solutions for unit boundary values that it was kept as, 0.44 ms now; with
+// the factors kept 0.26 and 0.13 ms. What bounds a level is the inversion
 // (24 us: 64 dependent pivots) and the products on the FP64 matrix cores
 // (9 us; 37 us where the rows are several per CU). Blocks are padded by the
 // identity to WP (the widest subdomain's w, to a multiple of 16) and kept by
@@ -952,10 +952,11 @@ __global__ void __launch_bounds__(CrSolve<WP>::kThreads) stage2_cr_solve_kernel(
 
 // All levels from `first` on, forward and back, a workgroup per subdomain: for
 // the levels of few rows a launch each costs more than one CU's bandwidth.
-// Kept blocks, four strips at 65^2, 129^2, 257^2: 125, 135 and 165 us a call
-// with a launch for every level, 106, 125 and 153 us so.
+// Kept blocks, four strips, calls back to back: 129^2 (blocks of 32) 100 us
+// with a launch for every level, 92 us from 8 rows on, 89 from 16, 96 from 32;
+// 65^2 (blocks of 16) 91 us, and 75 with all levels here.
 template <int WP>
-constexpr int kTopRows = WP == 16 ? 64 : WP == 32 ? 32 : 8;
+constexpr int kTopRows = WP == 16 ? 64 : WP == 32 ? 16 : 8;
 constexpr int kTopThreads = 1024;
 template <int WP>
 __global__ void __launch_bounds__(kTopThreads) stage2_cr_top_kernel(const Stage2Grid g, const SubBox *boxes,
