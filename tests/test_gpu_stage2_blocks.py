@@ -45,6 +45,23 @@ def test_block_edges(ctx, axis, w1, w2, rows):
     assert got[0].tobytes() == got[1].tobytes()
 
 
+def test_unlike_boxes(ctx):
+    """Interfaces on both axes: 10 to 200 points a side, one subdomain with
+    fewer block rows than the others' upper levels leave out."""
+    from oracle import stage2 as S2
+    pd = dict(W.unit_square_problem(seed=0), b0=[3.0, -2.0])
+    n = (10 + 60 + 3, 30 + 200 + 3)
+    cuts = [[11 / (n[0] - 1)], [31 / (n[1] - 1)]]
+    nodes = np.array([[cuts[0][0], y] for y in (0.05, 0.4, 0.8)] + [[x, cuts[1][0]] for x in (0.05, 0.4, 0.8)])
+    vals = W.manufactured_u(pd, nodes) + np.random.default_rng(1).normal(scale=0.01, size=len(nodes))
+    prob = pdd.Problem(ctx, pd)
+    got = [pdd.stage2(prob, n, cuts, nodes, vals, 3.0).cpu().numpy() for _ in range(2)]
+    prob.close()
+    ref = S2.stage2(pd, n, cuts, nodes, vals, 3.0)
+    assert np.max(np.abs(got[0] - ref) / np.maximum(1.0, np.abs(ref))) <= 1e-10
+    assert got[0].tobytes() == got[1].tobytes()
+
+
 @pytest.mark.parametrize("count", [0, 1, 62, 63, 134, 135, 300])
 def test_weights(ctx, count):
     from oracle import stage2 as S2
