@@ -80,7 +80,11 @@ extern "C" pdd_status pdd_grid_residual(pdd_problem *problem, const pdd_grid *u,
     if ((uint64_t)u->n[0] * u->n[1] * (D == 3 ? (uint64_t)u->n[2] : 1) >= (1ull << 40))
         return fail(PDD_E_INVALID, "grid too large");
     HIP_TRY(hipSetDevice(problem->ctx->device));
-    const hipError_t e = pdd::launch_grid_residual(problem->pd, problem->desc.sigma, u, resid,
+    // the source is evaluated at the grid's points, which may lie far outside
+    // the problem's box: their arguments choose the trig functions
+    pdd::DevProblem<double> pd = problem->pd;
+    pd.big_trig = !(pdd::trig_revolutions(problem->desc, u->lo, u->hi) <= pdd::kFp64TrigRevolutions);
+    const hipError_t e = pdd::launch_grid_residual(pd, problem->desc.sigma, u, resid,
                                                    static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return fail(PDD_E_HIP, "grid residual launch: %s", hipGetErrorString(e));
     return PDD_OK;

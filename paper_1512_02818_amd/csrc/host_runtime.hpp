@@ -56,6 +56,9 @@ struct HostItem {
     std::vector<uint64_t> starts;  // item-relative prefix (non-uniform counts)
 };
 
+// Largest |k_d x_d + phase_d| / (2 pi) of the problem's trig terms over the box
+// [lo, hi].
+double trig_revolutions(const pdd_problem_desc &d, const double *lo, const double *hi);
 // Checks an item's arguments against its problem (nothing is enqueued).
 pdd_status validate_item(HostItem &it);
 // Key of the launch-shape table: precision, dimension, estimator (kEst*) and

@@ -262,19 +262,15 @@ pdd_status check_desc(const pdd_problem_desc *d)
     return PDD_OK;
 }
 
-// Largest |k_d x_d + phase_d| / (2 pi) of the trig terms over the bounding
-// box of the domain (a corner maximises |k_d x_d|).
-double trig_revolutions(const pdd_problem_desc &d)
+// trig_revolutions over the bounding box of the problem's domain.
+double domain_revolutions(const pdd_problem_desc &d)
 {
-    double mx = 0.0;
-    for (int m = 0; m < d.n_trig; ++m)
-        for (int i = 0; i < d.dim; ++i) {
-            const double lo = d.domain == PDD_DOMAIN_BOX ? d.lo[i] : d.center[i] - d.radius;
-            const double hi = d.domain == PDD_DOMAIN_BOX ? d.hi[i] : d.center[i] + d.radius;
-            const double k = d.trig[m].k[i], ph = d.trig[m].phase[i];
-            mx = std::max(mx, std::max(std::fabs(k * lo + ph), std::fabs(k * hi + ph)));
-        }
-    return mx * 0.15915494309189533577;
+    double lo[3] = {}, hi[3] = {};
+    for (int i = 0; i < d.dim; ++i) {
+        lo[i] = d.domain == PDD_DOMAIN_BOX ? d.lo[i] : d.center[i] - d.radius;
+        hi[i] = d.domain == PDD_DOMAIN_BOX ? d.hi[i] : d.center[i] + d.radius;
+    }
+    return trig_revolutions(d, lo, hi);
 }
 
 bool strictly_inside(const pdd_problem_desc &d, const double *x)
@@ -333,6 +329,18 @@ GridView<T> make_view(const pdd_grid *g, int dim)
 }
 
 }  // namespace
+
+// (a corner of the box maximises |k_d x_d + phase_d|)
+double pdd::trig_revolutions(const pdd_problem_desc &d, const double *lo, const double *hi)
+{
+    double mx = 0.0;
+    for (int m = 0; m < d.n_trig; ++m)
+        for (int i = 0; i < d.dim; ++i) {
+            const double k = d.trig[m].k[i], ph = d.trig[m].phase[i];
+            mx = std::max(mx, std::max(std::fabs(k * lo[i] + ph), std::fabs(k * hi[i] + ph)));
+        }
+    return mx * 0.15915494309189533577;
+}
 
 int pdd::occupancy(pdd_ctx *ctx, const void *fn, int block, bool cache)
 {
@@ -1113,7 +1121,7 @@ pdd_status pdd_create_problem(pdd_ctx *ctx, const pdd_problem_desc *desc, pdd_pr
     p->serial = next_problem_serial();
     p->ctx = ctx;
     p->desc = *desc;
-    p->trig_rev_max = trig_revolutions(*desc);
+    p->trig_rev_max = domain_revolutions(*desc);
     if ((st = fill_problem(*desc, p->pf, true)) || (st = fill_problem(*desc, p->pd, false))) {
         delete p;
         return st;
@@ -1194,7 +1202,7 @@ pdd_status pdd_create_problem_tabulated(pdd_ctx *ctx, const pdd_problem_desc *de
     p->serial = next_problem_serial();
     p->ctx = ctx;
     p->desc = *desc;
-    p->trig_rev_max = trig_revolutions(*desc);
+    p->trig_rev_max = domain_revolutions(*desc);
     if ((st = fill_problem(*desc, p->pf, true)) || (st = fill_problem(*desc, p->pd, false))) {
         delete p;
         return st;
