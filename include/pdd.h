@@ -453,15 +453,22 @@ typedef struct {
  * Every subdomain (the grid box between consecutive interfaces) is then solved
  * for (1/2) sigma^2 Lap v + b.grad v + c v = f with the values on its
  * boundary, by second-order finite differences on the grid (central second
- * and first differences, b, c, f of the problem in FP64) and block
- * cyclic reduction without pivoting (block rows along the longer side, FP64).
- * The eliminated blocks depend on the operator (sigma, b, c), the grid and
- * the interfaces only, so the context keeps those of its last call: a call
- * with the same operator, grid, interfaces and problem (another set of nodal
- * values) then only substitutes its right side. Where the blocks would take
- * more than 8 GiB or cannot be allocated, or with PDD_STAGE2_SUBSTITUTE=1 in the environment, a
- * banded LU, one workgroup per subdomain, takes their place. The result
- * equals a direct solve to rounding (the same in a fresh context and in a
+ * and first differences, b, c, f of the problem in FP64), without pivoting.
+ * Where |b_d| dx_d <= sigma^2 and c <= 0 in the whole box (tabulated b or c: at
+ * every interior point), by block cyclic reduction (block rows along the longer
+ * side, FP64), else by a banded LU, one workgroup per subdomain. Both
+ * eliminate matrices that depend on the operator (sigma, b, c), the grid and
+ * the interfaces only, so the context keeps the factors of its last call: a
+ * call with the same operator, grid, interfaces and problem (another set of
+ * nodal values) then only substitutes its right side (cyclic reduction) or adds
+ * up kept response columns, each subdomain's solution for f and for a unit
+ * value at each row next to its boundary (LU; at most 2 GiB in all, else it
+ * substitutes too). LU also takes the place of the cyclic reduction where that
+ * one's blocks would take more than 8 GiB or cannot be allocated, and with
+ * PDD_STAGE2_SUBSTITUTE=1 in the environment, which makes every call
+ * substitute. The result equals a direct solve of the same kind to rounding
+ * (no pivoting: the error grows with |b| dx / sigma^2 and near a resonance of a
+ * positive c, as that of banded LU does) (the same in a fresh context and in a
  * kept one, bit for bit). `nodes` (host, n_nodes x 2) are the interface nodes
  * and `values` (host) their nodal values; a node may lie on several lines.
  * Synchronous; u is complete when the call returns. Errors: PDD_E_INVALID for

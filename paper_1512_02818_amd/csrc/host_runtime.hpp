@@ -139,11 +139,17 @@ struct pdd_ctx {
     pdd::DeviceBuffer nodes, starts, acc, rec, partials, gather, cells;
     pdd::DeviceBuffer tail;    // walking paths handed over between path kernels of a launch
     pdd::DeviceBuffer stage2;  // second stage: tables and stencils
-    // factors of the last second stage's subdomain matrices, and what they
-    // factor (the operator, the grid, the interfaces, and how): a call with the
-    // same ones only solves for its right sides
+    // factors of the last second stage's subdomain matrices, what they factor
+    // (the operator, the grid, the interfaces) and how (blocks of the cyclic
+    // reduction, or LU), and whether the cyclic reduction is for these matrices:
+    // a call with the same ones only solves for its right sides
     pdd::DeviceBuffer stage2_factor;
     std::vector<double> stage2_key;
+    bool stage2_blocks = false, stage2_dominant = false;
+    // with LU factors, the subdomains' response columns to their boundary values
+    // (and to f), for the key and the problem
+    pdd::DeviceBuffer stage2_resp;
+    std::vector<double> stage2_resp_key;
     void *stage = nullptr;
     size_t stage_cap = 0;
     void *readback = nullptr;  // pinned host copy of pilot statistics

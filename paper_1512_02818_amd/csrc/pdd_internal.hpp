@@ -368,25 +368,50 @@ hipError_t launch_stage2_lines(const Stage2Grid &g, const Stage2Line *lines, int
 struct Stage2Cr {
     uint64_t at, mn;
 };
+// Response of a subdomain's interior to its boundary values: the rows next
+// to the box's boundary (nb of them, at rb[rb_at ..]) and, at out_at in the
+// response buffer, nb + 1 columns of n values (column q < nb: the solution
+// for a unit right side at row rb[rb_at + q]; column nb: the solution for the
+// source f with zero boundary values).
+struct Stage2Resp {
+    uint64_t rb_at, out_at;
+    int32_t nb, pad;
+};
+constexpr int kStage2MaxBoundaryRows = 4096;
 // What launch_stage2_solve is to do after the stencils: factor (unless
 // `factored`: factor, and lmul, already hold the factors of these subdomains'
-// matrices) and solve, by block cyclic reduction (cr_tab: one per subdomain;
-// max_L the largest L; wp the largest w, rounded up to a multiple of 16) or, with cr_tab null, by banded LU (factor: unknowns x
-// (kStage2MaxBand + 2) doubles; lmul: unknowns x kStage2MaxBand).
+// matrices) and solve.
 struct Stage2Plan {
     bool factored;
-    const Stage2Cr *cr_tab;  // device, or null
+    // block cyclic reduction: one entry per subdomain (device), the largest L,
+    // the largest w rounded up to a multiple of 16
+    const Stage2Cr *cr_tab;
     int32_t max_L, wp;
+    // or, with cr_tab null, banded LU: factor has unknowns x (kStage2MaxBand +
+    // 2) doubles, lmul unknowns x kStage2MaxBand; then either the right side is
+    // substituted (resp_tab null), or f's response column and the boundary
+    // values' are added up (the columns computed first unless `resp_ready`)
     double *factor, *lmul;
-    double *rhs;             // unknowns doubles
+    const Stage2Resp *resp_tab;  // device, one per subdomain
+    const uint32_t *rb;          // device rows next to the boundary
+    double *resp;                // device response columns
+    int32_t max_cols;            // largest nb + 1
+    bool resp_ready;
+    double *rhs;                 // launch_stage2_stencils' (in parts for the response columns)
 };
 // Finite-difference stencils of every subdomain's unknowns (6 doubles per
 // unknown: slow-1, fast-1, centre, fast+1, slow+1 coefficients and the right
-// side with the boundary values moved over), then the subdomains' solutions by
-// the plan, written into u.
-hipError_t launch_stage2_solve(const DevProblem<double> &P, const Stage2Grid &g, const SubBox *boxes,
-                               int32_t n_boxes, uint32_t max_unknowns, double *stencil, const Stage2Plan &plan,
-                               hipStream_t s);
+// side with the boundary values moved over), and in rhs the right side again or,
+// with `parts`, two doubles per unknown: the source f alone and the boundary
+// values' part. *not_dominant (memory that the device can write; zero before;
+// may be null) is set to 1 where a neighbour's coefficient is negative or c
+// positive at some unknown.
+hipError_t launch_stage2_stencils(const DevProblem<double> &P, const Stage2Grid &g, const SubBox *boxes,
+                                  int32_t n_boxes, uint32_t max_unknowns, double *stencil, double *rhs, bool parts,
+                                  int32_t *not_dominant, hipStream_t s);
+// The subdomains' solutions by the plan, written into u.
+hipError_t launch_stage2_solve(const Stage2Grid &g, const SubBox *boxes, int32_t n_boxes, uint32_t max_unknowns,
+                               const double *stencil, const Stage2Plan &plan, hipStream_t s);
 hipError_t launch_finalize(const FinalizeArgs &a, hipStream_t s);
 hipError_t launch_zero(void *ptr, uint64_t bytes, hipStream_t s);
 // Starting sums of every group node: zero, or the statistics already in the

@@ -464,6 +464,27 @@ pdd_status pdd::validate_item(HostItem &it)
 
 namespace {
 
+// Whether |b_d| dx_d <= sigma^2 and c <= 0 for the analytic drift and killing
+// rate everywhere in the problem's 2D box: its five-point matrices then have
+// coefficients of one sign off the diagonal and are diagonally dominant.
+bool dominant_over_box(const pdd_problem_desc &d, double dx0, double dx1)
+{
+    const double dx[2] = {dx0, dx1};
+    double near2 = 0.0, far2 = 0.0;  // smallest and largest |x|^2
+    for (int i = 0; i < 2; ++i) {
+        double most = 0.0;  // |b_i| is largest at a corner
+        for (int corner = 0; corner < 4; ++corner) {
+            const double x[2] = {corner & 1 ? d.hi[0] : d.lo[0], corner & 2 ? d.hi[1] : d.lo[1]};
+            most = std::max(most, std::fabs(d.b0[i] + d.B[i][0] * x[0] + d.B[i][1] * x[1]));
+        }
+        if (!(most * dx[i] <= d.sigma * d.sigma)) return false;
+        const double nearest = std::max(0.0, std::max(d.lo[i], -d.hi[i])), farthest = std::max(-d.lo[i], d.hi[i]);
+        near2 += nearest * nearest;
+        far2 += farthest * farthest;
+    }
+    return d.c_a + d.c_b * (d.c_b > 0.0 ? far2 : near2) <= 0.0;
+}
+
 pdd_status check_tuning(const pdd_tuning &tune)
 {
     if (tune.block != 64 && tune.block != 128 && tune.block != 256)
@@ -1096,7 +1117,7 @@ void pdd_shutdown(pdd_ctx *ctx)
     if (ctx->any_done) (void)hipEventSynchronize(ctx->done);
     if (ctx->any_staged) (void)hipEventSynchronize(ctx->staged);
     for (DeviceBuffer *b : {&ctx->nodes, &ctx->starts, &ctx->tail, &ctx->acc, &ctx->rec, &ctx->partials,
-                            &ctx->gather, &ctx->cells, &ctx->stage2, &ctx->stage2_factor})
+                            &ctx->gather, &ctx->cells, &ctx->stage2, &ctx->stage2_factor, &ctx->stage2_resp})
         if (b->ptr) (void)hipFree(b->ptr);
     if (ctx->stage) (void)hipHostFree(ctx->stage);
     if (ctx->readback) (void)hipHostFree(ctx->readback);
@@ -1749,10 +1770,24 @@ pdd_status pdd_stage2(pdd_problem *problem, const pdd_partition *part, const dou
             lines.push_back(L);
             line_pos.push_back(cut_pos[a][q]);
         }
-    // blocks of the cyclic reduction, up to 8 GiB (2.3 million unknowns) and
-    // where the device has them; else banded LU (as every call with
-    // PDD_STAGE2_SUBSTITUTE=1 in the environment, which the tests use to check
-    // the two ways against each other)
+    // the subdomain matrices depend on the operator (sigma, b, c), the grid
+    // and the interfaces: factored already when the last call had the same
+    std::vector<double> key = {(double)d.dim, d.lo[0], d.lo[1], d.hi[0], d.hi[1], d.sigma, d.b0[0], d.b0[1],
+                               d.B[0][0], d.B[0][1], d.B[1][0], d.B[1][1], d.c_a, d.c_b,
+                               (problem->pd.tab & 15u) ? (double)problem->serial : -1.0, (double)n[0], (double)n[1]};
+    for (int a = 0; a < 2; ++a) {
+        key.push_back((double)cut_pos[a].size());
+        key.insert(key.end(), cut_pos[a].begin(), cut_pos[a].end());
+    }
+    const bool same_matrices = ctx->stage2_key == key;
+    if (!same_matrices) ctx->stage2_key.clear();
+    // the matrices that the cyclic reduction is for: of a problem with analytic b
+    // and c by their largest values over the box, else (below) by every unknown's
+    // coefficients
+    const bool dominance_known = same_matrices || !(problem->pd.tab & 15u);
+    bool dominant = same_matrices ? ctx->stage2_dominant : dominance_known && dominant_over_box(d, g.dx0, g.dx1);
+    // blocks of the cyclic reduction, which is taken up to 8 GiB (2.3 million
+    // unknowns)
     std::vector<Stage2Cr> cr_tab(boxes.size());
     uint64_t cr_values = 0;
     int32_t max_L = 0, max_w = 0;
@@ -1766,89 +1801,150 @@ pdd_status pdd_stage2(pdd_problem *problem, const pdd_partition *part, const dou
         cr_tab[q].mn = cr_values + rows * 3 * wp * wp;
         cr_values += (rows * 3 + pairs * 4) * wp * wp;
     }
-    const char *force_subst = std::getenv("PDD_STAGE2_SUBSTITUTE");
-    bool use_cr = cr_values * sizeof(double) <= (8ull << 30) && !(force_subst && force_subst[0] == '1');
+    const size_t cr_bytes = cr_values * sizeof(double), lu_bytes = unknowns * (2 * kStage2MaxBand + 2) * sizeof(double);
+    const bool cr_fits = cr_bytes <= (8ull << 30);
+    // where LU may be taken: the rows of every subdomain next to its boundary, and
+    // the layout of its response columns (nb + 1 columns of its unknowns)
+    const bool may_use_lu = !dominant || !cr_fits;
+    std::vector<Stage2Resp> resp_tab(boxes.size());
+    std::vector<uint32_t> rb;
+    uint64_t resp_values = 0;
+    int32_t max_cols = 0;
+    bool few_rows = true;
+    for (size_t q = 0; q < boxes.size() && may_use_lu; ++q) {
+        const SubBox &bx = boxes[q];
+        const uint32_t w = (uint32_t)bx.w, last = (uint32_t)bx.L - 1;
+        resp_tab[q].rb_at = rb.size();
+        for (uint32_t row = 0; row <= last; ++row)
+            for (uint32_t f = 0; f < w; f = row == 0 || row == last || f + 1 == w ? f + 1 : w - 1)
+                rb.push_back(row * w + f);
+        resp_tab[q].nb = (int32_t)(rb.size() - resp_tab[q].rb_at);
+        resp_tab[q].out_at = resp_values;
+        resp_values += (uint64_t)(resp_tab[q].nb + 1) * w * bx.L;
+        max_cols = std::max(max_cols, resp_tab[q].nb + 1);
+        few_rows = few_rows && resp_tab[q].nb <= kStage2MaxBoundaryRows;
+    }
     // device tables: lines | t | values, then weights | boxes | blocks' places |
-    // stencils | right sides | large lines' matrices; the lines' marks stay in the
-    // staging buffer
+    // response layout | boundary rows | stencils | right sides | large lines'
+    // matrices; the lines' marks, and one for the operator, stay in the staging
+    // buffer
     const size_t off_lines = 0;
     const size_t off_t = align_up(off_lines + lines.size() * sizeof(Stage2Line), 256);
     const size_t off_lam = align_up(off_t + t_all.size() * sizeof(double), 256);
     const size_t off_boxes = align_up(off_lam + z_all.size() * sizeof(double), 256);
     const size_t off_cr = align_up(off_boxes + boxes.size() * sizeof(SubBox), 256);
-    const size_t table_bytes = align_up(off_cr + cr_tab.size() * sizeof(Stage2Cr), 256);
+    const size_t off_resp = align_up(off_cr + cr_tab.size() * sizeof(Stage2Cr), 256);
+    const size_t off_rb = align_up(off_resp + resp_tab.size() * sizeof(Stage2Resp), 256);
+    const size_t table_bytes = align_up(off_rb + rb.size() * sizeof(uint32_t), 256);
     const size_t off_stencil = table_bytes;
     const size_t off_rhs = align_up(off_stencil + unknowns * 6 * sizeof(double), 256);
-    const size_t off_weights = align_up(off_rhs + unknowns * sizeof(double), 256);
+    const size_t off_weights = align_up(off_rhs + unknowns * 2 * sizeof(double), 256);
     const size_t bytes = off_weights + weights_values * sizeof(double);
     if ((st = ensure(ctx, ctx->stage2, bytes))) return st;
-    // the subdomain matrices depend on the operator (sigma, b, c), the grid
-    // and the interfaces: factored already when the last call had the same
-    std::vector<double> key = {(double)d.dim, d.lo[0], d.lo[1], d.hi[0], d.hi[1], d.sigma, d.b0[0], d.b0[1],
-                               d.B[0][0], d.B[0][1], d.B[1][0], d.B[1][1], d.c_a, d.c_b,
-                               (problem->pd.tab & 15u) ? (double)problem->serial : -1.0, (double)n[0], (double)n[1],
-                               use_cr ? 1.0 : 0.0};
-    const size_t use_cr_at = key.size() - 1;
-    for (int a = 0; a < 2; ++a) {
-        key.push_back((double)cut_pos[a].size());
-        key.insert(key.end(), cut_pos[a].begin(), cut_pos[a].end());
-    }
-    const size_t lu_bytes = unknowns * (2 * kStage2MaxBand + 2) * sizeof(double);
-    const size_t factor_bytes = use_cr ? cr_values * sizeof(double) : lu_bytes;
-    const bool factored =
-        ctx->stage2_key == key && ctx->stage2_factor.ptr && ctx->stage2_factor.cap >= factor_bytes;
-    if (!factored) {
-        ctx->stage2_key.clear();
-        st = ensure(ctx, ctx->stage2_factor, factor_bytes);
-        if (st == PDD_E_NOMEM && use_cr) {
-            (void)hipGetLastError();
-            use_cr = false;
-            key[use_cr_at] = 0.0;
-            st = ensure(ctx, ctx->stage2_factor, lu_bytes);
-        }
-        if (st) return st;
-    }
-    if ((st = ensure_stage(ctx, table_bytes + lines.size() * sizeof(int32_t)))) return st;
+    if ((st = ensure_stage(ctx, table_bytes + (lines.size() + 1) * sizeof(int32_t)))) return st;
     char *h = static_cast<char *>(ctx->stage);
     std::memcpy(h + off_lines, lines.data(), lines.size() * sizeof(Stage2Line));
     std::memcpy(h + off_t, t_all.data(), t_all.size() * sizeof(double));
     std::memcpy(h + off_lam, z_all.data(), z_all.size() * sizeof(double));
     std::memcpy(h + off_boxes, boxes.data(), boxes.size() * sizeof(SubBox));
     std::memcpy(h + off_cr, cr_tab.data(), cr_tab.size() * sizeof(Stage2Cr));
+    std::memcpy(h + off_resp, resp_tab.data(), resp_tab.size() * sizeof(Stage2Resp));
+    std::memcpy(h + off_rb, rb.data(), rb.size() * sizeof(uint32_t));
     char *dv = static_cast<char *>(ctx->stage2.ptr);
     int32_t *marks = reinterpret_cast<int32_t *>(h + table_bytes);
-    std::memset(marks, 0, lines.size() * sizeof(int32_t));
+    std::memset(marks, 0, (lines.size() + 1) * sizeof(int32_t));
     // the staging buffer is in use until the call's own wait at the end (an
     // event behind the upload would hold the kernels up by 5 us)
     auto enqueue = [&]() -> pdd_status {
         HIP_TRY(hipMemcpyAsync(dv, h, table_bytes, hipMemcpyHostToDevice, s));
         const Stage2Line *dv_lines = reinterpret_cast<const Stage2Line *>(dv + off_lines);
+        const SubBox *dv_boxes = reinterpret_cast<const SubBox *>(dv + off_boxes);
         const double *dv_t = reinterpret_cast<const double *>(dv + off_t);
         double *dv_lam = reinterpret_cast<double *>(dv + off_lam);
+        double *dv_stencil = reinterpret_cast<double *>(dv + off_stencil);
         void *dv_marks = nullptr;
         HIP_TRY(hipHostGetDevicePointer(&dv_marks, marks, 0));
         HIP_TRY(launch_stage2_weights(g, dv_lines, (int32_t)lines.size(), dv_t, dv_lam,
                                       reinterpret_cast<double *>(dv + off_weights), static_cast<int32_t *>(dv_marks),
                                       s));
         HIP_TRY(launch_stage2_lines(g, dv_lines, (int32_t)lines.size(), dv_t, dv_lam, s));
+        auto stencils = [&](bool parts, int32_t *not_dominant) {
+            return launch_stage2_stencils(problem->pd, g, dv_boxes, (int32_t)boxes.size(), (uint32_t)max_unknowns,
+                                          dv_stencil, reinterpret_cast<double *>(dv + off_rhs), parts, not_dominant, s);
+        };
+        // (a wait, once per operator)
+        const bool have_stencils = !dominance_known;
+        if (!dominance_known) {
+            HIP_TRY(stencils(false, static_cast<int32_t *>(dv_marks) + lines.size()));
+            HIP_TRY(hipStreamSynchronize(s));
+            dominant = marks[lines.size()] == 0;
+        }
+        // cyclic reduction where it fits and the device has the memory for its
+        // blocks; else banded LU, with response columns up to 2 GiB. (PDD_STAGE2_SUBSTITUTE=1 in the environment: LU, every
+        // call substituting; the tests check the ways against each other by it.)
+        const char *force_subst = std::getenv("PDD_STAGE2_SUBSTITUTE");
+        const bool subst = force_subst && force_subst[0] == '1';
+        bool use_cr = dominant && cr_fits && !subst;
+        const bool factored = same_matrices && ctx->stage2_blocks == use_cr && ctx->stage2_factor.ptr &&
+                              ctx->stage2_factor.cap >= (use_cr ? cr_bytes : lu_bytes);
+        if (!factored) {
+            ctx->stage2_key.clear();
+            pdd_status e = ensure(ctx, ctx->stage2_factor, use_cr ? cr_bytes : lu_bytes);
+            if (e == PDD_E_NOMEM && use_cr) {
+                (void)hipGetLastError();
+                use_cr = false;
+                e = ensure(ctx, ctx->stage2_factor, lu_bytes);
+            }
+            if (e) return e;
+        }
         Stage2Plan plan{};
         plan.factored = factored;
-        plan.cr_tab = use_cr ? reinterpret_cast<const Stage2Cr *>(dv + off_cr) : nullptr;
-        plan.max_L = max_L;
-        plan.wp = (int32_t)wp;
         plan.factor = static_cast<double *>(ctx->stage2_factor.ptr);
-        plan.lmul = plan.factor + unknowns * (kStage2MaxBand + 2);
         plan.rhs = reinterpret_cast<double *>(dv + off_rhs);
-        HIP_TRY(launch_stage2_solve(problem->pd, g, reinterpret_cast<const SubBox *>(dv + off_boxes),
-                                    (int32_t)boxes.size(), (uint32_t)max_unknowns,
-                                    reinterpret_cast<double *>(dv + off_stencil), plan, s));
+        std::vector<double> resp_key;
+        if (use_cr) {
+            plan.cr_tab = reinterpret_cast<const Stage2Cr *>(dv + off_cr);
+            plan.max_L = max_L;
+            plan.wp = (int32_t)wp;
+        } else {
+            plan.lmul = plan.factor + unknowns * (kStage2MaxBand + 2);
+            // the response columns depend on the factors and on f: the factors'
+            // key and the problem
+            resp_key = key;
+            resp_key.push_back((double)problem->serial);
+            const size_t resp_bytes = resp_values * sizeof(double);
+            bool use_resp = may_use_lu && few_rows && resp_bytes <= (2ull << 30) && !subst;
+            plan.resp_ready = use_resp && factored && ctx->stage2_resp_key == resp_key && ctx->stage2_resp.ptr &&
+                              ctx->stage2_resp.cap >= resp_bytes;
+            if (use_resp && !plan.resp_ready) {
+                ctx->stage2_resp_key.clear();
+                const pdd_status e = ensure(ctx, ctx->stage2_resp, resp_bytes);
+                if (e == PDD_E_NOMEM) {
+                    (void)hipGetLastError();
+                    use_resp = false;
+                } else if (e) {
+                    return e;
+                }
+            }
+            if (use_resp) {
+                plan.resp_tab = reinterpret_cast<const Stage2Resp *>(dv + off_resp);
+                plan.rb = reinterpret_cast<const uint32_t *>(dv + off_rb);
+                plan.resp = static_cast<double *>(ctx->stage2_resp.ptr);
+                plan.max_cols = max_cols;
+            }
+        }
+        if (!have_stencils || plan.resp_tab) HIP_TRY(stencils(plan.resp_tab != nullptr, nullptr));
+        HIP_TRY(launch_stage2_solve(g, dv_boxes, (int32_t)boxes.size(), (uint32_t)max_unknowns, dv_stencil, plan, s));
+        ctx->stage2_key = key;
+        ctx->stage2_blocks = use_cr;
+        ctx->stage2_dominant = dominant;
+        if (plan.resp_tab) ctx->stage2_resp_key = resp_key;
         return PDD_OK;
     };
     if ((st = enqueue())) {
         (void)hipStreamSynchronize(s);
         return st;
     }
-    ctx->stage2_key = key;
     HIP_TRY(hipEventRecord(ctx->done, s));
     ctx->any_done = true;
     HIP_TRY(hipEventSynchronize(ctx->done));
