@@ -771,12 +771,13 @@ __global__ void __launch_bounds__(256) stage2_apply_kernel(const Stage2Grid g, c
 // ones are factored by the banded LU. The LU's chain of w L dependent
 // pivots, one workgroup a subdomain, becomes 1 + log2 L levels whose rows are
 // independent. Four strips of 63 x 255 unknowns: 39.9 ms with the LU and the
-// solutions for unit boundary values that it was kept as, 0.44 ms now; with
+// solutions for unit boundary values that it was kept as, 0.49 ms now; with
 // the factors kept 0.26 and 0.13 ms. What bounds a level is the inversion
 // (24 us: 64 dependent pivots) and the products on the FP64 matrix cores
 // (9 us; 37 us where the rows are several per CU). Blocks are padded by the
 // identity to WP (the widest subdomain's w, to a multiple of 16) and kept by
-// column: D (D^-1 once eliminated), P, Q of every row, and M, N and the new A,
+// column: D (D^-1 once eliminated), P, Q of every row (D's rounding in P's place
+// before), and M, N and the new A,
 // C of every (row, level); level 0, whose A and C are diagonal, has no P, Q, M
 // and N (stored all the same they took 32 us of 0.48 ms).
 template <int WP>
@@ -811,22 +812,34 @@ constexpr int kCrThreads = 1024;
 constexpr int kCrWaves = kCrThreads / 64;
 typedef double Acc4 __attribute__((ext_vector_type(4)));
 
-// A block (by column) to LDS.
+// A block (by column) to registers, and from there to LDS.
+template <int WP>
+struct CrCopy {
+    static constexpr int kPer = (WP * WP + kCrThreads - 1) / kCrThreads;
+    double t[kPer];
+    __device__ __forceinline__ void fetch(const double *src)
+    {
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const int e = threadIdx.x + u * kCrThreads;
+            t[u] = e < WP * WP ? gload(src + e) : 0.0;
+        }
+    }
+    __device__ __forceinline__ void put(double *dst) const
+    {
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const int e = threadIdx.x + u * kCrThreads;
+            if (e < WP * WP) dst[(e / WP) * (WP + 1) + e % WP] = t[u];
+        }
+    }
+};
 template <int WP>
 __device__ __forceinline__ void cr_stage(double *dst, const double *src)
 {
-    constexpr int kPer = (WP * WP + kCrThreads - 1) / kCrThreads;
-    double t[kPer];
-#pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-        const int e = threadIdx.x + u * kCrThreads;
-        t[u] = e < WP * WP ? gload(src + e) : 0.0;
-    }
-#pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-        const int e = threadIdx.x + u * kCrThreads;
-        if (e < WP * WP) dst[(e / WP) * (WP + 1) + e % WP] = t[u];
-    }
+    CrCopy<WP> c;
+    c.fetch(src);
+    c.put(dst);
 }
 
 // 16 x 16 tile (ti, tj) of acc + sign X Y on the matrix cores, X and Y in LDS.
@@ -849,19 +862,71 @@ __device__ __forceinline__ double *cr_element(double *block, int ti, int tj, int
     return block + (tj * 16 + 4 * v + (lane >> 4)) * WP + ti * 16 + (lane & 15);
 }
 
+// a + b, and what its rounding left out.
+__device__ __forceinline__ double cr_add(double a, double b, double &lost)
+{
+    const double s = a + b, c = s - a;
+    lost = (a - (s - c)) + (b - c);
+    return s;
+}
+
+// What rounds a value v, |v| <= most, to a multiple of 2^-22 of the next power
+// of two above `most`: (v + u) - u for this u.
+__device__ __forceinline__ double cr_rounder(double most)
+{
+    return __builtin_ldexp(1.5, __builtin_amdgcn_frexp_exp(most) + 30);
+}
+
+// 16 x 16 tile of acc - (D + S) X, D, S (D's rounding) and X in LDS, nearly as if
+// summed exactly: with D + S = D1 + D2 and X = X1 + X2 (D1, X1 of 23 bits each
+// against the largest values) every partial sum of acc - D1 X1 is exact, acc
+// being that of I, and the rest is 2^-22 of it.
+template <int WP>
+__device__ __forceinline__ Acc4 cr_residual_tile(const double *D, const double *S, const double *X, int ti, int tj,
+                                                 double ud, double ux, Acc4 acc)
+{
+    const int lane = threadIdx.x & 63, low = lane & 15, high = lane >> 4;
+    const double *d = D + high * (WP + 1) + ti * 16 + low, *x = X + (tj * 16 + low) * (WP + 1) + high;
+    const double *l = S + (d - D);
+#pragma unroll 4
+    for (int k = 0; k < WP; k += 4)
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-((x[k] + ux) - ux), (d[k * (WP + 1)] + ud) - ud, acc, 0, 0, 0);
+#pragma unroll 2
+    for (int k = 0; k < WP; k += 4) {
+        const double d1 = (d[k * (WP + 1)] + ud) - ud, d2 = (d[k * (WP + 1)] - d1) + l[k * (WP + 1)];
+        const double x1 = (x[k] + ux) - ux, x2 = x[k] - x1;
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-x2, d1, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-x1, d2, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-x2, d2, acc, 0, 0, 0);
+    }
+    return acc;
+}
+
 // D^-1, P and Q (D^-1 alone at the FIRST level) of the odd multiples of
 // 2^level, one workgroup each. D is inverted in registers: lane r of wave q
 // holds columns 4 q .. 4 q + 3 of row r. The pivots of a wave's columns are its
 // own work, without a barrier (row k comes from lane k); their multipliers then
 // go to the other waves through LDS: one barrier per four pivots. (32 us a
 // level with one per pivot, 27 us with eight waves of eight columns, 24 us so.)
-// Rows are left unscaled until the end.
+// Rows are left unscaled until the end. At the lower levels one Newton step,
+// X + X (I - D X), then takes out the elimination's rounding: the rows of a
+// level have (nearly) the same D where the coefficients vary little, so its
+// errors do not average out over them, and without the step the solution was 3
+// to 8 times as far from exact as the banded LU's. Level 1's inverse counts
+// most; there I - D X is summed as if exactly. What the update left out in
+// rounding D is kept in the place of P until then. (Errors against the banded
+// LU's, strips of 63 x 255 unknowns, c varying and c = 0 throughout: 3.7 and 7.4
+// without, 0.7 and 2.1 with the steps alone, 0.6 and 1.2 so; steps at fewer
+// levels 0.8 to 1.3, exact sums at all of them no better. A new operator on
+// 257^2 points takes 0.49 ms, 0.44 without, 0.57 with exact sums at all levels.)
+constexpr int kCrNewtonLevels = 4;
 template <int WP, bool FIRST>
 __global__ void __launch_bounds__(kCrThreads) stage2_cr_eliminate_kernel(const SubBox *boxes, const Stage2Cr *tab,
                                                                          const double *stencil, double *cr, int level)
 {
-    constexpr int kLds = FIRST ? 1 : WP * (WP + 1);
-    __shared__ double X[kLds], A[kLds], C[kLds];
+    constexpr int kLds = WP * (WP + 1);
+    __shared__ double X[kLds], R[kLds];  // R: D, then I - D X
+    __shared__ double A[FIRST ? 1 : kLds], C[FIRST ? 1 : kLds];
     constexpr int kCols = 64 / kCrWaves;
     __shared__ double mult[2][kCols][64], inverse[64];
     const CrBox<WP> bx(boxes, tab, blockIdx.y);
@@ -878,11 +943,17 @@ __global__ void __launch_bounds__(kCrThreads) stage2_cr_eliminate_kernel(const S
             a[e] = bx.centre(stencil, i, r, k);
         else
             a[e] = r < WP && k < WP ? gload(row + k * WP + r) : (r == k ? 1.0 : 0.0);
+        if (!FIRST && r < WP && k < WP) R[k * (WP + 1) + r] = a[e];
     }
-    if (!FIRST) {  // the last update's
+    CrCopy<WP> to_a;
+    if (!FIRST) {  // the last update's; D's rounding is in A's place meanwhile
         const double *ac = bx.pair(cr, level - 1, i >> level) + 2 * nb;
-        cr_stage<WP>(A, ac);
+        to_a.fetch(ac);
         cr_stage<WP>(C, ac + nb);
+        if (level < kCrNewtonLevels)
+            cr_stage<WP>(A, row + nb);
+        else
+            to_a.put(A);
     }
     for (int k0 = 0, b = 0; k0 < WP; k0 += kCols, b ^= 1) {
         if (q * kCols == k0) {
@@ -913,24 +984,81 @@ __global__ void __launch_bounds__(kCrThreads) stage2_cr_eliminate_kernel(const S
         }
     }
     const double scale = r < WP ? inverse[r] : 1.0;
-    double *D = row, *P = row + nb, *Q = row + 2 * nb;
 #pragma unroll
     for (int e = 0; e < kCols; ++e) {
         const int k = q * kCols + e;
         a[e] *= scale;
-        if (r >= WP || k >= WP) continue;
-        gstore(D + k * WP + r, a[e]);
-        if (!FIRST) X[k * (WP + 1) + r] = a[e];
+        if (r < WP && k < WP) X[k * (WP + 1) + r] = a[e];
     }
-    if (FIRST) return;
     __syncthreads();
-    const int nt = WP / 16;
+    double *D = row, *P = row + nb, *Q = row + 2 * nb;
+    const int nt = WP / 16, ti = q / nt, tj = q % nt;
+    const bool mine = q < nt * nt;  // a tile a wave
+    Acc4 acc{0, 0, 0, 0};
+    if (FIRST || level < kCrNewtonLevels) {
+        const int tile = (tj * 16 + (r >> 4)) * (WP + 1) + ti * 16 + (r & 15);  // acc[v]: 4 v columns on
+        if (FIRST) {
+            if (r < WP) {
+                const double lower = r ? bx.centre(stencil, i, r, r - 1) : 0.0, centre = bx.centre(stencil, i, r, r);
+                const double upper = r + 1 < WP ? bx.centre(stencil, i, r, r + 1) : 0.0;
+#pragma unroll
+                for (int e = 0; e < kCols; ++e) {
+                    const int k = q * kCols + e;
+                    if (k >= WP) continue;
+                    const double *x = X + k * (WP + 1);
+                    double v = madd(-centre, a[e], r == k ? 1.0 : 0.0);
+                    v = madd(-lower, x[r ? r - 1 : 0], v);
+                    R[k * (WP + 1) + r] = madd(-upper, x[r + 1 < WP ? r + 1 : r], v);
+                }
+            }
+        } else {
+            if (mine) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) acc[v] = ti * 16 + (r & 15) == tj * 16 + 4 * v + (r >> 4) ? 1.0 : 0.0;
+                if (level == 1) {
+                    // (the largest entries of a diagonally dominant D and of its
+                    // inverse are on their diagonals)
+                    const int at = r < WP ? r * (WP + 2) : 0;
+                    const double ud = cr_rounder(wave_max(fabs(R[at]))), ux = cr_rounder(wave_max(fabs(X[at])));
+                    acc = cr_residual_tile<WP>(R, A, X, ti, tj, ud, ux, acc);
+                } else {
+                    acc = cr_tile<WP>(A, X, ti, tj, -1.0, cr_tile<WP>(R, X, ti, tj, -1.0, acc));
+                }
+            }
+            __syncthreads();
+            if (mine)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) R[tile + 4 * v * (WP + 1)] = acc[v];
+            to_a.put(A);
+        }
+        __syncthreads();
+        if (mine) {
+            acc = cr_tile<WP>(X, R, ti, tj, 1.0, Acc4{0, 0, 0, 0});
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                acc[v] += X[tile + 4 * v * (WP + 1)];
+                gstore(cr_element<WP>(D, ti, tj, v), acc[v]);
+            }
+        }
+        if (FIRST) return;
+        __syncthreads();
+        if (mine)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) X[tile + 4 * v * (WP + 1)] = acc[v];
+        __syncthreads();
+    } else {
+#pragma unroll
+        for (int e = 0; e < kCols; ++e) {
+            const int k = q * kCols + e;
+            if (r < WP && k < WP) gstore(D + k * WP + r, a[e]);
+        }
+    }
     for (int n = q; n < 2 * nt * nt; n += kCrWaves) {
         const bool second = n >= nt * nt;
-        const int m = second ? n - nt * nt : n, ti = m / nt, tj = m % nt;
-        const Acc4 acc = cr_tile<WP>(X, second ? C : A, ti, tj, 1.0, Acc4{0, 0, 0, 0});
+        const int m = second ? n - nt * nt : n;
+        acc = cr_tile<WP>(X, second ? C : A, m / nt, m % nt, 1.0, Acc4{0, 0, 0, 0});
 #pragma unroll
-        for (int v = 0; v < 4; ++v) gstore(cr_element<WP>(second ? Q : P, ti, tj, v), acc[v]);
+        for (int v = 0; v < 4; ++v) gstore(cr_element<WP>(second ? Q : P, m / nt, m % nt, v), acc[v]);
     }
 }
 
@@ -958,7 +1086,9 @@ __global__ void __launch_bounds__(kCrThreads) stage2_cr_first_update_kernel(cons
     for (int e = threadIdx.x; e < nb; e += kCrThreads) {
         const int r = e % WP, k = e / WP;
         const double va = ai[r] * gload(lower + e), vc = has_upper ? ci[r] * gload(upper + e) : 0.0;
-        gstore(D + e, bx.centre(stencil, i, r, k) - va * cl[k] - vc * au[k]);
+        double lost;
+        gstore(D + e, cr_add(bx.centre(stencil, i, r, k), -madd(va, cl[k], vc * au[k]), lost));
+        gstore(D + nb + e, lost);
         gstore(ac + e, -(va * al[k]));
         gstore(ac + nb + e, -(vc * cu[k]));
     }
@@ -995,11 +1125,9 @@ __global__ void __launch_bounds__(kCrThreads) stage2_cr_update_kernel(const SubB
     __syncthreads();
     for (int m = q; m < tiles; m += kCrWaves) {
         const int ti = m / nt, tj = m % nt;
-        Acc4 acc{0, 0, 0, 0};
-        if (part == 2)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) acc[v] = gload(cr_element<WP>(D, ti, tj, v));
-        acc = cr_tile<WP>(X[0], Y[0], ti, tj, sign, acc);
+        // (A Q + C P is summed up before it is taken from D, whose rounding
+        // would otherwise go into every term)
+        Acc4 acc = cr_tile<WP>(X[0], Y[0], ti, tj, sign, Acc4{0, 0, 0, 0});
         if (part != 2) {
 #pragma unroll
             for (int v = 0; v < 4; ++v) gstore(cr_element<WP>(out, ti, tj, v), acc[v]);
@@ -1007,7 +1135,16 @@ __global__ void __launch_bounds__(kCrThreads) stage2_cr_update_kernel(const SubB
         }
         if (has_upper) acc = cr_tile<WP>(X[1], Y[1], ti, tj, sign, acc);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) gstore(cr_element<WP>(part == 2 ? D : out + nb, ti, tj, v), acc[v]);
+        for (int v = 0; v < 4; ++v) {
+            double *at = cr_element<WP>(part == 2 ? D : out + nb, ti, tj, v);
+            if (part == 2) {
+                double lost;
+                gstore(at, cr_add(gload(at), acc[v], lost));
+                gstore(at + nb, gload(at + nb) + lost);
+            } else {
+                gstore(at, acc[v]);
+            }
+        }
     }
 }
 

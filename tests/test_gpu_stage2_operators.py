@@ -15,48 +15,76 @@ torch = pytest.importorskip("torch")
 from paper_1512_02818_amd import pdd  # noqa: E402
 from paper_1512_02818_amd import workloads as W  # noqa: E402
 
-N0, N1, DX, M = 129, 65, 1.0 / 256, 63
+DX, M = 1.0 / 256, 63
 
 
 def apply(st, x):
-    """The five-point operator, coefficients [west, south, centre, north, east], on an array [y][x]."""
+    """The five-point operator, coefficients [west, south, centre, north, east] at every point, on an array [y][x]."""
     r = st[2] * x
-    r[:, 1:] += st[0] * x[:, :-1]
-    r[:, :-1] += st[4] * x[:, 1:]
-    r[1:] += st[1] * x[:-1]
-    r[:-1] += st[3] * x[1:]
+    r[:, 1:] += st[0][:, 1:] * x[:, :-1]
+    r[:, :-1] += st[4][:, :-1] * x[:, 1:]
+    r[1:] += st[1][1:] * x[:-1]
+    r[:-1] += st[3][:-1] * x[1:]
     return r
+
+
+def bands(st):
+    """Its coefficients in rows of 2 w + 1, in the order of the points."""
+    rows, w = st[2].shape
+    A = np.zeros((rows, w, 2 * w + 1))
+    A[:, :, w], A[1:, :, 0], A[:-1, :, 2 * w] = st[2], st[1][1:], st[3][:-1]
+    A[:, 1:, w - 1], A[:, :-1, w + 1] = st[0][:, 1:], st[4][:, :-1]
+    return A.reshape(rows * w, 2 * w + 1)
 
 
 def exact(st, f):
     import scipy.sparse as sp
     import scipy.sparse.linalg as sl
-    one, inner = np.ones(M * M), np.ones(M * M - 1)
-    inner[M - 1::M] = 0.0
-    lu = sl.splu(sp.diags([st[2] * one, st[0] * inner, st[4] * inner, st[1] * one[M:], st[3] * one[M:]],
-                          [0, -1, 1, -M, M], format="csc"))
-    x, wide = np.zeros((M, M), np.longdouble), [np.longdouble(v) for v in st]
+    w, A = f.shape[1], bands(st)
+    off = sorted({-w, -1, 0, 1, w})
+    lu = sl.splu(sp.diags([A[max(0, -o):len(A) - max(0, o), w + o] for o in off], off, format="csc"))
+    x, wide = np.zeros(f.shape, np.longdouble), [v.astype(np.longdouble) for v in st]
     for _ in range(12):
-        x = x + lu.solve((f - apply(wide, x)).astype(np.float64).ravel()).reshape(M, M)
+        x = x + lu.solve((f - apply(wide, x)).astype(np.float64).ravel()).reshape(f.shape)
     return x
 
 
 def banded_lu(st, f):
-    n = M * M
-    A = np.zeros((n, 2 * M + 1))
-    A[:, M], A[M:, 0], A[:-M, 2 * M] = st[2], st[1], st[3]
-    inner = np.arange(n) % M
-    A[inner > 0, M - 1], A[inner < M - 1, M + 1] = st[0], st[4]
-    y, x, o = f.astype(np.float64).ravel(), np.zeros(n + M), np.arange(M)
+    w, A = f.shape[1], bands(st)
+    n, y, o = len(A), f.astype(np.float64).ravel(), np.arange(w)
+    x = np.zeros(n + w)
     for k in range(n - 1):
-        m = min(M, n - 1 - k)
+        m = min(w, n - 1 - k)
         rows = k + 1 + o[:m]
-        mult = A[rows, M - 1 - o[:m]] / A[k, M]
-        A[rows[:, None], o[None] - o[:m, None] + M] -= mult[:, None] * A[k, M + 1:]
+        mult = A[rows, w - 1 - o[:m]] / A[k, w]
+        A[rows[:, None], o[None] - o[:m, None] + w] -= mult[:, None] * A[k, w + 1:]
         y[rows] -= mult * y[k]
     for k in range(n - 1, -1, -1):
-        x[k] = (y[k] - A[k, M + 1:] @ x[k + 1:k + 1 + M]) / A[k, M]
-    return x[:n].reshape(M, M)
+        x[k] = (y[k] - A[k, w + 1:] @ x[k + 1:k + 1 + w]) / A[k, w]
+    return x[:n].reshape(f.shape)
+
+
+def errors(pd, u, lo, dx, box, b, c):
+    """Errors, relative to the largest value, of the values u inside box = (i0, i1, j0, j1) and of banded LU
+    (by rows along the shorter side), for u's values on the box's edges; b(x, y), c(x, y): the coefficients."""
+    from oracle import oracle as O
+    i0, i1, j0, j1 = box
+    x, y = np.meshgrid(lo[0] + np.arange(i0 + 1, i1) * dx[0], lo[1] + np.arange(j0 + 1, j1) * dx[1])
+    b, c = b(x, y), c(x, y)
+    h = [0.5 * pd["sigma"] ** 2 / d ** 2 for d in dx]
+    st = [h[0] - b[0] / (2 * dx[0]), h[1] - b[1] / (2 * dx[1]), -2 * h[0] - 2 * h[1] + c + 0 * x,
+          h[1] + b[1] / (2 * dx[1]), h[0] + b[0] / (2 * dx[0])]
+    f = O.source(pd, np.stack([x.ravel(), y.ravel()], axis=1)).reshape(x.shape).astype(np.longdouble)
+    v = u[j0:j1 + 1, i0:i1 + 1].astype(np.longdouble)
+    f[:, 0] -= st[0][:, 0] * v[1:-1, 0]
+    f[0] -= st[1][0] * v[0, 1:-1]
+    f[-1] -= st[3][-1] * v[-1, 1:-1]
+    f[:, -1] -= st[4][:, -1] * v[1:-1, -1]
+    v = v[1:-1, 1:-1]
+    if f.shape[1] > f.shape[0]:
+        f, v, st = f.T.copy(), v.T.copy(), [st[q].T.copy() for q in (1, 0, 2, 4, 3)]
+    ref = exact(st, f)
+    return [float(np.max(np.abs(e - ref)) / np.max(np.abs(ref))) for e in (v, banded_lu(st, f))]
 
 
 def constant_grid(v):
@@ -70,7 +98,6 @@ def constant_grid(v):
 def test_operators(b, sigma, c, tab):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
-    from oracle import oracle as O
     pd = dict(W.unit_square_problem(seed=0), lo=[0.0, 0.0], hi=[0.5, 0.25], sigma=sigma, B=[[0.0, 0.0], [0.0, 0.0]],
               b0=[b, -b], c_a=c, c_b=0.0)
     if tab:
@@ -83,23 +110,44 @@ def test_operators(b, sigma, c, tab):
     vals = W.manufactured_u(pd, nodes) + np.random.default_rng(1).normal(scale=0.01, size=len(nodes))
     ctx = pdd.Context(0)
     prob = pdd.Problem(ctx, pd)
-    got = [pdd.stage2(prob, (N0, N1), [[0.25], []], nodes, vals, 3.0).cpu().numpy() for _ in range(2)]
+    got = [pdd.stage2(prob, (2 * M + 3, M + 2), [[0.25], []], nodes, vals, 3.0).cpu().numpy() for _ in range(2)]
     prob.close()
     ctx.close()
     assert got[0].tobytes() == got[1].tobytes()  # the second call takes what the first kept
-    u = got[0]
-    s2 = 0.5 * sigma * sigma / DX ** 2
-    st = [s2 - b / (2 * DX), s2 + b / (2 * DX), c - 4 * s2, s2 - b / (2 * DX), s2 + b / (2 * DX)]
-    for i0 in (0, 64):
-        x, y = np.meshgrid((i0 + 1 + np.arange(M)) * DX, (1 + np.arange(M)) * DX)
-        f = O.source(pd, np.stack([x.ravel(), y.ravel()], axis=1)).reshape(M, M).astype(np.longdouble)
-        box = u[:, i0:i0 + 65]
-        f[:, 0] -= np.longdouble(st[0]) * box[1:-1, 0]
-        f[0] -= np.longdouble(st[1]) * box[0, 1:-1]
-        f[-1] -= np.longdouble(st[3]) * box[-1, 1:-1]
-        f[:, -1] -= np.longdouble(st[4]) * box[1:-1, -1]
-        ref = exact(st, f)
-        scale = np.max(np.abs(ref))
-        err, lu = (float(np.max(np.abs(v - ref)) / scale) for v in (box[1:-1, 1:-1], banded_lu(st, f)))
+    for i0 in (0, M + 1):
+        err, lu = errors(pd, got[0], (0.0, 0.0), (DX, DX), (i0, i0 + M + 1, 0, M + 1),
+                         lambda x, y: (b + 0 * x, -b + 0 * x), lambda x, y: c)
         print(f"b {b} sigma {sigma} c {c} {tab}: {err:.1e}, banded LU {lu:.1e}", flush=True)
         assert err <= 4 * lu + 16 * np.finfo(float).eps
+
+
+@pytest.mark.parametrize("w,rows", [(1, 7), (15, 15), (16, 255), (31, 127), (33, 63), (47, 191), (63, 63), (64, 255)])
+@pytest.mark.parametrize("axis,laplace", [(0, False), (1, False), (0, True)])
+def test_strips(w, rows, axis, laplace):
+    """Strips of every width of the cyclic reduction's blocks, over one to eight levels, with an operator that
+    varies and with the Laplacian, whose rounding errors are alike in all rows: no further from exact than the
+    banded LU, but for twice (the errors are maxima of rounding noise)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    n = [2 * w + 3, rows + 2]
+    hi = [(m - 1) * DX for m in n]
+    nodes = np.array([[(w + 1) * DX, hi[1] * t] for t in (0.2, 0.4, 0.6, 0.8)])
+    cuts = [[(w + 1) * DX], []]
+    if axis:
+        n, hi, nodes, cuts = n[::-1], hi[::-1], nodes[:, ::-1].copy(), cuts[::-1]
+    pd = dict(W.unit_square_problem(seed=0), lo=[0.0, 0.0], hi=hi)
+    if laplace:
+        pd.update(B=[[0.0, 0.0], [0.0, 0.0]], c_a=0.0, c_b=0.0)
+    vals = W.manufactured_u(pd, nodes) + np.random.default_rng(w).normal(scale=0.01, size=len(nodes))
+    ctx = pdd.Context(0)
+    prob = pdd.Problem(ctx, pd)
+    u = pdd.stage2(prob, tuple(n), cuts, nodes, vals, 3.0).cpu().numpy()
+    prob.close()
+    ctx.close()
+    B = pd["B"]
+    for s0 in (0, w + 1):
+        box = (s0, s0 + w + 1, 0, rows + 1)
+        err, lu = errors(pd, u, (0.0, 0.0), (DX, DX), box[2:] + box[:2] if axis else box,
+                         lambda x, y: (B[0][0] * x, B[1][1] * y), lambda x, y: pd["c_a"] + pd["c_b"] * (x * x + y * y))
+        print(f"{w} x {rows}, axis {axis}, {laplace}: {err:.1e}, banded LU {lu:.1e}", flush=True)
+        assert err <= 2 * lu + 4 * np.finfo(float).eps
