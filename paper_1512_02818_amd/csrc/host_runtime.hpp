@@ -146,6 +146,7 @@ struct pdd_ctx {
     pdd::DeviceBuffer stage2_factor;
     std::vector<double> stage2_key;
     bool stage2_blocks = false, stage2_dominant = false;
+    bool stage2_refused = false;  // no memory for more than LU factors
     // with LU factors, the subdomains' response columns to their boundary values
     // (and to f), for the key and the problem
     pdd::DeviceBuffer stage2_resp;

@@ -1884,7 +1884,10 @@ pdd_status pdd_stage2(pdd_problem *problem, const pdd_partition *part, const dou
         // call substituting; the tests check the ways against each other by it.)
         const char *force_subst = std::getenv("PDD_STAGE2_SUBSTITUTE");
         const bool subst = force_subst && force_subst[0] == '1';
-        bool use_cr = dominant && cr_fits && !subst;
+        // (memory refused once is not asked for again with these matrices: their
+        // LU factors are kept instead)
+        bool refused = same_matrices && ctx->stage2_refused;
+        bool use_cr = dominant && cr_fits && !subst && !refused;
         const bool factored = same_matrices && ctx->stage2_blocks == use_cr && ctx->stage2_factor.ptr &&
                               ctx->stage2_factor.cap >= (use_cr ? cr_bytes : lu_bytes);
         if (!factored) {
@@ -1893,6 +1896,7 @@ pdd_status pdd_stage2(pdd_problem *problem, const pdd_partition *part, const dou
             if (e == PDD_E_NOMEM && use_cr) {
                 (void)hipGetLastError();
                 use_cr = false;
+                refused = true;
                 e = ensure(ctx, ctx->stage2_factor, lu_bytes);
             }
             if (e) return e;
@@ -1913,7 +1917,7 @@ pdd_status pdd_stage2(pdd_problem *problem, const pdd_partition *part, const dou
             resp_key = key;
             resp_key.push_back((double)problem->serial);
             const size_t resp_bytes = resp_values * sizeof(double);
-            bool use_resp = may_use_lu && few_rows && resp_bytes <= (2ull << 30) && !subst;
+            bool use_resp = may_use_lu && few_rows && resp_bytes <= (2ull << 30) && !subst && !refused;
             plan.resp_ready = use_resp && factored && ctx->stage2_resp_key == resp_key && ctx->stage2_resp.ptr &&
                               ctx->stage2_resp.cap >= resp_bytes;
             if (use_resp && !plan.resp_ready) {
@@ -1922,6 +1926,7 @@ pdd_status pdd_stage2(pdd_problem *problem, const pdd_partition *part, const dou
                 if (e == PDD_E_NOMEM) {
                     (void)hipGetLastError();
                     use_resp = false;
+                    refused = true;
                 } else if (e) {
                     return e;
                 }
@@ -1938,6 +1943,7 @@ pdd_status pdd_stage2(pdd_problem *problem, const pdd_partition *part, const dou
         ctx->stage2_key = key;
         ctx->stage2_blocks = use_cr;
         ctx->stage2_dominant = dominant;
+        ctx->stage2_refused = refused;
         if (plan.resp_tab) ctx->stage2_resp_key = resp_key;
         return PDD_OK;
     };
