@@ -476,7 +476,9 @@ typedef struct {
  * lines or given twice, a node off every interface or outside the box, a
  * singular interpolation system; PDD_E_UNSUPPORTED for a problem that is not
  * a 2D box or a subdomain whose shorter side has more than 64 interior
- * points; PDD_E_NOMEM / PDD_E_HIP from the device. */
+ * points; PDD_E_NOMEM / PDD_E_HIP from the device. A call refused for a
+ * singular interpolation system leaves u's values inside the box as they were
+ * (the box's edges may hold g already). */
 pdd_status pdd_stage2(pdd_problem *problem, const pdd_partition *part, const double *nodes, const double *values,
                       int64_t n_nodes, double *u, void *stream);
 

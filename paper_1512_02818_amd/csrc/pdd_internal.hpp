@@ -326,6 +326,7 @@ struct Stage2Grid {
     double lo0, lo1, span0, span1;  // point i of axis d at lo_d + span_d i / (n_d - 1)
     double dx0, dx1;                 // span_d / (n_d - 1)
     double half_s2;                  // (1/2) sigma^2
+    int32_t *failed;                 // set where a line's system is singular: u's interior is then left alone
 };
 // One subdomain: the grid box [i0, i1] x [j0, j1] (boundary indices
 // included); its interior unknowns in the order r = s w + f, f running along

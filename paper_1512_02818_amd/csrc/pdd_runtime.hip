@@ -1824,11 +1824,11 @@ pdd_status pdd_stage2(pdd_problem *problem, const pdd_partition *part, const dou
         max_cols = std::max(max_cols, resp_tab[q].nb + 1);
         few_rows = few_rows && resp_tab[q].nb <= kStage2MaxBoundaryRows;
     }
-    // device tables: lines | t | values, then weights | boxes | blocks' places |
-    // response layout | boundary rows | stencils | right sides | large lines'
-    // matrices; the lines' marks, and one for the operator, stay in the staging
-    // buffer
-    const size_t off_lines = 0;
+    // device tables: the failure mark | lines | t | values, then weights | boxes |
+    // blocks' places | response layout | boundary rows | stencils | right sides |
+    // large lines' matrices; the lines' marks, and one for the operator, stay in
+    // the staging buffer
+    const size_t off_lines = 256;
     const size_t off_t = align_up(off_lines + lines.size() * sizeof(Stage2Line), 256);
     const size_t off_lam = align_up(off_t + t_all.size() * sizeof(double), 256);
     const size_t off_boxes = align_up(off_lam + z_all.size() * sizeof(double), 256);
@@ -1843,6 +1843,7 @@ pdd_status pdd_stage2(pdd_problem *problem, const pdd_partition *part, const dou
     if ((st = ensure(ctx, ctx->stage2, bytes))) return st;
     if ((st = ensure_stage(ctx, table_bytes + (lines.size() + 1) * sizeof(int32_t)))) return st;
     char *h = static_cast<char *>(ctx->stage);
+    std::memset(h, 0, off_lines);
     std::memcpy(h + off_lines, lines.data(), lines.size() * sizeof(Stage2Line));
     std::memcpy(h + off_t, t_all.data(), t_all.size() * sizeof(double));
     std::memcpy(h + off_lam, z_all.data(), z_all.size() * sizeof(double));
@@ -1851,6 +1852,7 @@ pdd_status pdd_stage2(pdd_problem *problem, const pdd_partition *part, const dou
     std::memcpy(h + off_resp, resp_tab.data(), resp_tab.size() * sizeof(Stage2Resp));
     std::memcpy(h + off_rb, rb.data(), rb.size() * sizeof(uint32_t));
     char *dv = static_cast<char *>(ctx->stage2.ptr);
+    g.failed = reinterpret_cast<int32_t *>(dv);
     int32_t *marks = reinterpret_cast<int32_t *>(h + table_bytes);
     std::memset(marks, 0, (lines.size() + 1) * sizeof(int32_t));
     // the staging buffer is in use until the call's own wait at the end (an

@@ -175,7 +175,7 @@ __device__ __forceinline__ double wave_max(double v)
 // 0.20 ms either way).
 constexpr int kWeightsThreads = 1024;
 __device__ __forceinline__ void solve_weights(double *M, double *z, const double *first, const double *last,
-                                              const double *t, double eps, int m, int32_t *mark)
+                                              const double *t, double eps, int m, int32_t *mark, int32_t *failed)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     constexpr int kWaves = kWeightsThreads / 64;
@@ -205,7 +205,7 @@ __device__ __forceinline__ void solve_weights(double *M, double *z, const double
         __syncthreads();
         if (pivot == 0.0) {  // every wave alike
             for (int r = threadIdx.x; r < m; r += kWeightsThreads) z[r] = 0.0;
-            if (threadIdx.x == 0) *mark = 1;
+            if (threadIdx.x == 0) *mark = *failed = 1;
             return;
         }
         // rows c and p change places; their multipliers take the entries of
@@ -253,9 +253,9 @@ __global__ void __launch_bounds__(kWeightsThreads) stage2_weights_kernel(const S
     const double *first = g.u + (L.d == 0 ? (size_t)L.k : (size_t)L.k * g.n0);
     const double *last = g.u + (L.d == 0 ? (size_t)(g.n1 - 1) * g.n0 + L.k : (size_t)L.k * g.n0 + g.n0 - 1);
     if (L.m <= kStage2MaxLdsNodes)
-        solve_weights(s_M, z, first, last, t + L.at, L.eps, L.m, marks + blockIdx.x);
+        solve_weights(s_M, z, first, last, t + L.at, L.eps, L.m, marks + blockIdx.x, g.failed);
     else
-        solve_weights(matrices + L.matrix, z, first, last, t + L.at, L.eps, L.m, marks + blockIdx.x);
+        solve_weights(matrices + L.matrix, z, first, last, t + L.at, L.eps, L.m, marks + blockIdx.x, g.failed);
 }
 
 // One workgroup row per line (blockIdx.y); the points of the line strictly
@@ -263,6 +263,7 @@ __global__ void __launch_bounds__(kWeightsThreads) stage2_weights_kernel(const S
 __global__ void __launch_bounds__(256) stage2_lines_kernel(const Stage2Grid g, const Stage2Line *lines, int32_t n_lines,
                                                            const double *t, const double *lam)
 {
+    if (*g.failed) return;
     const Stage2Line L = lines[blockIdx.y];
     const int ne = L.d == 0 ? g.n1 : g.n0;  // points along the line
     for (int p = 1 + blockIdx.x * blockDim.x + threadIdx.x; p < ne - 1; p += gridDim.x * blockDim.x) {
@@ -516,6 +517,7 @@ __global__ void __launch_bounds__(kStage2SubstThreads) stage2_subst_kernel(const
     const double *Lm = lmul + bx.first * MW;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
+    if (*g.failed) return;
     double v = tid < 64 && lane < w ? st[(size_t)lane * 6 + 5] : 0.0;  // rows 0 .. w - 1
     int s = 0;  // lane of pivot k: k mod w
     for (uint64_t k0 = 0; k0 < n; k0 += CH) {
@@ -736,6 +738,7 @@ __global__ void __launch_bounds__(256) stage2_apply_kernel(const Stage2Grid g, c
                                                            const double *resp)
 {
     __shared__ double yb[kStage2MaxBoundaryRows];
+    if (*g.failed) return;
     const SubBox bx = boxes[blockIdx.y];
     const Stage2Resp rt = tab[blockIdx.y];
     const uint64_t n = (uint64_t)bx.w * (uint64_t)bx.L;
@@ -1203,6 +1206,7 @@ struct CrSolve {
             const bool there = r < w && (q == 1 ? active : q == 0 ? lo : up);
             x[q][r] = there ? gload(f + (int64_t)(q - 1) * t * w + r) : 0.0;
         }
+        const bool failed = *g.failed != 0;
         const double sa = level == 0 && active ? bx.slot(stencil, i, r, 0) : 1.0;
         const double sc = level == 0 && active ? bx.slot(stencil, i, r, 4) : 1.0;
         __syncthreads();
@@ -1226,7 +1230,7 @@ struct CrSolve {
                 gstore(f + r, v);
                 int gi, gj;
                 stage2_point(bx.b, (uint64_t)(i - 1) * w + r, gi, gj);
-                g.u[(size_t)gj * g.n0 + gi] = v;
+                if (!failed) g.u[(size_t)gj * g.n0 + gi] = v;
             }
         }
     }
