@@ -326,7 +326,10 @@ struct Stage2Grid {
     double lo0, lo1, span0, span1;  // point i of axis d at lo_d + span_d i / (n_d - 1)
     double dx0, dx1;                 // span_d / (n_d - 1)
     double half_s2;                  // (1/2) sigma^2
-    int32_t *failed;                 // set where a line's system is singular: u's interior is then left alone
+    int32_t *line_failed;            // per line, whether its system is singular
+    int32_t *failed;                 // whether one is (launch_stage2_stencils): u's interior is then left alone
+    double *lines;                   // values of line q between the box's edges, point p at q line_stride + p
+    int32_t line_stride;
 };
 // One subdomain: the grid box [i0, i1] x [j0, j1] (boundary indices
 // included); its interior unknowns in the order r = s w + f, f running along
@@ -334,6 +337,7 @@ struct Stage2Grid {
 // `first`: its first unknown in the stencil / factor tables.
 struct SubBox {
     int32_t i0, i1, j0, j1;
+    int32_t side[4];  // the lines at i0, i1, j0 and j1 (-1: the problem's box ends there)
     int32_t w, L, fast_x, pad;
     uint64_t first;
 };
@@ -342,7 +346,7 @@ constexpr int kStage2MaxBand = 64;  // shorter interior side of a subdomain, at 
 // grid index k), m data points at coordinates t[0..m-1] along the other axis
 // with multiquadric weights lam[0..m-1] (at offset `at` in the tables; before
 // the weights are solved for: the data points' values). `matrix`: offset of
-// its system's m x (m + 1) doubles in launch_stage2_weights' buffer, where m >
+// its system's m x (m + 1) doubles in Stage2Edges::matrices, where m >
 // kStage2MaxLdsNodes.
 struct Stage2Line {
     int32_t d, k, m, pad;
@@ -350,19 +354,21 @@ struct Stage2Line {
     double eps;
 };
 constexpr int kStage2MaxLdsNodes = 136;
-// Physical-boundary values g of the grid (every point of the box's edges).
-hipError_t launch_stage2_boundary(const DevProblem<double> &P, const Stage2Grid &g, hipStream_t s);
-// The lines' multiquadric weights from their values; the values at a line's
-// ends are taken from u's boundary first. marks[q] (host memory that
-// the device can write; zero before) is set to 1 where line q's system is
-// singular (its weights are zero then).
-hipError_t launch_stage2_weights(const Stage2Grid &g, const Stage2Line *lines, int32_t n_lines, const double *t,
-                                 double *lam, double *matrices, int32_t *marks, hipStream_t s);
-// Interface lines: the multiquadric interpolants at the grid points of each
-// line between the box's edges; a point where an axis-0 and an axis-1 line
-// cross takes the mean of the two.
-hipError_t launch_stage2_lines(const Stage2Grid &g, const Stage2Line *lines, int32_t n_lines, const double *t,
-                               const double *lam, hipStream_t s);
+// Tables in host memory that the device can read (pinned), and device memory.
+struct Stage2Edges {
+    const Stage2Line *host_lines;
+    const double *host_t, *host_z;  // the lines' data points
+    double *t, *lam, *matrices;     // for the lines of more than kStage2MaxLdsNodes points
+    int32_t *host_marks;            // set to 1 for a line whose system is singular (zero before)
+    int32_t n_lines;
+    const uint64_t *host_table;     // copied to `table` for the kernels after this one
+    uint64_t *table;
+    uint64_t table_words;
+};
+// g at every point of the box's edges (into u), the lines' multiquadric weights
+// from their values (the values at a line's ends are g), and the interpolants at
+// the lines' points (into g.lines).
+hipError_t launch_stage2_edges(const DevProblem<double> &P, const Stage2Grid &g, const Stage2Edges &a, hipStream_t s);
 // Where a subdomain's blocks are in the cyclic reduction's buffer (in
 // doubles): three blocks per block row from `at` on, four per (row, level) pair
 // from `mn` on.
@@ -406,10 +412,12 @@ struct Stage2Plan {
 // with `parts`, two doubles per unknown: the source f alone and the boundary
 // values' part. *not_dominant (memory that the device can write; zero before;
 // may be null) is set to 1 where a neighbour's coefficient is negative or c
-// positive at some unknown.
+// positive at some unknown. The lines' points also go into u, a point where an
+// axis-0 and an axis-1 line cross as the mean of the two (unless *g.failed, which
+// is set here).
 hipError_t launch_stage2_stencils(const DevProblem<double> &P, const Stage2Grid &g, const SubBox *boxes,
-                                  int32_t n_boxes, uint32_t max_unknowns, double *stencil, double *rhs, bool parts,
-                                  int32_t *not_dominant, hipStream_t s);
+                                  int32_t n_boxes, uint32_t max_unknowns, const Stage2Line *lines, int32_t n_lines,
+                                  double *stencil, double *rhs, bool parts, int32_t *not_dominant, hipStream_t s);
 // The subdomains' solutions by the plan, written into u.
 hipError_t launch_stage2_solve(const Stage2Grid &g, const SubBox *boxes, int32_t n_boxes, uint32_t max_unknowns,
                                const double *stencil, const Stage2Plan &plan, hipStream_t s);

@@ -1720,6 +1720,12 @@ pdd_status pdd_stage2(pdd_problem *problem, const pdd_partition *part, const dou
             bx.i0 = ix[a], bx.i1 = ix[a + 1], bx.j0 = iy[b], bx.j1 = iy[b + 1];
             const int mx = bx.i1 - bx.i0 - 1, my = bx.j1 - bx.j0 - 1;
             if (mx < 1 || my < 1) continue;
+            const int at[4] = {bx.i0, bx.i1, bx.j0, bx.j1};
+            for (int q = 0; q < 4; ++q) {  // the lines are numbered as the cuts are given, axis 0 first
+                const std::vector<int> &c = cut_idx[q / 2];
+                const auto f = std::find(c.begin(), c.end(), at[q]);
+                bx.side[q] = f == c.end() ? -1 : (int)(f - c.begin()) + (q < 2 ? 0 : (int)cut_idx[0].size());
+            }
             bx.fast_x = mx <= my;
             bx.w = bx.fast_x ? mx : my;
             bx.L = bx.fast_x ? my : mx;
@@ -1742,8 +1748,6 @@ pdd_status pdd_stage2(pdd_problem *problem, const pdd_partition *part, const dou
     g.span0 = d.hi[0] - d.lo[0], g.span1 = d.hi[1] - d.lo[1];
     g.dx0 = g.span0 / (n[0] - 1), g.dx1 = g.span1 / (n[1] - 1);
     g.half_s2 = 0.5 * d.sigma * d.sigma;
-    // physical boundary first: the ends of every interface line carry g
-    HIP_TRY(launch_stage2_boundary(problem->pd, g, s));
     pdd_status st;
     // every line's data points: its ends (their values are filled in on the
     // device) and its nodes
@@ -1824,60 +1828,73 @@ pdd_status pdd_stage2(pdd_problem *problem, const pdd_partition *part, const dou
         max_cols = std::max(max_cols, resp_tab[q].nb + 1);
         few_rows = few_rows && resp_tab[q].nb <= kStage2MaxBoundaryRows;
     }
-    // device tables: the failure mark | lines | t | values, then weights | boxes |
-    // blocks' places | response layout | boundary rows | stencils | right sides |
-    // large lines' matrices; the lines' marks, and one for the operator, stay in
-    // the staging buffer
-    const size_t off_lines = 256;
-    const size_t off_t = align_up(off_lines + lines.size() * sizeof(Stage2Line), 256);
-    const size_t off_lam = align_up(off_t + t_all.size() * sizeof(double), 256);
-    const size_t off_boxes = align_up(off_lam + z_all.size() * sizeof(double), 256);
+    // tables for the device: lines | boxes | blocks' places | response layout |
+    // boundary rows; behind them in the staging buffer the lines' data points and
+    // values and their marks, and one for the operator; on the device the marks, the
+    // long lines' points and weights, stencils, right sides, lines' points and long
+    // lines' matrices
+    const size_t off_lines = 0;
+    const size_t off_boxes = align_up(off_lines + lines.size() * sizeof(Stage2Line), 256);
     const size_t off_cr = align_up(off_boxes + boxes.size() * sizeof(SubBox), 256);
     const size_t off_resp = align_up(off_cr + cr_tab.size() * sizeof(Stage2Cr), 256);
     const size_t off_rb = align_up(off_resp + resp_tab.size() * sizeof(Stage2Resp), 256);
     const size_t table_bytes = align_up(off_rb + rb.size() * sizeof(uint32_t), 256);
-    const size_t off_stencil = table_bytes;
+    const size_t data_bytes = align_up(t_all.size() * sizeof(double), 256), mark_bytes = (lines.size() + 1) * sizeof(int32_t);
+    const size_t off_failed = table_bytes;
+    const size_t off_t = align_up(off_failed + mark_bytes, 256);
+    const size_t off_lam = off_t + data_bytes;
+    const size_t off_stencil = off_lam + data_bytes;
     const size_t off_rhs = align_up(off_stencil + unknowns * 6 * sizeof(double), 256);
-    const size_t off_weights = align_up(off_rhs + unknowns * 2 * sizeof(double), 256);
+    const size_t off_points = align_up(off_rhs + unknowns * 2 * sizeof(double), 256);
+    g.line_stride = std::max(n[0], n[1]);
+    const size_t off_weights = align_up(off_points + lines.size() * (size_t)g.line_stride * sizeof(double), 256);
     const size_t bytes = off_weights + weights_values * sizeof(double);
     if ((st = ensure(ctx, ctx->stage2, bytes))) return st;
-    if ((st = ensure_stage(ctx, table_bytes + (lines.size() + 1) * sizeof(int32_t)))) return st;
+    if ((st = ensure_stage(ctx, table_bytes + 2 * data_bytes + mark_bytes))) return st;
     char *h = static_cast<char *>(ctx->stage);
-    std::memset(h, 0, off_lines);
     std::memcpy(h + off_lines, lines.data(), lines.size() * sizeof(Stage2Line));
-    std::memcpy(h + off_t, t_all.data(), t_all.size() * sizeof(double));
-    std::memcpy(h + off_lam, z_all.data(), z_all.size() * sizeof(double));
     std::memcpy(h + off_boxes, boxes.data(), boxes.size() * sizeof(SubBox));
     std::memcpy(h + off_cr, cr_tab.data(), cr_tab.size() * sizeof(Stage2Cr));
     std::memcpy(h + off_resp, resp_tab.data(), resp_tab.size() * sizeof(Stage2Resp));
     std::memcpy(h + off_rb, rb.data(), rb.size() * sizeof(uint32_t));
+    std::memcpy(h + table_bytes, t_all.data(), t_all.size() * sizeof(double));
+    std::memcpy(h + table_bytes + data_bytes, z_all.data(), z_all.size() * sizeof(double));
+    int32_t *marks = reinterpret_cast<int32_t *>(h + table_bytes + 2 * data_bytes);
+    std::memset(marks, 0, mark_bytes);
     char *dv = static_cast<char *>(ctx->stage2.ptr);
-    g.failed = reinterpret_cast<int32_t *>(dv);
-    int32_t *marks = reinterpret_cast<int32_t *>(h + table_bytes);
-    std::memset(marks, 0, (lines.size() + 1) * sizeof(int32_t));
-    // the staging buffer is in use until the call's own wait at the end (an
-    // event behind the upload would hold the kernels up by 5 us)
+    g.failed = reinterpret_cast<int32_t *>(dv + off_failed);
+    g.line_failed = g.failed + 1;
+    g.lines = reinterpret_cast<double *>(dv + off_points);
+    // the staging buffer is in use until the call's own wait at the end
     auto enqueue = [&]() -> pdd_status {
-        HIP_TRY(hipMemcpyAsync(dv, h, table_bytes, hipMemcpyHostToDevice, s));
         const Stage2Line *dv_lines = reinterpret_cast<const Stage2Line *>(dv + off_lines);
         const SubBox *dv_boxes = reinterpret_cast<const SubBox *>(dv + off_boxes);
-        const double *dv_t = reinterpret_cast<const double *>(dv + off_t);
-        double *dv_lam = reinterpret_cast<double *>(dv + off_lam);
         double *dv_stencil = reinterpret_cast<double *>(dv + off_stencil);
-        void *dv_marks = nullptr;
-        HIP_TRY(hipHostGetDevicePointer(&dv_marks, marks, 0));
-        HIP_TRY(launch_stage2_weights(g, dv_lines, (int32_t)lines.size(), dv_t, dv_lam,
-                                      reinterpret_cast<double *>(dv + off_weights), static_cast<int32_t *>(dv_marks),
-                                      s));
-        HIP_TRY(launch_stage2_lines(g, dv_lines, (int32_t)lines.size(), dv_t, dv_lam, s));
+        void *dv_stage = nullptr;  // the staging buffer's address on the device
+        HIP_TRY(hipHostGetDevicePointer(&dv_stage, h, 0));
+        char *hv = static_cast<char *>(dv_stage);
+        Stage2Edges edges{};
+        edges.host_lines = reinterpret_cast<const Stage2Line *>(hv + off_lines);
+        edges.host_t = reinterpret_cast<const double *>(hv + table_bytes);
+        edges.host_z = reinterpret_cast<const double *>(hv + table_bytes + data_bytes);
+        edges.t = reinterpret_cast<double *>(dv + off_t);
+        edges.lam = reinterpret_cast<double *>(dv + off_lam);
+        edges.matrices = reinterpret_cast<double *>(dv + off_weights);
+        edges.host_marks = reinterpret_cast<int32_t *>(hv + table_bytes + 2 * data_bytes);
+        edges.n_lines = (int32_t)lines.size();
+        edges.host_table = reinterpret_cast<const uint64_t *>(hv);
+        edges.table = reinterpret_cast<uint64_t *>(dv);
+        edges.table_words = table_bytes / sizeof(uint64_t);
+        HIP_TRY(launch_stage2_edges(problem->pd, g, edges, s));
         auto stencils = [&](bool parts, int32_t *not_dominant) {
             return launch_stage2_stencils(problem->pd, g, dv_boxes, (int32_t)boxes.size(), (uint32_t)max_unknowns,
-                                          dv_stencil, reinterpret_cast<double *>(dv + off_rhs), parts, not_dominant, s);
+                                          dv_lines, (int32_t)lines.size(), dv_stencil,
+                                          reinterpret_cast<double *>(dv + off_rhs), parts, not_dominant, s);
         };
         // (a wait, once per operator)
         const bool have_stencils = !dominance_known;
         if (!dominance_known) {
-            HIP_TRY(stencils(false, static_cast<int32_t *>(dv_marks) + lines.size()));
+            HIP_TRY(stencils(false, edges.host_marks + lines.size()));
             HIP_TRY(hipStreamSynchronize(s));
             dominant = marks[lines.size()] == 0;
         }
@@ -1953,9 +1970,9 @@ pdd_status pdd_stage2(pdd_problem *problem, const pdd_partition *part, const dou
         (void)hipStreamSynchronize(s);
         return st;
     }
-    HIP_TRY(hipEventRecord(ctx->done, s));
-    ctx->any_done = true;
-    HIP_TRY(hipEventSynchronize(ctx->done));
+    // the stream itself is waited for, not an event behind the work: from seven
+    // launches on the caller's next wait took 25 us after an event, 4 us so
+    HIP_TRY(hipStreamSynchronize(s));
     for (size_t q = 0; q < lines.size(); ++q)
         if (marks[q])
             return fail(PDD_E_INVALID, "interpolation system of interface %g is singular (repeated nodes?)",

@@ -104,27 +104,23 @@ __device__ __forceinline__ double stage2_coord(double lo, double span, int n, in
     return lo + span * (double)i / (double)(n - 1);
 }
 
-// g at every point of the box's edges.
-__global__ void __launch_bounds__(256) stage2_boundary_kernel(const DevProblem<double> P, const Stage2Grid g)
+// g at point q of the box's edges.
+__device__ __forceinline__ void stage2_edge_point(const DevProblem<double> &P, const Stage2Grid &g, const MathOf<double> &mt,
+                                                  int q)
 {
     const int n0 = g.n0, n1 = g.n1;
-    const int total = 2 * n0 + 2 * (n1 - 2);
-    MathOf<double> mt;
-    mt.init();
-    for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < total; q += gridDim.x * blockDim.x) {
-        int i, j;
-        if (q < n0) {
-            i = q, j = 0;
-        } else if (q < 2 * n0) {
-            i = q - n0, j = n1 - 1;
-        } else {
-            const int r = q - 2 * n0;
-            i = (r & 1) ? n0 - 1 : 0;
-            j = 1 + (r >> 1);
-        }
-        const double x[2] = {stage2_coord(g.lo0, g.span0, n0, i), stage2_coord(g.lo1, g.span1, n1, j)};
-        g.u[(size_t)j * n0 + i] = boundary_value<double, 2, true>(mt, P, x, P.tab);
+    int i, j;
+    if (q < n0) {
+        i = q, j = 0;
+    } else if (q < 2 * n0) {
+        i = q - n0, j = n1 - 1;
+    } else {
+        const int r = q - 2 * n0;
+        i = (r & 1) ? n0 - 1 : 0;
+        j = 1 + (r >> 1);
     }
+    const double x[2] = {stage2_coord(g.lo0, g.span0, n0, i), stage2_coord(g.lo1, g.span1, n1, j)};
+    g.u[(size_t)j * n0 + i] = boundary_value<double, 2, true>(mt, P, x, P.tab);
 }
 
 __device__ __forceinline__ double multiquadric(const double *t, const double *lam, int m, double eps, double x)
@@ -167,25 +163,40 @@ __device__ __forceinline__ double wave_max(double v)
 
 // Multiquadric weights of one line, one workgroup each: Phi lam = z by Gaussian
 // elimination with partial pivoting, Phi and, as its last column, z in LDS up to
-// kStage2MaxLdsNodes data points (149 KB), else in `matrices`. The elimination's
-// operations on each element, and its pivots, are those of the textbook loop.
-// Bound by its chain of pivots, three barriers and a division each. 14 lines of
-// 114 points: a second stage of 257^2 points with kept factors took 2.1 ms with
-// the systems solved on the host and takes 0.45 ms (three lines of 8 points:
-// 0.20 ms either way).
-constexpr int kWeightsThreads = 1024;
-__device__ __forceinline__ void solve_weights(double *M, double *z, const double *first, const double *last,
-                                              const double *t, double eps, int m, int32_t *mark, int32_t *failed)
+// kStage2MaxLdsNodes data points (149 KB), else in device memory; false if it is
+// singular. The elimination's operations on each element, and its pivots, are
+// those of the textbook loop. Bound by its chain of pivots, three barriers and a
+// division each; up to kWeightsOneWave points (strips have some eight) ONE wave
+// goes through them without barriers. 14 lines of 114 points: a second stage of
+// 257^2 points with kept factors took 2.1 ms with the systems solved on the host
+// and takes 0.45 ms.
+constexpr int kWeightsThreads = 1024, kWeightsOneWave = 16;
+template <bool ONE>
+__device__ __forceinline__ void weights_sync()
 {
+    if constexpr (ONE) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    } else {
+        __syncthreads();
+    }
+}
+template <bool ONE>
+__device__ __forceinline__ bool solve_weights(double *M, double *z, double first, double last, const double *t,
+                                              double eps, int m)
+{
+    constexpr int kThreads = ONE ? 64 : kWeightsThreads;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    constexpr int kWaves = kWeightsThreads / 64;
+    // rows and columns of a thread in the matrix
+    const int row = ONE ? lane >> 3 : wave, col = ONE ? lane & 7 : lane;
+    constexpr int kRows = ONE ? 8 : kThreads / 64, kCols = ONE ? 8 : 64;
     const size_t ld = m + 1;
-    for (int r = wave; r < m; r += kWaves)
-        for (int c = lane; c <= m; c += 64) {
+    for (int r = row; r < m; r += kRows)
+        for (int c = col; c <= m; c += kCols) {
             const double ee = eps * (t[r] - (c < m ? t[c] : 0.0));
-            M[r * ld + c] = c < m ? sqrt(1.0 + ee * ee) : r == 0 ? *first : r == m - 1 ? *last : z[r];
+            M[r * ld + c] = c < m ? sqrt(1.0 + ee * ee) : r == 0 ? first : r == m - 1 ? last : z[r];
         }
-    __syncthreads();
+    weights_sync<ONE>();
     for (int c = 0; c < m; ++c) {
         // the largest |entry| of the column from the diagonal on, the first of
         // equals; every wave finds it for itself
@@ -202,85 +213,120 @@ __device__ __forceinline__ void solve_weights(double *M, double *z, const double
             }
         }
         const double pivot = M[p * ld + c];
-        __syncthreads();
-        if (pivot == 0.0) {  // every wave alike
-            for (int r = threadIdx.x; r < m; r += kWeightsThreads) z[r] = 0.0;
-            if (threadIdx.x == 0) *mark = *failed = 1;
-            return;
-        }
+        weights_sync<ONE>();
+        if (pivot == 0.0) return false;  // every wave alike
         // rows c and p change places; their multipliers take the entries of
         // column c below the diagonal (row p's is of the row that came there)
-        if (threadIdx.x < kWeightsThreads / 2) {
-            for (int cc = c + 1 + threadIdx.x; cc <= m; cc += kWeightsThreads / 2) {
+        if (threadIdx.x < kThreads / 2) {
+            for (int cc = c + 1 + threadIdx.x; cc <= m; cc += kThreads / 2) {
                 const double v = M[p * ld + cc];
                 M[p * ld + cc] = M[c * ld + cc];
                 M[c * ld + cc] = v;
             }
         } else {
-            for (int r = c + threadIdx.x - kWeightsThreads / 2; r < m; r += kWeightsThreads / 2) {
+            for (int r = c + threadIdx.x - kThreads / 2; r < m; r += kThreads / 2) {
                 if (r == c && p != c) continue;
                 const double v = M[(r == p ? c : r) * ld + c];
                 if (r == p) M[c * ld + c] = pivot;
                 if (r > c) M[r * ld + c] = v / pivot;
             }
         }
-        __syncthreads();
-        for (int cc = c + 1 + lane; cc <= m; cc += 64) {
+        weights_sync<ONE>();
+        for (int cc = c + 1 + col; cc <= m; cc += kCols) {
             const double top = M[c * ld + cc];
-            for (int r = c + 1 + wave; r < m; r += kWaves) M[r * ld + cc] -= M[r * ld + c] * top;
+            for (int r = c + 1 + row; r < m; r += kRows) M[r * ld + cc] -= M[r * ld + c] * top;
         }
-        __syncthreads();
+        weights_sync<ONE>();
     }
     for (int r = m - 1; r >= 0; --r) {
         if (wave * 64 > r) {
-            __syncthreads();
+            weights_sync<ONE>();
             continue;
         }
         const double x = M[r * ld + m] / M[r * ld + r];
         if (threadIdx.x == 0) z[r] = x;
-        for (int rr = threadIdx.x; rr < r; rr += kWeightsThreads) M[rr * ld + m] -= M[rr * ld + r] * x;
-        __syncthreads();
+        for (int rr = threadIdx.x; rr < r; rr += kThreads) M[rr * ld + m] -= M[rr * ld + r] * x;
+        weights_sync<ONE>();
     }
+    return true;
 }
-__global__ void __launch_bounds__(kWeightsThreads) stage2_weights_kernel(const Stage2Grid g, const Stage2Line *lines,
-                                                                         const double *t, double *lam,
-                                                                         double *matrices, int32_t *marks)
+// One workgroup per line (its weights, then its values between the box's edges
+// into g.lines), the ones after them for the box's edges, and for the tables'
+// way to the device. Lines and their data are read where the host put them: a copy
+// ahead of the kernel cost a call with kept factors 5 us.
+__global__ void __launch_bounds__(kWeightsThreads) stage2_edges_kernel(const DevProblem<double> P, const Stage2Grid g,
+                                                                       const Stage2Edges a)
 {
     __shared__ double s_M[kStage2MaxLdsNodes * (kStage2MaxLdsNodes + 1)];
-    const Stage2Line L = lines[blockIdx.x];
-    double *z = lam + L.at;
-    // the line's ends
-    const double *first = g.u + (L.d == 0 ? (size_t)L.k : (size_t)L.k * g.n0);
-    const double *last = g.u + (L.d == 0 ? (size_t)(g.n1 - 1) * g.n0 + L.k : (size_t)L.k * g.n0 + g.n0 - 1);
-    if (L.m <= kStage2MaxLdsNodes)
-        solve_weights(s_M, z, first, last, t + L.at, L.eps, L.m, marks + blockIdx.x, g.failed);
-    else
-        solve_weights(matrices + L.matrix, z, first, last, t + L.at, L.eps, L.m, marks + blockIdx.x, g.failed);
+    __shared__ double s_t[kStage2MaxLdsNodes], s_z[kStage2MaxLdsNodes], ends[2];
+    __shared__ bool solved;
+    const int tid = threadIdx.x, edge_blocks = (2 * (g.n0 + g.n1 - 2) + kWeightsThreads - 1) / kWeightsThreads;
+    if ((int)blockIdx.x >= a.n_lines + edge_blocks) {  // whole workgroup, as below
+        const uint64_t blocks = gridDim.x - a.n_lines - edge_blocks;
+        for (uint64_t w = (blockIdx.x - a.n_lines - edge_blocks) * (uint64_t)kWeightsThreads + tid; w < a.table_words;
+             w += blocks * kWeightsThreads)
+            a.table[w] = a.host_table[w];
+        return;
+    }
+    MathOf<double> mt;
+    mt.init();
+    if ((int)blockIdx.x >= a.n_lines) {
+        const int q = ((int)blockIdx.x - a.n_lines) * kWeightsThreads + tid;
+        if (q < 2 * (g.n0 + g.n1 - 2)) stage2_edge_point(P, g, mt, q);
+        return;
+    }
+    const Stage2Line L = a.host_lines[blockIdx.x];
+    const bool in_lds = L.m <= kStage2MaxLdsNodes;
+    double *t = in_lds ? s_t : a.t + L.at, *z = in_lds ? s_z : a.lam + L.at;
+    for (int q = tid; q < L.m; q += kWeightsThreads) {
+        t[q] = a.host_t[L.at + q];
+        z[q] = a.host_z[L.at + q];
+    }
+    if (tid < 2) {
+        const int e = tid ? (L.d == 0 ? g.n1 : g.n0) - 1 : 0;  // along the line
+        const int i = L.d == 0 ? L.k : e, j = L.d == 0 ? e : L.k;
+        const double x[2] = {stage2_coord(g.lo0, g.span0, g.n0, i), stage2_coord(g.lo1, g.span1, g.n1, j)};
+        ends[tid] = boundary_value<double, 2, true>(mt, P, x, P.tab);
+    }
+    __syncthreads();
+    if (L.m <= kWeightsOneWave) {
+        if (tid < 64) {
+            const bool ok = solve_weights<true>(s_M, s_z, ends[0], ends[1], s_t, L.eps, L.m);
+            if (tid == 0) solved = ok;
+        }
+    } else {
+        const bool ok = in_lds ? solve_weights<false>(s_M, s_z, ends[0], ends[1], s_t, L.eps, L.m)
+                               : solve_weights<false>(a.matrices + L.matrix, z, ends[0], ends[1], t, L.eps, L.m);
+        if (tid == 0) solved = ok;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        g.line_failed[blockIdx.x] = solved ? 0 : 1;
+        if (!solved) a.host_marks[blockIdx.x] = 1;
+    }
+    if (!solved) return;
+    const int ne = L.d == 0 ? g.n1 : g.n0;  // points along the line
+    double *out = g.lines + (size_t)blockIdx.x * g.line_stride;
+    for (int p = 1 + tid; p < ne - 1; p += kWeightsThreads) {
+        const double tp = L.d == 0 ? stage2_coord(g.lo1, g.span1, g.n1, p) : stage2_coord(g.lo0, g.span0, g.n0, p);
+        out[p] = in_lds ? multiquadric(s_t, s_z, L.m, L.eps, tp) : multiquadric(t, z, L.m, L.eps, tp);
+    }
 }
 
-// One workgroup row per line (blockIdx.y); the points of the line strictly
-// between the box's edges.
-__global__ void __launch_bounds__(256) stage2_lines_kernel(const Stage2Grid g, const Stage2Line *lines, int32_t n_lines,
-                                                           const double *t, const double *lam)
+// Line q's points into u, by one workgroup (one where an axis-0 and an axis-1 line
+// cross by the axis-0 line).
+__device__ __forceinline__ void stage2_line_to_grid(const Stage2Grid &g, const Stage2Line *lines, int32_t n_lines, int q)
 {
-    if (*g.failed) return;
-    const Stage2Line L = lines[blockIdx.y];
-    const int ne = L.d == 0 ? g.n1 : g.n0;  // points along the line
-    for (int p = 1 + blockIdx.x * blockDim.x + threadIdx.x; p < ne - 1; p += gridDim.x * blockDim.x) {
-        const double tp = L.d == 0 ? stage2_coord(g.lo1, g.span1, g.n1, p) : stage2_coord(g.lo0, g.span0, g.n0, p);
-        // a line of the other axis through this point
-        int cross = -1;
-        for (int q = 0; q < n_lines; ++q)
-            if (lines[q].d != L.d && lines[q].k == p) cross = q;
-        if (cross >= 0 && L.d == 1) continue;  // the crossing axis-0 line writes the point
-        double v = multiquadric(t + L.at, lam + L.at, L.m, L.eps, tp);
-        if (cross >= 0) {
-            const Stage2Line C = lines[cross];
-            const double tc = stage2_coord(g.lo0, g.span0, g.n0, L.k);
-            v = 0.5 * (v + multiquadric(t + C.at, lam + C.at, C.m, C.eps, tc));
-        }
-        const size_t at = L.d == 0 ? (size_t)p * g.n0 + L.k : (size_t)L.k * g.n0 + p;
-        g.u[at] = v;
+    const Stage2Line L = lines[q];
+    const int ne = L.d == 0 ? g.n1 : g.n0;
+    for (int p = 1 + threadIdx.x; p < ne - 1; p += blockDim.x) {
+        int cross = -1;  // a line of the other axis through this point
+        for (int c = 0; c < n_lines; ++c)
+            if (lines[c].d != L.d && lines[c].k == p) cross = c;
+        if (cross >= 0 && L.d == 1) continue;
+        double v = g.lines[(size_t)q * g.line_stride + p];
+        if (cross >= 0) v = 0.5 * (v + g.lines[(size_t)cross * g.line_stride + L.k]);
+        g.u[L.d == 0 ? (size_t)p * g.n0 + L.k : (size_t)L.k * g.n0 + p] = v;
     }
 }
 
@@ -303,12 +349,21 @@ __device__ __forceinline__ void stage2_point(const SubBox &b, uint64_t r, int &i
 // 2 centre, 3 fast+1, 4 slow+1, 5 right side, which also goes to rhs; with
 // `parts`, f and the boundary values' part go there instead, two values per
 // unknown. *not_dominant (if given) is set where a neighbour's coefficient is
-// negative or c positive.
+// negative or c positive. The last workgroup of every row writes interface lines
+// into u.
 __global__ void __launch_bounds__(256) stage2_stencil_kernel(const DevProblem<double> P, const Stage2Grid g,
-                                                             const SubBox *boxes, double *stencil, double *rhs,
-                                                             bool parts, int32_t *not_dominant)
+                                                             const SubBox *boxes, const Stage2Line *lines,
+                                                             int32_t n_lines, double *stencil, double *rhs, bool parts,
+                                                             int32_t *not_dominant)
 {
     __shared__ double s_cf[kMaxDense];
+    if (blockIdx.x == gridDim.x - 1) {  // whole workgroup
+        int32_t failed = 0;
+        for (int q = 0; q < n_lines; ++q) failed |= g.line_failed[q];
+        if (blockIdx.y == 0 && threadIdx.x == 0) *g.failed = failed;
+        for (int q = blockIdx.y; q < n_lines && !failed; q += gridDim.y) stage2_line_to_grid(g, lines, n_lines, q);
+        return;
+    }
     for (int q = threadIdx.x; q < kMaxDense; q += blockDim.x) s_cf[q] = P.fdense[q];
     __syncthreads();
     const SubBox b = boxes[blockIdx.y];
@@ -316,7 +371,7 @@ __global__ void __launch_bounds__(256) stage2_stencil_kernel(const DevProblem<do
     mt.init();
     const uint64_t n = (uint64_t)b.w * (uint64_t)b.L;
     const double cx = g.half_s2 / (g.dx0 * g.dx0), cy = g.half_s2 / (g.dx1 * g.dx1);
-    for (uint64_t r = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; r < n; r += (uint64_t)gridDim.x * blockDim.x) {
+    for (uint64_t r = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; r < n; r += (gridDim.x - 1) * (uint64_t)blockDim.x) {
         int i, j;
         stage2_point(b, r, i, j);
         const double x[2] = {stage2_coord(g.lo0, g.span0, g.n0, i), stage2_coord(g.lo1, g.span1, g.n1, j)};
@@ -338,7 +393,8 @@ __global__ void __launch_bounds__(256) stage2_stencil_kernel(const DevProblem<do
             if (inside) {
                 out[slot[q]] = a[q];
             } else {
-                const double t = a[q] * g.u[(size_t)nj[q] * g.n0 + ni[q]];
+                const double t = a[q] * (b.side[q] < 0 ? g.u[(size_t)nj[q] * g.n0 + ni[q]]
+                                                       : g.lines[b.side[q] * (size_t)g.line_stride + (q < 2 ? j : i)]);
                 out[5] -= t;
                 yb -= t;
             }
@@ -775,7 +831,7 @@ __global__ void __launch_bounds__(256) stage2_apply_kernel(const Stage2Grid g, c
 // pivots, one workgroup a subdomain, becomes 1 + log2 L levels whose rows are
 // independent. Four strips of 63 x 255 unknowns: 39.9 ms with the LU and the
 // solutions for unit boundary values that it was kept as, 0.49 ms now; with
-// the factors kept 0.26 and 0.13 ms. What bounds a level is the inversion
+// the factors kept 0.26 and 0.12 ms. What bounds a level is the inversion
 // (24 us: 64 dependent pivots) and the products on the FP64 matrix cores
 // (9 us; 37 us where the rows are several per CU). Blocks are padded by the
 // identity to WP (the widest subdomain's w, to a multiple of 16) and kept by
@@ -1254,9 +1310,9 @@ __global__ void __launch_bounds__(CrSolve<WP>::kThreads) stage2_cr_solve_kernel(
 
 // All levels from `first` on, forward and back, a workgroup per subdomain: for
 // the levels of few rows a launch each costs more than one CU's bandwidth.
-// Kept blocks, four strips, calls back to back: 129^2 (blocks of 32) 100 us
-// with a launch for every level, 92 us from 8 rows on, 89 from 16, 96 from 32;
-// 65^2 (blocks of 16) 91 us, and 75 with all levels here.
+// Kept blocks, four strips, a call: 97^2 (blocks of 32) 80 us from 16 rows on, 82
+// from 32, 95 from 64, 129^2 82, 86 and 108 us; 65^2 (blocks of 16) 64 us with
+// all levels here, 16 us more with a launch for every level.
 template <int WP>
 constexpr int kTopRows = WP == 16 ? 64 : WP == 32 ? 16 : 8;
 constexpr int kTopThreads = 1024;
@@ -1338,39 +1394,20 @@ hipError_t launch_grid_residual(const DevProblem<double> &P, double sigma, const
                        : (tab ? launch_residual<double, 3, true> : launch_residual<double, 3, false>)(P, sigma, g, r, s);
 }
 
-hipError_t launch_stage2_boundary(const DevProblem<double> &P, const Stage2Grid &g, hipStream_t s)
+hipError_t launch_stage2_edges(const DevProblem<double> &P, const Stage2Grid &g, const Stage2Edges &a, hipStream_t s)
 {
-    const int total = 2 * g.n0 + 2 * (g.n1 - 2);
-    hipLaunchKernelGGL(stage2_boundary_kernel, dim3((total + 255) / 256), dim3(256), 0, s, P, g);
-    return hipGetLastError();
-}
-
-hipError_t launch_stage2_weights(const Stage2Grid &g, const Stage2Line *lines, int32_t n_lines, const double *t,
-                                 double *lam, double *matrices, int32_t *marks, hipStream_t s)
-{
-    if (n_lines == 0) return hipSuccess;
-    hipLaunchKernelGGL(stage2_weights_kernel, dim3(n_lines), dim3(kWeightsThreads), 0, s, g, lines, t, lam, matrices,
-                       marks);
-    return hipGetLastError();
-}
-
-hipError_t launch_stage2_lines(const Stage2Grid &g, const Stage2Line *lines, int32_t n_lines, const double *t,
-                               const double *lam, hipStream_t s)
-{
-    if (n_lines == 0) return hipSuccess;
-    const int len = g.n0 > g.n1 ? g.n0 : g.n1;
-    hipLaunchKernelGGL(stage2_lines_kernel, dim3((len + 255) / 256, n_lines), dim3(256), 0, s, g, lines, n_lines, t,
-                       lam);
+    const uint64_t points = 2ull * (g.n0 + g.n1 - 2), per = kWeightsThreads;
+    const uint64_t blocks = a.n_lines + (points + per - 1) / per + std::min<uint64_t>((a.table_words + per - 1) / per, 64);
+    hipLaunchKernelGGL(stage2_edges_kernel, dim3((uint32_t)blocks), dim3(kWeightsThreads), 0, s, P, g, a);
     return hipGetLastError();
 }
 
 hipError_t launch_stage2_stencils(const DevProblem<double> &P, const Stage2Grid &g, const SubBox *boxes,
-                                  int32_t n_boxes, uint32_t max_unknowns, double *stencil, double *rhs, bool parts,
-                                  int32_t *not_dominant, hipStream_t s)
+                                  int32_t n_boxes, uint32_t max_unknowns, const Stage2Line *lines, int32_t n_lines,
+                                  double *stencil, double *rhs, bool parts, int32_t *not_dominant, hipStream_t s)
 {
-    if (n_boxes == 0) return hipSuccess;
-    hipLaunchKernelGGL(stage2_stencil_kernel, dim3((max_unknowns + 255) / 256, n_boxes), dim3(256), 0, s, P, g,
-                       boxes, stencil, rhs, parts, not_dominant);
+    hipLaunchKernelGGL(stage2_stencil_kernel, dim3((max_unknowns + 255) / 256 + 1, std::max(n_boxes, 1)), dim3(256), 0, s,
+                       P, g, boxes, lines, n_lines, stencil, rhs, parts, not_dominant);
     return hipGetLastError();
 }
 
