@@ -132,8 +132,9 @@ typedef struct {
  * context's entry for its (precision, dim, estimator) group, set by
  * pdd_autotune or pdd_set_tuning, else the default {256, occupancy, 64, 0,
  * 0, 0}; fields left 0 in a given tuning take the default. Launches of at most
- * 400,000 paths have a shape of their own. Results never depend on the launch
- * shape. */
+ * 400,000 paths (FP64 with a tabulated drift: 65,536, in the allocation-free
+ * solve 200,000 in 2D and 100,000 in 3D) have a shape of their own. Results
+ * never depend on the launch shape. */
 typedef struct {
     int32_t block;        /* threads per workgroup: 64, 128 or 256 */
     int32_t blocks_per_cu;/* persistent workgroups per compute unit */

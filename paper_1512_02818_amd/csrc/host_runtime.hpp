@@ -81,8 +81,20 @@ inline uint32_t refill_mask(const pdd_tuning &t)
 // most lanes idle for most of the launch. Measured, group walk against one
 // path per lane and a hand-over (18 nodes, h = 1e-3): 180,000 paths 0.44 and
 // 0.54 ms in FP32 2D, 0.65 and 0.82 ms in FP64; 360,000: 0.62 and 0.78, 1.06
-// and 1.09; 540,000: 0.81 and 0.86, 1.44 and 1.32.
+// and 1.09; 540,000: 0.81 and 0.86, 1.44 and 1.32. A step of FP64 walks with a
+// tabulated drift is mostly the gather of it, which the group walk does twice
+// (phases 2 and 3): 20 nodes of the paper's example on 513^2 grids 2.4 and 2.5 ms at
+// 60,000 paths, 3.3 and 3.0 at 100,000, 9.3 and 5.0 at 399,000; on 129^2 1.9 and
+// 2.0, 2.6 and 2.4, 7.3 and 4.2; 3D on 33^3 2.6 and 2.7, 3.5 and 3.1, 9.7 and 4.6.
+// Without a buffer for the hand-over (pdd_solve_nodes_noalloc) the lines cross
+// later: 513^2 5.7 and 5.1 ms at 220,000, 4.3 and 4.6 at 150,000; 3D 3.5 and 3.3
+// at 100,000.
 constexpr uint64_t kGroupDirectSlots = 400000;
+inline uint64_t group_direct_slots(bool fp64, bool tabulated_drift, bool hand_over, int dim)
+{
+    if (!fp64 || !tabulated_drift) return kGroupDirectSlots;
+    return hand_over ? 65536 : dim == 2 ? 200000 : 100000;
+}
 // Paths handed over by a launch, at most (their buffer: 33 MB in FP32 3D). The
 // items of a batch share it: 64 uneven problems take 140 ms with it and 180 ms
 // with half of it, no less with twice of it.

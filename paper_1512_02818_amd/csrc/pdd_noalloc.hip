@@ -189,7 +189,7 @@ pdd_status run_noalloc(pdd_ctx *ctx, const HostItem &it, const pdd_tuning &tune,
         const uint64_t blocks_needed = ((len + 63) / 64 * 64 + tune.block - 1) / tune.block;
         const int grid = (int)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)ctx->n_cu * bpc, blocks_needed));
         L.grab = ticket_size(tune, len, (uint64_t)grid * (tune.block / 64));
-        if (len <= kGroupDirectSlots) {  // (nothing is handed over here: there is no buffer for it)
+        if (len <= group_direct_slots(sizeof(T) == 8, (P.tab & 7u) != 0, false, D)) {  // (nothing is handed over here: there is no buffer for it)
             HIP_TRY((launch_path_kernel_group<T, D, kEstPlain>(L, d_item, d_prob, group_grid<T>(ctx, len), kind, s)));
         } else if (one) {
             OneItemArgs<T> A;

@@ -659,9 +659,11 @@ pdd_status run_group(pdd_ctx *ctx, std::vector<HostItem *> &items, const pdd_tun
     // a wave has the next item's paths to go on with (64 uneven problems: 142
     // ms at 16, 150 ms at 32; one item of 360,000 FP64 paths: 8.5 and 7.4 ms)
     const uint32_t tail_max = n_k > 1 ? 16 : 32;
+    const bool tabulated_drift = std::any_of(items.begin(), items.end(), [](HostItem *i) { return (i->prob->pd.tab & 7u) != 0; });
+    const uint64_t direct_slots = group_direct_slots(sizeof(T) == 8, tabulated_drift, true, D);
     // the longest launch decides whether paths are handed over at all; without
     // memory for them they end where they began
-    uint64_t tail_cap = std::min(per_launch, total) > kGroupDirectSlots ? std::min<uint64_t>(total, kTailEntries) : 0;
+    uint64_t tail_cap = std::min(per_launch, total) > direct_slots ? std::min<uint64_t>(total, kTailEntries) : 0;
     pdd_status st;
     if (tail_cap && ensure(ctx, ctx->tail, tail_cap * sizeof(TailState<T, D>))) {
         tail_cap = 0;
@@ -924,7 +926,7 @@ pdd_status run_group(pdd_ctx *ctx, std::vector<HostItem *> &items, const pdd_tun
         L.refill_mask = refill_mask<D>(tune);
         L.seg = reinterpret_cast<const uint32_t *>(dv + off_seg) + 2 * ctr_at[launch];
         if (timed && b == 0) HIP_TRY(hipEventRecord(ev.first, s));
-        if (len <= kGroupDirectSlots) {  // few paths: walked by groups of lanes from the start
+        if (len <= direct_slots) {  // few paths: walked by groups of lanes from the start
             HIP_TRY((launch_path_kernel_group<T, D, EST>(L, d_items, d_probs, group_grid<T>(ctx, len), kind, s)));
         } else {
             const uint64_t waves_needed = (len + 63) / 64;
