@@ -34,12 +34,13 @@ def hipcc() -> str:
 
 
 PROBE_LIB = os.path.join(HERE, "libpdd_probe.so")
-PROBE_SOURCES = ["issue_probe.hip"]
+PROBE_SOURCES = ["issue_probe.hip", "math_probe.hip"]
 
 
 def build_probe(verbose: bool = False) -> str:
     """Compile the VALU issue-rate probe (the benchmark's --issue-rates mode)
-    into its own library, libpdd_probe.so."""
+    and the FP64 functions' probe (tests) into their own library,
+    libpdd_probe.so."""
     srcs = [os.path.join(HERE, "csrc", s) for s in PROBE_SOURCES]
     tmp = PROBE_LIB + ".tmp"
     cmd = [hipcc()] + FLAGS + ["-shared"] + srcs + ["-o", tmp]
@@ -55,7 +56,7 @@ def build_probe(verbose: bool = False) -> str:
 
 def build(verbose: bool = False) -> str:
     """Compile every HIP source into libpdd.so (always recompiles; the sources
-    at the same time), and the issue-rate probe into libpdd_probe.so."""
+    at the same time), and the probes into libpdd_probe.so."""
     tmp = LIB + ".tmp"
     with tempfile.TemporaryDirectory() as objs:
         def run(cmd):

@@ -225,9 +225,13 @@ struct Arith<float> {
 // are bound by vector issue, and these functions are most of a step: 18 nodes
 // x 200,000 paths on the unit square (h = 1e-3) take 6.6 ms, 9.1 ms with the
 // library's functions; 1,792 nodes x 256 paths on [0, 4]^2 16.4 ms, before
-// 24.3 ms. Polynomials are minimax in relative
-// error (Remez exchange in 50 digits), so each function is within 1.2 units in
-// the last place of its argument's exact value.
+// 24.3 ms. Polynomials are minimax in relative error (Remez exchange in 50
+// digits). Against the exact value of their argument, at most, in units in the
+// last place: the logarithm 0.81, the square root 0.51, the exponential 0.89, sine
+// and cosine of a turn's part 1.82 (its product with 2 pi is rounded); sine and
+// cosine of a trig term's argument 0.87 units of 2^-53, absolute (and in the last
+// place up to pi / 4; next to a zero after many turns the relative error is larger,
+// as pi / 2 has two parts).
 // Their coefficients come from constant memory by scalar loads at each use:
 // as literals the compiler keeps all of them for the whole walk loop in scalar
 // registers, which do not hold them, and each use then reads its spilled
@@ -307,7 +311,8 @@ struct Fp64Math {
         sincos_octant(m, r, madd(n, t[2], a - r), s, c);
         quadrant((uint32_t)(int32_t)n, s, c);
     }
-    // -2 ln((w + 1/2) 2^-32). ln(1 + f) = 2 atanh(s), s = f / (2 + f), is
+    // -2 ln((w + 1/2) 2^-32), arranged as in Sun's fdlibm (the coefficients are not
+    // its): ln(1 + f) = 2 atanh(s), s = f / (2 + f), is
     // f - f^2 / 2 + s (f^2 / 2 + z L(z)), z = s^2, which keeps the relative
     // accuracy near 1 (L to 2^-59.5 for sqrt(1/2) <= 1 + f < sqrt(2)).
     __device__ static __forceinline__ double minus_two_ln(uint32_t w)
