@@ -385,15 +385,21 @@ struct Stage2Resp {
     int32_t nb, pad;
 };
 constexpr int kStage2MaxBoundaryRows = 4096;
+// Subdomains first .. first + n - 1, with blocks of wp x wp (wp a multiple of 16);
+// their largest L.
+struct Stage2Run {
+    int32_t first, n, max_L, wp;
+};
 // What launch_stage2_solve is to do after the stencils: factor (unless
 // `factored`: factor, and lmul, already hold the factors of these subdomains'
 // matrices) and solve.
 struct Stage2Plan {
     bool factored;
-    // block cyclic reduction: one entry per subdomain (device), the largest L,
-    // the largest w rounded up to a multiple of 16
+    // block cyclic reduction: one entry per subdomain (device), and the runs of
+    // subdomains with blocks of one size
     const Stage2Cr *cr_tab;
-    int32_t max_L, wp;
+    Stage2Run runs[4];
+    int32_t n_runs;
     // or, with cr_tab null, banded LU: factor has unknowns x (kStage2MaxBand +
     // 2) doubles, lmul unknowns x kStage2MaxBand; then either the right side is
     // substituted (resp_tab null), or f's response column and the boundary

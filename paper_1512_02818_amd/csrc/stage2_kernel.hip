@@ -834,7 +834,7 @@ __global__ void __launch_bounds__(256) stage2_apply_kernel(const Stage2Grid g, c
 // the factors kept 0.26 and 0.12 ms. What bounds a level is the inversion
 // (24 us: 64 dependent pivots) and the products on the FP64 matrix cores
 // (9 us; 37 us where the rows are several per CU). Blocks are padded by the
-// identity to WP (the widest subdomain's w, to a multiple of 16) and kept by
+// identity to WP (a multiple of 16, the same for a run of subdomains) and kept by
 // column: D (D^-1 once eliminated), P, Q of every row (D's rounding in P's place
 // before), and M, N and the new A,
 // C of every (row, level); level 0, whose A and C are diagonal, has no P, Q, M
@@ -1343,40 +1343,43 @@ __global__ void __launch_bounds__(kTopThreads) stage2_cr_top_kernel(const Stage2
 }
 
 template <int WP>
-hipError_t launch_cyclic_reduction(const Stage2Grid &g, const SubBox *boxes, int32_t n_boxes, const double *stencil,
+hipError_t launch_cyclic_reduction(const Stage2Run &run, const Stage2Grid &g, const SubBox *all, const double *stencil,
                                    const Stage2Plan &plan, hipStream_t s)
 {
+    const SubBox *boxes = all + run.first;
+    const Stage2Cr *tab = plan.cr_tab + run.first;
+    const int max_L = run.max_L;
     int levels = 0;
-    while ((1 << levels) <= plan.max_L) ++levels;
-    const auto odd = [&](int l) { return dim3((unsigned)(((plan.max_L >> l) + 1) / 2), n_boxes); };
-    const auto even = [&](int l, int parts) { return dim3((unsigned)(plan.max_L >> (l + 1)), n_boxes, parts); };
+    while ((1 << levels) <= max_L) ++levels;
+    const auto odd = [&](int l) { return dim3((unsigned)(((max_L >> l) + 1) / 2), run.n); };
+    const auto even = [&](int l, int parts) { return dim3((unsigned)(max_L >> (l + 1)), run.n, parts); };
     hipError_t e = hipSuccess;
     for (int l = 0; l < levels && !plan.factored; ++l) {
         const auto eliminate = l == 0 ? stage2_cr_eliminate_kernel<WP, true> : stage2_cr_eliminate_kernel<WP, false>;
-        hipLaunchKernelGGL(eliminate, odd(l), dim3(kCrThreads), 0, s, boxes, plan.cr_tab, stencil, plan.factor, l);
+        hipLaunchKernelGGL(eliminate, odd(l), dim3(kCrThreads), 0, s, boxes, tab, stencil, plan.factor, l);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if (l + 1 == levels) break;
         if (l == 0)
             hipLaunchKernelGGL((stage2_cr_first_update_kernel<WP>), even(0, 1), dim3(kCrThreads), 0, s, boxes,
-                               plan.cr_tab, stencil, plan.factor);
+                               tab, stencil, plan.factor);
         else
-            hipLaunchKernelGGL((stage2_cr_update_kernel<WP>), even(l, 3), dim3(kCrThreads), 0, s, boxes, plan.cr_tab,
+            hipLaunchKernelGGL((stage2_cr_update_kernel<WP>), even(l, 3), dim3(kCrThreads), 0, s, boxes, tab,
                                plan.factor, l);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     int top = 0;
-    while ((plan.max_L >> top) >= kTopRows<WP>) ++top;
+    while ((max_L >> top) >= kTopRows<WP>) ++top;
     for (int l = 0; l < top; ++l) {
         hipLaunchKernelGGL((stage2_cr_solve_kernel<WP, true>), even(l, 1), dim3(CrSolve<WP>::kThreads), 0, s, g, boxes,
-                           plan.cr_tab, stencil, plan.factor, plan.rhs, l);
+                           tab, stencil, plan.factor, plan.rhs, l);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(stage2_cr_top_kernel<WP>, dim3(n_boxes), dim3(kTopThreads), 0, s, g, boxes, plan.cr_tab, stencil,
+    hipLaunchKernelGGL(stage2_cr_top_kernel<WP>, dim3(run.n), dim3(kTopThreads), 0, s, g, boxes, tab, stencil,
                        plan.factor, plan.rhs, top);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     for (int l = top - 1; l >= 0; --l) {
         hipLaunchKernelGGL((stage2_cr_solve_kernel<WP, false>), odd(l), dim3(CrSolve<WP>::kThreads), 0, s, g, boxes,
-                           plan.cr_tab, stencil, plan.factor, plan.rhs, l);
+                           tab, stencil, plan.factor, plan.rhs, l);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     return hipSuccess;
@@ -1439,12 +1442,16 @@ hipError_t launch_stage2_solve(const Stage2Grid &g, const SubBox *boxes,
                            plan.resp_tab, plan.rb, plan.resp);
         return hipGetLastError();
     }
-    switch (plan.wp) {
-        case 16: return launch_cyclic_reduction<16>(g, boxes, n_boxes, stencil, plan, s);
-        case 32: return launch_cyclic_reduction<32>(g, boxes, n_boxes, stencil, plan, s);
-        case 48: return launch_cyclic_reduction<48>(g, boxes, n_boxes, stencil, plan, s);
-        default: return launch_cyclic_reduction<64>(g, boxes, n_boxes, stencil, plan, s);
+    for (int q = 0; q < plan.n_runs && e == hipSuccess; ++q) {
+        const Stage2Run &run = plan.runs[q];
+        switch (run.wp) {
+            case 16: e = launch_cyclic_reduction<16>(run, g, boxes, stencil, plan, s); break;
+            case 32: e = launch_cyclic_reduction<32>(run, g, boxes, stencil, plan, s); break;
+            case 48: e = launch_cyclic_reduction<48>(run, g, boxes, stencil, plan, s); break;
+            default: e = launch_cyclic_reduction<64>(run, g, boxes, stencil, plan, s); break;
+        }
     }
+    return e;
 }
 
 }  // namespace pdd

@@ -151,3 +151,29 @@ def test_strips(w, rows, axis, laplace):
                          lambda x, y: (B[0][0] * x, B[1][1] * y), lambda x, y: pd["c_a"] + pd["c_b"] * (x * x + y * y))
         print(f"{w} x {rows}, axis {axis}, {laplace}: {err:.1e}, banded LU {lu:.1e}", flush=True)
         assert err <= 2 * lu + 4 * np.finfo(float).eps
+
+
+def test_sizes_apart():
+    """Strips of 63 columns and of 1, 5, 17 and 40 beside each other, 511 rows: 2.1 GB with blocks of one size, so
+    each of the four sizes (16, 32, 48, 64) has its own."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    widths = [1, 63, 5, 1, 40, 17] + [1] * 12
+    edges = np.cumsum([0] + [w + 1 for w in widths])
+    rows, lines = 511, edges[1:-1]
+    n = (int(edges[-1]) + 1, rows + 2)
+    pd = dict(W.unit_square_problem(seed=0), lo=[0.0, 0.0], hi=[(m - 1) * DX for m in n])
+    nodes = np.array([[i * DX, y] for i in lines for y in (0.4, 1.1, 1.7)])
+    vals = W.manufactured_u(pd, nodes) + np.random.default_rng(2).normal(scale=0.01, size=len(nodes))
+    ctx = pdd.Context(0)
+    prob = pdd.Problem(ctx, pd)
+    got = [pdd.stage2(prob, n, [[i * DX for i in lines], []], nodes, vals, 3.0).cpu().numpy() for _ in range(2)]
+    prob.close()
+    ctx.close()
+    assert got[0].tobytes() == got[1].tobytes()
+    B = pd["B"]
+    for q in (0, 1, 2, 4, 5, 6, 17):
+        err, lu = errors(pd, got[0], (0.0, 0.0), (DX, DX), (int(edges[q]), int(edges[q + 1]), 0, rows + 1),
+                         lambda x, y: (B[0][0] * x, B[1][1] * y), lambda x, y: pd["c_a"] + pd["c_b"] * (x * x + y * y))
+        print(f"width {widths[q]}: {err:.1e}, banded LU {lu:.1e}", flush=True)
+        assert err <= 2 * lu + 4 * np.finfo(float).eps
