@@ -311,8 +311,12 @@ def _stream_handle(stream):
     import torch
     if stream is None:
         # the current stream's handle without the object that
-        # torch.cuda.current_stream() makes for it (3 us of a call)
-        return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+        # torch.cuda.current_stream() makes for it (3 us of a call), where this
+        # build of torch gives it
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is not None:
+            return C.c_void_p(raw(torch.cuda.current_device()))
+        stream = torch.cuda.current_stream()
     return C.c_void_p(stream.cuda_stream)
 
 
