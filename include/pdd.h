@@ -605,7 +605,10 @@ typedef struct {
     uint64_t failed;                          /* ended with an error other than cancellation */
     uint64_t queued, inflight, epochs;
     uint64_t nodes_completed, path_steps;
-    uint64_t mem_in_use, mem_peak, mem_fixed; /* bytes: admitted requests; their peak; record scratch */
+    uint64_t mem_in_use, mem_peak, mem_fixed; /* bytes: admitted requests; their peak; record scratch
+                                                 (each epoch in flight also has a buffer of at
+                                                 most 42 MB for paths handed between kernels, and
+                                                 its tables, which the budget does not count) */
     double p50_ms, p99_ms;                    /* latency percentiles of every request not shed (above) */
     double mean_ms;                           /* mean latency of completed requests */
     double wall_s;                            /* first submit to last completion */

@@ -82,10 +82,18 @@ extern "C" pdd_status pdd_grid_residual(pdd_problem *problem, const pdd_grid *u,
     HIP_TRY(hipSetDevice(problem->ctx->device));
     // the source is evaluated at the grid's points, which may lie far outside
     // the problem's box: their arguments choose the trig functions
-    pdd::DevProblem<double> pd = problem->pd;
-    pd.big_trig = !(pdd::trig_revolutions(problem->desc, u->lo, u->hi) <= pdd::kFp64TrigRevolutions);
-    const hipError_t e = pdd::launch_grid_residual(pd, problem->desc.sigma, u, resid,
-                                                   static_cast<hipStream_t>(stream));
+    const int32_t big_trig = !(pdd::trig_revolutions(problem->desc, u->lo, u->hi) <= pdd::kFp64TrigRevolutions);
+    const auto launch = [&](const pdd::DevProblem<double> &pd) {
+        return pdd::launch_grid_residual(pd, problem->desc.sigma, u, resid, static_cast<hipStream_t>(stream));
+    };
+    hipError_t e;
+    if (big_trig == problem->pd.big_trig) {
+        e = launch(problem->pd);
+    } else {
+        pdd::DevProblem<double> pd = problem->pd;
+        pd.big_trig = big_trig;
+        e = launch(pd);
+    }
     if (e != hipSuccess) return fail(PDD_E_HIP, "grid residual launch: %s", hipGetErrorString(e));
     return PDD_OK;
 }

@@ -32,6 +32,7 @@ namespace {
 // nodes x 1,000 correction paths on the unit square 0.75 and 0.18 ms, x 10,000
 // plain FP64 paths 2.0 and 0.64 ms, 64 uneven problems of 4.0e6 paths 295 and
 // 141 ms, 1,792 nodes x 8,192 long walks 322 and 293 ms.
+
 // Broadcast within a quad: its lane g's value (quad_perm g, g, g, g).
 template <int g>
 __device__ __forceinline__ int quad32(int v)

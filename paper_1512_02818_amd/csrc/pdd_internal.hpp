@@ -304,12 +304,12 @@ const void *path_kernel_symbol(bool one, int kind);
 // points: a record of n_grids x 2^D values per cell, grid c's at c 2^D.
 template <class T, int D>
 hipError_t launch_grid_cells(const T *const *data, int n_grids, const int32_t *n, T *cells, hipStream_t s);
-// One grid, converted from S to T, into records of `stride` values per cell, at
-// offset `off` in each.
 // out[p stride + off] = data[p] converted from S to T, p < n_points.
 template <class S, class T>
 hipError_t launch_grid_points_strided(const S *data, uint64_t n_points, T *out, uint32_t stride, uint32_t off,
                                       hipStream_t s);
+// One grid, converted from S to T, into records of `stride` values per cell, at
+// offset `off` in each.
 template <class S, class T, int D>
 hipError_t launch_grid_cells_strided(const S *data, const int32_t *n, T *cells, uint32_t stride, uint32_t off,
                                      hipStream_t s);

@@ -45,6 +45,9 @@ constexpr size_t kNaOffSeg = kNaOffFinal + 256;
 constexpr size_t kNaOffCounter = kNaOffSeg + 256;
 constexpr size_t kNaEnd = kNaOffCounter + 256;
 static_assert(kNaEnd <= PDD_NOALLOC_SCRATCH_BYTES, "scratch layout exceeds the array");
+// (a launch's reduction is split where nodes have more than a chunk of paths)
+static_assert(reduce_partials(kNaRecSlots, (kNaRecSlots - 1) / (kReduceChunk + 1) + 2) * sizeof(NodeAcc) <= kNaPartBytes,
+              "chunk partials of a launch");
 static_assert(sizeof(ItemDesc<double>) <= 1024 && sizeof(ItemDesc<float>) <= 1024, "item slot");
 static_assert(sizeof(DevProblem<double>) <= 8192 && sizeof(FinalItem) <= 256, "problem / final slots");
 static_assert(kNaOffAcc % 256 == 0 && kNaOffNodes % 256 == 0 && kNaOffPart % 256 == 0, "alignment");
@@ -90,9 +93,6 @@ pdd_status run_noalloc(pdd_ctx *ctx, const HostItem &it, const pdd_tuning &tune,
     const uint32_t n = (uint32_t)it.n_nodes;
     uint64_t per_launch = std::min<uint64_t>(kNaRecSlots, std::max<uint64_t>(total, 1));
     if (tune.max_launch_paths > 0) per_launch = std::min<uint64_t>(per_launch, (uint64_t)tune.max_launch_paths);
-    // chunk partials of one launch, known before anything is enqueued
-    if (N > kReduceChunk && reduce_partials(per_launch, (per_launch - 1) / N + 2) * sizeof(NodeAcc) > kNaPartBytes)
-        return fail(PDD_E_INTERNAL, "no-alloc scratch: chunk partials do not fit");
     double *sc_phi = reinterpret_cast<double *>(base + kNaOffPhi);
     uint32_t *sc_steps = reinterpret_cast<uint32_t *>(base + kNaOffSteps);
     NodeAcc *acc = reinterpret_cast<NodeAcc *>(base + kNaOffAcc);

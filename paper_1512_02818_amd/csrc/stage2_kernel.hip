@@ -8,10 +8,6 @@
 namespace pdd {
 namespace {
 
-// Residual r = f - ((1/2) sigma^2 Lap u + b.grad u + c u) of a gridded u at
-// its points, b, c, f from the problem (FP64), the derivatives of u by
-// second-order differences (central inside; three-point one-sided first and
-// four-point one-sided second derivatives at the ends of each axis).
 // First and second derivative along one axis at point p, whose index there is
 // a of n (stride st): central inside, one-sided at the two ends.
 template <class S, class I>
@@ -32,6 +28,10 @@ __device__ __forceinline__ void fd(const S *__restrict__ u, I p, double u0, I st
     second = n2 / (dx * dx);
 }
 
+// Residual r = f - ((1/2) sigma^2 Lap u + b.grad u + c u) of a gridded u at
+// its points, b, c, f from the problem (FP64), the derivatives of u by
+// second-order differences (central inside; three-point one-sided first and
+// four-point one-sided second derivatives at the ends of each axis).
 // I: the type that holds a point's number (a division by a 64-bit grid size
 // costs more than the derivatives). TAB: the problem has tabulated coefficients
 // or trig arguments that need the library's reduction. Bound by the source's
