@@ -169,7 +169,7 @@ __device__ __forceinline__ double wave_max(double v)
 // division each; up to kWeightsOneWave points (strips have some eight) ONE wave
 // goes through them without barriers. 14 lines of 114 points: a second stage of
 // 257^2 points with kept factors took 2.1 ms with the systems solved on the host
-// and takes 0.45 ms.
+// and takes 0.35 ms.
 constexpr int kWeightsThreads = 1024, kWeightsOneWave = 16;
 template <bool ONE>
 __device__ __forceinline__ void weights_sync()
@@ -830,7 +830,7 @@ __global__ void __launch_bounds__(256) stage2_apply_kernel(const Stage2Grid g, c
 // ones are factored by the banded LU. The LU's chain of w L dependent
 // pivots, one workgroup a subdomain, becomes 1 + log2 L levels whose rows are
 // independent. Four strips of 63 x 255 unknowns: 39.9 ms with the LU and the
-// solutions for unit boundary values that it was kept as, 0.49 ms now; with
+// solutions for unit boundary values that it was kept as, 0.50 ms now; with
 // the factors kept 0.26 and 0.12 ms. What bounds a level is the inversion
 // (24 us: 64 dependent pivots) and the products on the FP64 matrix cores
 // (9 us; 37 us where the rows are several per CU). Blocks are padded by the
@@ -977,7 +977,7 @@ __device__ __forceinline__ Acc4 cr_residual_tile(const double *D, const double *
 // LU's, strips of 63 x 255 unknowns, c varying and c = 0 throughout: 3.7 and 7.4
 // without, 0.7 and 2.1 with the steps alone, 0.6 and 1.2 so; steps at fewer
 // levels 0.8 to 1.3, exact sums at all of them no better. A new operator on
-// 257^2 points takes 0.49 ms, 0.44 without, 0.57 with exact sums at all levels.)
+// 257^2 points takes 0.50 ms, 0.44 without, 0.57 with exact sums at all levels.)
 constexpr int kCrNewtonLevels = 4;
 template <int WP, bool FIRST>
 __global__ void __launch_bounds__(kCrThreads) stage2_cr_eliminate_kernel(const SubBox *boxes, const Stage2Cr *tab,
